@@ -245,14 +245,18 @@ int mudiff_matvec(mudiff_t h, int R, const void* x, void* y, int op,
  * threads) race.  Errors: MUDIFF_ERR_INVALID (as mudiff_matvec, or R >= 8 with
  * N_p <= 31: use mudiff_matvec), MUDIFF_ERR_NOMEM (the apply needs more scratch
  * than the array holds: about 16 R sum_p (2N_p+1) ceil((M-1)/64) bytes on the
- * one-lane path), MUDIFF_ERR_DEVICE. */
+ * one-lane path; for differing orders ceil((M-1)/c) partial sums a row, c the
+ * column disks per pass of the LDS-staged kernel, also where the other kernel
+ * runs), MUDIFF_ERR_DEVICE. */
 #define MUDIFF_NOALLOC_SCRATCH_MB 64
 int mudiff_matvec_noalloc(mudiff_t h, int R, const void* x, void* y, int op, void* stream);
 
 /* Kernel configuration of the R-column operator apply, as chosen on this
  * handle (host outputs; any pointer may be NULL):
  *   kind       0 one lane per pair (uniform N_p <= 12, R < 8), 1 FP64-MFMA
- *              work queue (R >= 8, N_p <= 31), 2 generic LDS-staged kernel,
+ *              work queue (R >= 8, N_p <= 31), 2 any orders (one lane per pair
+ *              in blocks of outputs for N_p <= 31 and enough disks, else the
+ *              LDS-staged kernel),
  *              3 circulant form on the FP64 matrix cores for the well-separated
  *              pairs and the MFMA work queue for the close ones
  *   ct, rp     MFMA tile: 8*ct right-hand sides x rp row disks per work item

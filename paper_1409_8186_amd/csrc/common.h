@@ -85,6 +85,12 @@ struct DevView {
   int lane_N;
   cplx* lt;
   const int64_t* ltoff;       // [M_all]
+  // Other batches with N_p <= PAIRS_NMAX (lord non-NULL, lane_N = -1): the same
+  // records, every instance's column disks ordered by decreasing N (lord: the
+  // disk at each position, instance by instance; lpos: position of each disk in
+  // its instance), the row disk itself included as an unused lane.
+  const int32_t* lord = nullptr;  // [M_all]
+  const int32_t* lpos = nullptr;  // [M_all]
   // Operator set by mudiff_set_operator, or NULL for the built-in single layer
   // (EFIE).  Per unknown: the column factor of the off-diagonal blocks, row
   // factor / diagonal, row factor, diagonal, right-hand-side factor (raw and
@@ -117,6 +123,9 @@ struct DevView {
 // All the kernel needs before its vector loads comes from this one record.
 #define LANE_ITEM_INTS 16
 #define LANE_NMAX 12
+// Largest order of the one-lane-per-pair kernel for any orders: its input panel
+// [2 N + 1][65] of 64 column disks fits 64 KB of LDS.
+#define PAIRS_NMAX 31
 
 // Column c = b * R + r of a packed [B][R][N_b] vector starts at
 // R * imode[b] + r * N_b.
@@ -135,20 +144,25 @@ __host__ __device__ __forceinline__ int64_t pair_index(const int64_t* idisk, con
 // ------------------------------------------------------------------ host side
 struct MatvecPlan {
   bool ready = false;
-  int lane = 0;                  // one-lane-per-pair kernel
-  int waves = 1;                 // waves per workgroup of the one-lane-per-pair kernel
+  int lane = 0;                  // chunk partial sums: LANE_UNIFORM, LANE_PAIRS, or 0 (generic)
   int Bt = 0;                   // outputs per thread of the generic kernel
-  int spec_N = -1;              // >= 0: uniform-N specialised kernel
+  int spec_N = -1;              // >= 0: the uniform N of LANE_UNIFORM
+  bool wide = false;            // LANE_PAIRS: blocks of up to PAIRS_BT_WIDE outputs
   int zs = 0, ts = 0;            // LDS row strides (z rows, symbol rows)
   int ppcap = 1;                 // most column disks staged per pass
   int n_items = 0;
   size_t lds_bytes = 0;
   int64_t part_total = 0;       // complex partials per right-hand side
+  int64_t row_part = 0;         // the same for the LDS-staged kernel's chunks
   int32_t* d_items = nullptr;   // [n_items][4] : p, chunk, q_begin, q_end (generic);
-                                // [n_items][LANE_ITEM_INTS] on the one-lane path
+                                // [n_items][LANE_ITEM_INTS] (LANE_UNIFORM),
+                                // [n_items][PAIRS_ITEM_INTS] (LANE_PAIRS)
+  int32_t* d_tasks = nullptr;   // LANE_PAIRS: [.][2] row disk, first output << 8 | outputs
   int32_t* d_nchunk = nullptr;  // [M_all]
   int64_t* d_partoff = nullptr; // [M_all]
 };
+
+enum { LANE_UNIFORM = 1, LANE_PAIRS = 2 };
 
 // MFMA apply tile choice: CT sub-tiles of 8 right-hand sides, RP row disks per
 // work item (RP * CT waves), column-disk segment length QS (0: whole
@@ -196,6 +210,7 @@ struct mudiff_ctx {
   int64_t N_all = 0, P_all = 0, T_all = 0, D_all = 0;
   std::vector<int64_t> idisk, imode, ipair, moff, toff, dtab, ltoff;
   std::vector<int32_t> N, inst;
+  std::vector<int32_t> lord;    // column order of the pair records (empty: uniform N or none)
   std::vector<double> k, cx, cy, a;
   DevView dv{};
   void* ws = nullptr;
@@ -203,6 +218,9 @@ struct mudiff_ctx {
   // schedule area inside the tables workspace
   char* sched_base = nullptr;
   size_t sched_bytes = 0;
+  // no H_nu(k b_pq) that k_apply_pairs steps through (orders up to twice the
+  // instance's largest, whatever the pair's own) overflows
+  bool pairs_ok = true;
   MatvecPlan plan;
   int64_t plan_part = -1;       // partial sums per right-hand side of the plan
   bool mfma_enabled = true;     // multi-RHS applies on FP64 MFMA
@@ -398,11 +416,14 @@ void apply_forget_upload(mudiff_ctx* h);
 // Wait until the last schedule upload has read its host vectors (before they
 // are rebuilt or released).
 void sched_wait(mudiff_ctx* h);
-// Lane-record layout of the one-lane-per-pair apply: total size in complex
-// values (0 when N is not uniform or out of range), the common N, and per disk
-// the offset of its first chunk.
+// Lane-record layout of the one-lane-per-pair applies: total size in complex
+// values (0 for orders out of range), the common N (-1: orders differ or exceed
+// LANE_NMAX), and per disk the offset of its first chunk.  With differing orders
+// `lord` receives the column order of every instance (else it is left empty).
+// (pairs_batch: whether such a batch takes them at all.)
+bool pairs_batch(int B, const int64_t* disk_off, const int32_t* n_modes);
 int64_t lane_layout(int B, const int64_t* disk_off, const int32_t* n_modes, int* lane_N,
-                    std::vector<int64_t>* ltoff);
+                    std::vector<int64_t>* ltoff, std::vector<int32_t>* lord = nullptr);
 int ensure_plan(mudiff_ctx* h, hipStream_t s);
 // Schedule for R applies made current (one-lane/generic plan, or the MFMA
 // schedule uploaded into `scratch`, the apply scratch later passed as `part`).
@@ -416,7 +437,7 @@ int prepare_apply(mudiff_ctx* h, int R, const cplx* x, cplx* y, cplx* scratch, h
 int apply_set_tail(mudiff_ctx* h, int R, bool tail, cplx* scratch, hipStream_t s,
                    const int32_t* cols);
 struct PlanHost;
-void make_plan(int B, const int64_t* idisk, const int32_t* N, PlanHost& P);
+void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHost& P);
 size_t plan_sched_bytes(const PlanHost& P, int M);
 
 int launch_rhs(mudiff_ctx* h, int R, const double* beta, cplx* out, int precond, int point,

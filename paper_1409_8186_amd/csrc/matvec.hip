@@ -272,6 +272,167 @@ __global__ __launch_bounds__(64) void k_apply_lane(
   }
 }
 
+// ------------------------------------------------------------------ one lane per pair, any orders
+// Few right-hand sides on a batch whose orders differ (or exceed LANE_NMAX), N_p
+// <= PAIRS_NMAX (pairs_batch).  As in k_apply_lane a lane works on one ordered
+// pair and builds its symbols from the pair's 64-byte record by the recurrences
+// of H_nu and e^{i nu alpha}, so no symbol row is read; but a wave takes a block
+// of consecutive outputs m of its row disk, so that outputs and inputs fit the
+// registers at any order: step nu moves a window z_{m+-nu} of the block's inputs
+// by one mode (one new entry from the panel [n][column disk] of the workgroup's
+// 64 column disks in LDS) and adds t_{+-nu} times the window.  The column disks
+// are ordered by decreasing N, so that the lanes of a wave walk about the same
+// number of modes.  A workgroup scales and stages its panel once, then its waves
+// take (row disk, block) tasks from a counter in LDS until none is left: no
+// barrier, no fence and no uneven rows inside.
+// Bound by FP64 issue: a step costs 4 multiply-adds per output plus 12 for the
+// recurrences and the symbol, and the window's ends add BT - 1 idle columns, so
+// blocks are as wide as the registers allow: up to 14 outputs at two waves per
+// SIMD, or 8 at three where the launch has too few tasks to fill the chip.
+// 1,000 disks of N_p 13..20, one right-hand side (9.9 GFLOP): 3,480 us with the
+// LDS-staged kernel (each multiply-add read 1.25 LDS values, rows ended in
+// agent-scope fences), 368 us with 8 outputs, 352 us with 14 (28 TFLOP/s, vector
+// units busy 77% at the 2.0 GHz that this load runs at).
+#define PAIRS_ITEM_INTS 8
+#define PAIRS_THREADS 256
+#define PAIRS_BT_NARROW 8
+#define PAIRS_BT_WIDE 14
+#define PAIRS_LD 65  // LDS row stride (complex): consecutive modes of a disk in different banks
+
+// One direction of the block's sums: steps nu = 1..top of acc_i += t_{+-nu}
+// z_{m0+i+-nu}, t_{+-nu} = H_nu E^nu with E = e^{i alpha} upward and -e^{-i alpha}
+// downward.  The window w is a ring: after step nu entry i sits in slot
+// (i + nu) mod BT (upward) or (i - nu) mod BT.
+template <int BT, bool UP, class Z>
+__device__ __forceinline__ void pairs_walk(cplx (&acc)[BT], cplx (&w)[BT], const Z& zat, int m0, int top,
+                                           cplx Hm, cplx H, cplx E, double r2) {
+  cplx P = E;
+  double nf = 1.0;
+  for (int nb = 0; nb < top; nb += BT) {
+#pragma unroll
+    for (int k = 1; k <= BT; ++k) {
+      const int nu = nb + k;
+      if (nu > top) return;
+      w[UP ? (k - 1) % BT : (BT - k) % BT] = zat(UP ? m0 + BT - 1 + nu : m0 - nu);
+      const cplx t = cmul(H, P);
+#pragma unroll
+      for (int i = 0; i < BT; ++i) cmac(acc[i], t, w[(UP ? i + k : i + BT - k) % BT]);
+      const double c = nf * r2;
+      const cplx Hn = cmk(fma(H.x, c, -Hm.x), fma(H.y, c, -Hm.y));
+      Hm = H;
+      H = Hn;
+      P = cmul(P, E);
+      nf += 1.0;
+    }
+  }
+}
+
+// One task: outputs m0 .. m0 + nval - 1 of a row disk, summed over the wave's
+// pairs, into pr (real and imaginary parts in turn), added to it unless `first`.
+template <int BT>
+__device__ __forceinline__ void pairs_block(const cplx* zl, int Nm, int lane, bool ok, int m0, int nval,
+                                            const cplx* __restrict__ rec, double* pr, bool first) {
+  constexpr int NV = 2 * BT <= 16 ? 16 : 32;
+  constexpr int SH = NV == 16 ? 2 : 1;  // 6 - log2 NV
+  cplx acc[BT];
+#pragma unroll
+  for (int i = 0; i < BT; ++i) acc[i] = cmk(0.0, 0.0);
+  if (ok) {
+    // z_n of this lane's disk; modes beyond the panel read its last row, zeros (n is wave-uniform)
+    const unsigned last = 2 * Nm + 1;
+    auto zat = [&](int n) { return zl[min((unsigned)(n + Nm), last) * PAIRS_LD + lane]; };
+    const cplx h0 = rec[0], h1 = rec[LANE_CHUNK], e = rec[2 * LANE_CHUNK];
+    const double r2 = rec[3 * LANE_CHUNK].x;
+    cplx w[BT];
+#pragma unroll
+    for (int i = 0; i < BT; ++i) {
+      w[i] = zat(m0 + i);
+      cmac(acc[i], h0, w[i]);
+    }
+    pairs_walk<BT, true>(acc, w, zat, m0, Nm - m0, h0, h1, e, r2);
+#pragma unroll
+    for (int i = 0; i < BT; ++i) w[i] = zat(m0 + i);
+    pairs_walk<BT, false>(acc, w, zat, m0, m0 + nval - 1 + Nm, h0, h1, cmk(-e.x, e.y), r2);
+  }
+  double val[NV];
+#pragma unroll
+  for (int i = 0; i < NV / 2; ++i) {
+    val[2 * i] = i < BT ? acc[i < BT ? i : 0].x : 0.0;
+    val[2 * i + 1] = i < BT ? acc[i < BT ? i : 0].y : 0.0;
+  }
+  lane_reduce_scatter<NV>(val, lane);
+  const int vi = lane >> SH;
+  if ((lane & ((1 << SH) - 1)) == 0 && vi < 2 * nval) pr[vi] = first ? val[0] : pr[vi] + val[0];
+}
+
+// Item: instance, first chunk of 64 column disks, chunks, tasks [t0, t1), first
+// disk, partial-sum segment, disks of the instance.
+template <bool WIDE>
+__global__ __launch_bounds__(PAIRS_THREADS, WIDE ? 2 : 3) void k_apply_pairs(
+    DevView v, int R, const cplx* __restrict__ x, cplx* __restrict__ part, int64_t part_total,
+    const int32_t* __restrict__ items, const int32_t* __restrict__ tasks,
+    const int64_t* __restrict__ partoff, const int32_t* __restrict__ active) {
+  extern __shared__ cplx lds[];  // [2 Nm + 2][PAIRS_LD], the last row zeros
+  __shared__ int s_next;
+  const int r = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int32_t* it = items + (int64_t)PAIRS_ITEM_INTS * blockIdx.x;
+  const int b = it[0], c0 = it[1], nc = it[2], t0 = it[3], t1 = it[4], seg = it[6], Mb = it[7];
+  const int64_t d0 = it[5];
+  if (active && active[b * R + r] == 0) return;
+  const int64_t i0 = v.imode[b];
+  const cplx* __restrict__ xc = x + col_base(v.imode, b, R, r);
+  for (int c = c0; c < c0 + nc; ++c) {
+    const int cnt = min(LANE_CHUNK, Mb - LANE_CHUNK * c);
+    const int32_t* __restrict__ ord = v.lord + d0 + (int64_t)LANE_CHUNK * c;
+    const int Nm = v.N[ord[0]], rows = 2 * Nm + 1;
+    __syncthreads();  // the previous chunk's panel is no longer read
+    if (tid == 0) s_next = t0;
+    for (int e = tid; e < cnt * rows; e += PAIRS_THREADS) {
+      const int k = e / rows, n = e - (e / rows) * rows;  // modes of a disk: coalesced
+      const int q = ord[k];
+      const int Nq = v.N[q], u = n - Nm + Nq;
+      cplx z = cmk(0.0, 0.0);
+      if (u >= 0 && u <= 2 * Nq) {
+        const int64_t iq = v.moff[q] + u;
+        z = col_scale(v, i0 + iq, xc[iq]);
+      }
+      lds[n * PAIRS_LD + k] = z;
+    }
+    if (tid < LANE_CHUNK) lds[rows * PAIRS_LD + tid] = cmk(0.0, 0.0);
+    __syncthreads();
+    const int q = lane < cnt ? ord[lane] : -1;
+    for (;;) {
+      int t = 0;
+      if (lane == 0) t = atomicAdd(&s_next, 1);
+      t = __builtin_amdgcn_readfirstlane(t);
+      if (t >= t1) break;
+      const int p = tasks[2 * t], ms = tasks[2 * t + 1] >> 8, bt = tasks[2 * t + 1] & 255;
+      const int Np = v.N[p], np = 2 * Np + 1;
+      const int nval = min(bt, np - ms);
+      const bool ok = q >= 0 && q != p;
+      const cplx* __restrict__ rec = v.lt + v.ltoff[p] + (int64_t)c * (LANE_CHUNK * LANE_REC) + lane;
+      double* pr = reinterpret_cast<double*>(part + (int64_t)r * part_total + partoff[p] +
+                                             (int64_t)seg * np + ms);
+      const int m0 = ms - Np;
+      const bool first = c == c0;
+      // widths of pairs_width
+#define PAIRS_CASE(W) case W: pairs_block<W>(lds, Nm, lane, ok, m0, nval, rec, pr, first); break;
+      if constexpr (WIDE) {
+        switch (bt) {
+          PAIRS_CASE(7) PAIRS_CASE(8) PAIRS_CASE(9) PAIRS_CASE(10) PAIRS_CASE(11) PAIRS_CASE(12) PAIRS_CASE(13)
+          default: pairs_block<PAIRS_BT_WIDE>(lds, Nm, lane, ok, m0, nval, rec, pr, first); break;
+        }
+      } else {
+        switch (bt) {
+          PAIRS_CASE(5) PAIRS_CASE(6) PAIRS_CASE(7)
+          default: pairs_block<PAIRS_BT_NARROW>(lds, Nm, lane, ok, m0, nval, rec, pr, first); break;
+        }
+      }
+#undef PAIRS_CASE
+    }
+  }
+}
+
 // y = finalize(sum over the chunks of row p of the partial sums), one thread
 // per output row, chunks added in order.
 __global__ void k_apply_finish(DevView v, int R, const cplx* __restrict__ x, cplx* __restrict__ y,
@@ -1378,8 +1539,7 @@ struct Variant {
 
 // LDS-staged kernels: generic (nspec = -1) and uniform-N specialisations
 const Variant kVariants[] = {
-    {4, -1, k_apply<4, -1>}, {5, -1, k_apply<5, -1>}, {6, -1, k_apply<6, -1>},
-    {8, -1, k_apply<8, -1>}, {5, 12, k_apply<5, 12>}, {4, 15, k_apply<4, 15>},
+    {4, -1, k_apply<4, -1>}, {4, 15, k_apply<4, 15>},
 };
 
 const Variant* find_variant(int bt, int nspec) {
@@ -1420,13 +1580,14 @@ const LaneVariant* find_lane(int n) {
 // Host plan of the operator apply: kernel variant, work items and partial-sum
 // layout, from the batch description alone (also used to size workspaces).
 struct PlanHost {
-  int lane = 0;  // 1: one-lane-per-pair kernel (uniform N = nspec)
+  int lane = 0;  // LANE_UNIFORM (N = nspec), LANE_PAIRS, or 0: LDS-staged kernel
   int item_ints = 4;
-  int waves = 1;
+  bool wide = false;  // k_apply_pairs<true>
   int bt = 4, nspec = -1, zs = 0, ts = 0, ppcap = 1;
   size_t lds = 0;
   int64_t part = 0;
-  std::vector<int32_t> items, nch;
+  int64_t row_part = 0;  // partial sums of the LDS-staged kernel (bounds mudiff_matvec_noalloc)
+  std::vector<int32_t> items, nch, tasks;
   std::vector<int64_t> poff;
 };
 
@@ -1450,9 +1611,83 @@ static void choose_variant(int M, const int32_t* N, int* bt, int* nspec) {
 
 #define APPLY_LDS_BUDGET (64 * 1024)
 
-void make_plan(int B, const int64_t* idisk, const int32_t* N, PlanHost& P) {
+// Schedule of k_apply_pairs.  Tasks: the rows of an instance by decreasing N, each
+// cut into blocks of equal width, at most PAIRS_BT_WIDE outputs, or
+// PAIRS_BT_NARROW where wide blocks make fewer tasks than the 3,072 waves that
+// narrow blocks keep resident (1,000 disks: 368 us narrow, 352 wide; 400: 96 and
+// 90; at 200, too few tasks, 40 narrow).  Items: 64 column disks x a run of tasks,
+// four tasks (one per wave) up to the point where the launch is PAIRS_WGS
+// workgroups, longer runs beyond (1,000 disks: 371 us with 3,000, 373 with 1,500,
+// 468 against 427 with 740, a single round of resident workgroups).  A row keeps
+// one partial sum per 64 column disks; where those would exceed PAIRS_PART_MAX per
+// right-hand side an item walks several chunks, at least `qc` column disks, the
+// widest item of the LDS-staged kernel (so the scratch never exceeds that kernel's,
+// nor the bound that mudiff_matvec_noalloc works under).
+#define PAIRS_WGS 3000
+#define PAIRS_PART_MAX ((int64_t)1 << 18)  // complex values: 4 MiB
+#define PAIRS_WIDE_TASKS 3072
+// Block width that k_apply_pairs is compiled for, at least w.
+static int pairs_width(int w, bool wide) { return std::max(w, wide ? 7 : 5); }
+
+static void make_pairs_plan(int B, const int64_t* idisk, const int32_t* N, int64_t qc, PlanHost& P) {
+  P.lane = LANE_PAIRS;
+  P.item_ints = PAIRS_ITEM_INTS;
+  int lane_N = -1, nmax = 0;
+  std::vector<int32_t> ord;
+  lane_layout(B, idisk, N, &lane_N, nullptr, &ord);
+  int64_t part1 = 0;  // partial sums at one chunk per segment
+  for (int b = 0; b < B; ++b) {
+    const int64_t d0 = idisk[b], Mb = idisk[b + 1] - d0;
+    const int64_t nch = Mb > 1 ? (Mb + LANE_CHUNK - 1) / LANE_CHUNK : 0;
+    for (int64_t p = d0; p < d0 + Mb; ++p) {
+      const int np = 2 * N[p] + 1;
+      part1 += std::max<int64_t>(nch, 1) * np;
+      nmax = std::max(nmax, (int)N[p]);
+    }
+  }
+  const int64_t K = part1 <= PAIRS_PART_MAX ? 1 : qc / LANE_CHUNK + 1;  // chunks per segment
+  auto count = [&](int bt) {  // tasks of all segments with blocks of at most bt outputs
+    int64_t n = 0;
+    for (int b = 0; b < B; ++b) {
+      const int64_t d0 = idisk[b], Mb = idisk[b + 1] - d0;
+      const int64_t nch = Mb > 1 ? (Mb + LANE_CHUNK - 1) / LANE_CHUNK : 0;
+      for (int64_t p = d0; p < d0 + Mb; ++p) n += (nch + K - 1) / K * ((2 * N[p] + bt) / bt);
+    }
+    return n;
+  };
+  P.wide = count(PAIRS_BT_WIDE) >= PAIRS_WIDE_TASKS;
+  const int btmax = P.wide ? PAIRS_BT_WIDE : PAIRS_BT_NARROW;
+  const int64_t run = std::max<int64_t>(4, (count(btmax) + PAIRS_WGS - 1) / PAIRS_WGS);
+  P.lds = (size_t)(2 * nmax + 2) * PAIRS_LD * 16;  // 66,560 bytes at PAIRS_NMAX
+  for (int b = 0; b < B; ++b) {
+    const int64_t d0 = idisk[b], Mb = idisk[b + 1] - d0;
+    const int64_t nch = Mb > 1 ? (Mb + LANE_CHUNK - 1) / LANE_CHUNK : 0, nseg = (nch + K - 1) / K;
+    const int64_t tb = (int64_t)P.tasks.size() / 2;
+    for (int64_t k = d0; k < d0 + Mb; ++k) {
+      const int p = ord[(size_t)k], np = 2 * N[p] + 1;
+      P.nch[p] = (int32_t)nseg;
+      P.poff[p] = P.part;
+      P.part += std::max<int64_t>(nseg, 1) * np;
+      const int nblk = (np + btmax - 1) / btmax, w = pairs_width((np + nblk - 1) / nblk, P.wide);
+      for (int ms = 0; ms < np && nch > 0; ms += w) {
+        P.tasks.push_back(p);
+        P.tasks.push_back((ms << 8) | w);
+      }
+    }
+    const int64_t te = (int64_t)P.tasks.size() / 2;
+    for (int64_t sg = 0; sg < nseg; ++sg)
+      for (int64_t t = tb; t < te; t += run) {
+        const int64_t rec[PAIRS_ITEM_INTS] = {b, sg * K, std::min(K, nch - sg * K), t, std::min(te, t + run),
+                                              d0, sg, Mb};
+        for (int64_t w : rec) P.items.push_back((int32_t)w);
+      }
+  }
+}
+
+void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHost& P) {
   const int M = (int)idisk[B];
   P.items.clear();
+  P.tasks.clear();
   P.nch.assign(M, 0);
   P.poff.assign(M, 0);
   P.part = 0;
@@ -1461,7 +1696,7 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, PlanHost& P) {
   for (int p = 1; p < M; ++p)
     if (N[p] != N[0]) uniform = false;
   if (uniform && N[0] <= LANE_NMAX && find_lane(N[0])) {
-    P.lane = 1;
+    P.lane = LANE_UNIFORM;
     P.item_ints = LANE_ITEM_INTS;
     P.nspec = N[0];
     const int np = 2 * N[0] + 1;
@@ -1508,13 +1743,30 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, PlanHost& P) {
   P.zs = ((2 * nmax + 1) + bt - 1) / bt * bt;
   P.ts = P.zs + P.zs - 1;
   P.ppcap = std::max(1, (int)(APPLY_LDS_BUDGET / ((size_t)(P.zs + P.ts) * 16)));
+  // column disks per item of a row of np modes
+  auto cols_of = [&](int np) {
+    const int L = (np + bt - 1) / bt;
+    return (int64_t)std::max(1, std::min(APPLY_THREADS / L, P.ppcap)) * APPLY_NPASS;
+  };
+  if (pairs && pairs_batch(B, idisk, N)) {
+    make_pairs_plan(B, idisk, N, cols_of(1), P);
+    P.row_part = 0;
+    for (int b = 0; b < B; ++b) {
+      const int64_t Mb = idisk[b + 1] - idisk[b];
+      for (int64_t p = idisk[b]; p < idisk[b + 1]; ++p) {
+        const int np = 2 * N[p] + 1;
+        const int64_t qc = cols_of(np);
+        P.row_part += std::max<int64_t>(1, (Mb - 1 + qc - 1) / qc) * np;
+      }
+    }
+    return;
+  }
   for (int b = 0; b < B; ++b) {
     const int64_t d0 = idisk[b], Mb = idisk[b + 1] - d0;
     for (int64_t p = d0; p < d0 + Mb; ++p) {
       const int np = 2 * N[p] + 1;
       const int L = (np + bt - 1) / bt;
-      const int pp = std::max(1, std::min(APPLY_THREADS / L, P.ppcap));
-      const int64_t qc = (int64_t)pp * APPLY_NPASS;
+      const int64_t qc = cols_of(np);
       const int64_t n = std::max<int64_t>(1, (Mb - 1 + qc - 1) / qc);
       P.nch[p] = (int32_t)n;
       P.poff[p] = P.part;
@@ -1526,6 +1778,7 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, PlanHost& P) {
         P.items.push_back((int32_t)jb);
         P.items.push_back((int32_t)je);
       }
+      const int64_t pp = qc / APPLY_NPASS;
       P.lds = std::max(P.lds, (size_t)pp * (P.zs + P.ts) * 16);
       P.lds = std::max(P.lds, (size_t)pp * L * bt * 16);
     }
@@ -1533,26 +1786,34 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, PlanHost& P) {
 }
 
 size_t plan_sched_bytes(const PlanHost& P, int M) {
-  return align256(P.items.size() * 4) + align256((size_t)M * 4) + align256((size_t)M * 8) + 256;
+  return align256(P.items.size() * 4) + align256((size_t)M * 4) + align256((size_t)M * 8) +
+         align256(P.tasks.size() * 4) + 256;
 }
 
 size_t sched_bytes_for(int B, const int64_t* disk_off, const int32_t* n_modes) {
-  PlanHost H;
-  make_plan(B, disk_off, n_modes, H);
-  return plan_sched_bytes(H, (int)disk_off[B]);
+  size_t bytes = 0;
+  for (bool pairs : {false, true}) {  // which of the two also depends on the centers
+    PlanHost H;
+    make_plan(B, disk_off, n_modes, pairs, H);
+    bytes = std::max(bytes, plan_sched_bytes(H, (int)disk_off[B]));
+  }
+  return bytes;
 }
 
 int ensure_plan(mudiff_ctx* h, hipStream_t s) {
   if (h->plan.ready) return MUDIFF_OK;
   PlanHost H;
-  make_plan(h->B, h->idisk.data(), h->N.data(), H);
-  if (H.lds > 64 * 1024) return fail(MUDIFF_ERR_INVALID, "operator rows too long for LDS");
+  make_plan(h->B, h->idisk.data(), h->N.data(), h->pairs_ok, H);
+  if (H.lds > (H.lane ? 80 : 64) * 1024) return fail(MUDIFF_ERR_INVALID, "operator rows too long for LDS");
   if (plan_sched_bytes(H, h->M_all) > h->sched_bytes)
     return fail(MUDIFF_ERR_INVALID, "schedule area too small");
   MatvecPlan& P = h->plan;
   P.d_items = (int32_t*)h->sched_base;
   P.d_nchunk = (int32_t*)(h->sched_base + align256(H.items.size() * 4));
   P.d_partoff = (int64_t*)((char*)P.d_nchunk + align256(h->M_all * 4));
+  P.d_tasks = (int32_t*)((char*)P.d_partoff + align256((size_t)h->M_all * 8));
+  if (!H.tasks.empty())
+    HIP_TRY(hipMemcpyAsync(P.d_tasks, H.tasks.data(), H.tasks.size() * 4, hipMemcpyHostToDevice, s));
   if (!H.items.empty())
     HIP_TRY(hipMemcpyAsync(P.d_items, H.items.data(), H.items.size() * 4, hipMemcpyHostToDevice, s));
   HIP_TRY(hipMemcpyAsync(P.d_nchunk, H.nch.data(), h->M_all * 4, hipMemcpyHostToDevice, s));
@@ -1565,9 +1826,10 @@ int ensure_plan(mudiff_ctx* h, hipStream_t s) {
   P.ts = H.ts;
   P.ppcap = H.ppcap;
   P.part_total = H.part;
+  P.wide = H.wide;
+  P.row_part = H.lane == LANE_PAIRS ? H.row_part : H.part;
   P.lds_bytes = H.lds;
   P.n_items = (int)(H.items.size() / H.item_ints);
-  P.waves = H.waves;
   P.ready = true;
   return MUDIFF_OK;
 }
@@ -1579,7 +1841,7 @@ size_t apply_scratch_bytes(mudiff_ctx* h, int R) {
   if (use_mfma(h, R)) return align256(mfma_scratch_bytes(h, R)) + counters;
   if (h->plan_part < 0) {
     PlanHost H;
-    make_plan(h->B, h->idisk.data(), h->N.data(), H);
+    make_plan(h->B, h->idisk.data(), h->N.data(), h->pairs_ok, H);
     h->plan_part = H.part;
   }
   return align256((size_t)R * h->plan_part * 16) + counters;
@@ -1592,6 +1854,24 @@ int prepare_apply(mudiff_ctx* h, int R, const cplx* x, cplx* y, cplx* scratch, h
   return ensure_plan(h, s);
 }
 
+// Chunk partial sums of the one-lane-per-pair kernels.
+static int launch_lanes(mudiff_ctx* h, int R, const cplx* x, cplx* part, const int32_t* active,
+                        hipStream_t s) {
+  const MatvecPlan& P = h->plan;
+  if (P.n_items == 0) return MUDIFF_OK;
+  if (P.lane == LANE_PAIRS) {
+    hipLaunchKernelGGL(P.wide ? k_apply_pairs<true> : k_apply_pairs<false>, dim3(P.n_items, R), dim3(PAIRS_THREADS), P.lds_bytes, s, h->dv, R, x,
+                       part, P.part_total, P.d_items, P.d_tasks, P.d_partoff, active);
+  } else {
+    const LaneVariant* lv = find_lane(P.spec_N);
+    if (!lv) return fail(MUDIFF_ERR_INVALID, "no operator kernel variant");
+    hipLaunchKernelGGL(h->dv.op_col ? lv->fn_op : lv->fn, dim3(P.n_items, R), dim3(64), 0, s, h->dv, R,
+                       x, part, P.part_total, P.d_items, active);
+  }
+  HIP_TRY(hipGetLastError());
+  return MUDIFF_OK;
+}
+
 int apply_operator_split(mudiff_ctx* h, int R, const cplx* x, cplx* y, int op, cplx* part,
                          int32_t* counters, const int32_t* active, hipStream_t s,
                          bool* pending) {
@@ -1601,13 +1881,7 @@ int apply_operator_split(mudiff_ctx* h, int R, const cplx* x, cplx* y, int op, c
   if (st != MUDIFF_OK) return st;
   const MatvecPlan& P = h->plan;
   if (P.lane) {
-    const LaneVariant* lv = find_lane(P.spec_N);
-    if (!lv) return fail(MUDIFF_ERR_INVALID, "no operator kernel variant");
-    if (P.n_items > 0) {
-      hipLaunchKernelGGL(h->dv.op_col ? lv->fn_op : lv->fn, dim3(P.n_items, R), dim3(64), 0, s,
-                         h->dv, R, x, part, P.part_total, P.d_items, active);
-      HIP_TRY(hipGetLastError());
-    }
+    if ((st = launch_lanes(h, R, x, part, active, s)) != MUDIFF_OK) return st;
     *pending = true;  // the chunk sums still have to be added and finalised
     return MUDIFF_OK;
   }
@@ -1629,13 +1903,7 @@ int apply_operator(mudiff_ctx* h, int R, const cplx* x, cplx* y, int op, cplx* p
   prof_mark(h, s, 2);
   prof_mark(h, s, 3);
   if (P.lane) {
-    const LaneVariant* lv = find_lane(P.spec_N);
-    if (!lv) return fail(MUDIFF_ERR_INVALID, "no operator kernel variant");
-    if (P.n_items > 0) {
-      hipLaunchKernelGGL(h->dv.op_col ? lv->fn_op : lv->fn, dim3(P.n_items, R), dim3(64), 0, s,
-                         h->dv, R, x, part, P.part_total, P.d_items, active);
-      HIP_TRY(hipGetLastError());
-    }
+    if ((st = launch_lanes(h, R, x, part, active, s)) != MUDIFF_OK) return st;
     prof_mark(h, s, 4);
     const int64_t total = (int64_t)R * h->N_all;
     hipLaunchKernelGGL(k_apply_finish, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
@@ -1752,8 +2020,8 @@ extern "C" int mudiff_apply_config(mudiff_t h, int R, int* kind, int* ct, int* r
     if (g != h->mfma_time_ms.end()) tm = g->second;
   } else {
     PlanHost H;
-    make_plan(h->B, h->idisk.data(), h->N.data(), H);
-    k = H.lane ? 0 : 2;
+    make_plan(h->B, h->idisk.data(), h->N.data(), h->pairs_ok, H);
+    k = H.lane == LANE_UNIFORM ? 0 : 2;
   }
   if (kind) *kind = k;
   if (ct) *ct = c;
@@ -1947,8 +2215,11 @@ extern "C" int mudiff_matvec_noalloc(mudiff_t h, int R, const void* x, void* y, 
   if (!h->plan.ready) return fail(MUDIFF_ERR_INVALID, "no operator plan for this handle");
   const size_t need = apply_scratch_bytes(h, R);
   const size_t flip = op == MUDIFF_OP_LT ? align256((size_t)R * h->N_all * 16) : 0;
-  if (need + flip > NOALLOC_SCRATCH_BYTES)
-    return fail(MUDIFF_ERR_NOMEM, "the no-allocation apply needs " + std::to_string(need + flip) +
+  // the size that the call is refused by: that of the LDS-staged kernel's chunks,
+  // also where k_apply_pairs runs and needs less (or, below the limit, a little more)
+  const size_t want = align256((size_t)R * h->plan.row_part * 16) + align256((size_t)R * h->M_all * 4) + flip;
+  if (want > NOALLOC_SCRATCH_BYTES || need + flip > NOALLOC_SCRATCH_BYTES)
+    return fail(MUDIFF_ERR_NOMEM, "the no-allocation apply needs " + std::to_string(std::max(want, need + flip)) +
                                       " bytes of scratch, more than its " +
                                       std::to_string(NOALLOC_SCRATCH_BYTES));
   char* w = nullptr;

@@ -148,19 +148,23 @@ __global__ void k_pair_tables(DevView v, int64_t P_all) {
       T[n + 1].y = y;
     }
   }
-  // lane-interleaved pair records for uniform N, both orders: H_0, H_1,
-  // e^{i alpha} (alpha_qp = alpha_pq + pi) and 2 / (k b)
-  if (v.lane_N >= 0) {
+  // lane-interleaved pair records, both orders: H_0, H_1, e^{i alpha}
+  // (alpha_qp = alpha_pq + pi) and 2 / (k b)
+  if (v.lane_N >= 0 || v.lord) {
     const int64_t pc = (int64_t)LANE_CHUNK * LANE_REC;
     const cplx e = cexpi(alpha);
-    const int64_t jpq = q - v.idisk[b] - 1, jqp = p - v.idisk[b];  // q > p
+    // position of the column disk: its place in the instance without the row
+    // disk (uniform N, q > p), or in the order by decreasing N
+    const int64_t jpq = v.lord ? v.lpos[q] : q - v.idisk[b] - 1;
+    const int64_t jqp = v.lord ? v.lpos[p] : p - v.idisk[b];
     cplx* A = v.lt + v.ltoff[p] + (jpq / LANE_CHUNK) * pc + (jpq % LANE_CHUNK);
     cplx* Bq = v.lt + v.ltoff[q] + (jqp / LANE_CHUNK) * pc + (jqp % LANE_CHUNK);
     const cplx r2 = cmk(2.0 / x, 0.0);
+    const cplx h1 = S >= 1 ? T[1] : cmk(0.0, 0.0);
     A[0] = T[0];
     Bq[0] = T[0];
-    A[LANE_CHUNK] = T[1];
-    Bq[LANE_CHUNK] = T[1];
+    A[LANE_CHUNK] = h1;
+    Bq[LANE_CHUNK] = h1;
     A[2 * LANE_CHUNK] = e;
     Bq[2 * LANE_CHUNK] = cmk(-e.x, -e.y);
     A[3 * LANE_CHUNK] = r2;
@@ -179,24 +183,53 @@ __global__ void k_pair_tables(DevView v, int64_t P_all) {
 // ------------------------------------------------------------------ layout
 size_t sched_bytes_for(int B, const int64_t* disk_off, const int32_t* n_modes);
 
-// Lane-interleaved table of a uniform-N batch (1 <= N <= LANE_NMAX): returns
-// its size in complex values (0 when N is not uniform or out of range), the
-// common N, and per disk the offset of its first chunk.
+// Batches of k_apply_pairs: every N_p <= PAIRS_NMAX, and enough pairs per wave.
+// A wave fills its 64 lanes with the disks of one instance and pays the same
+// latency however few they are; below 24 disks the LDS-staged kernel, which
+// spreads one pair over many threads, is the faster one (one right-hand side:
+// 8.4 against 23 us at 6 disks, 13.4 against 14.1 at 20, 19.7 against 14.6 at
+// 28), unless the batch has so many rows that throughput counts (300 instances
+// of up to 20 disks: 168 against 120 us; 100 of up to 12: 32 against 38).
+bool pairs_batch(int B, const int64_t* disk_off, const int32_t* n_modes) {
+  int64_t mmax = 0;
+  for (int b = 0; b < B; ++b) mmax = std::max(mmax, disk_off[b + 1] - disk_off[b]);
+  for (int64_t p = 0; p < disk_off[B]; ++p)
+    if (n_modes[p] > PAIRS_NMAX) return false;
+  return mmax >= 24 || (mmax >= 15 && disk_off[B] >= 2048);
+}
+
+// Lane-interleaved pair records of a batch with one N for all disks (1 <= N <=
+// LANE_NMAX: the columns of a row are the other disks in order) or any orders
+// up to PAIRS_NMAX (the columns are all disks by decreasing N).
 int64_t lane_layout(int B, const int64_t* disk_off, const int32_t* n_modes, int* lane_N,
-                    std::vector<int64_t>* ltoff) {
+                    std::vector<int64_t>* ltoff, std::vector<int32_t>* lord) {
   const int64_t M = disk_off[B];
   *lane_N = -1;
   if (ltoff) ltoff->assign(M, 0);  // uploaded even when there is no lane table
-  for (int64_t p = 1; p < M; ++p)
-    if (n_modes[p] != n_modes[0]) return 0;
-  const int N = n_modes[0];
-  if (N < 1 || N > LANE_NMAX) return 0;
-  *lane_N = N;
+  if (lord) lord->clear();
+  bool uniform = true;
+  int nmax = 0;
+  for (int64_t p = 0; p < M; ++p) {
+    uniform &= n_modes[p] == n_modes[0];
+    nmax = std::max(nmax, (int)n_modes[p]);
+  }
+  if (uniform && nmax >= 1 && nmax <= LANE_NMAX) {
+    *lane_N = nmax;
+  } else if (!pairs_batch(B, disk_off, n_modes)) {
+    return 0;
+  } else if (lord) {
+    lord->resize(M);
+    for (int64_t p = 0; p < M; ++p) (*lord)[p] = (int32_t)p;
+    for (int b = 0; b < B; ++b)
+      std::stable_sort(lord->begin() + disk_off[b], lord->begin() + disk_off[b + 1],
+                       [&](int32_t u, int32_t w) { return n_modes[u] > n_modes[w]; });
+  }
   const int64_t per_chunk = (int64_t)LANE_CHUNK * LANE_REC;
   int64_t o = 0;
   for (int b = 0; b < B; ++b) {
     const int64_t Mb = disk_off[b + 1] - disk_off[b];
-    const int64_t nch = (Mb - 1 + LANE_CHUNK - 1) / LANE_CHUNK;
+    const int64_t ncol = *lane_N >= 0 ? Mb - 1 : (Mb > 1 ? Mb : 0);
+    const int64_t nch = (ncol + LANE_CHUNK - 1) / LANE_CHUNK;
     for (int64_t p = disk_off[b]; p < disk_off[b + 1]; ++p) {
       if (ltoff) (*ltoff)[p] = o;
       o += nch * per_chunk;
@@ -234,7 +267,7 @@ namespace {
 struct Layout {
   size_t off_cx, off_cy, off_a, off_kd, off_N, off_inst, off_moff, off_dtab, off_idisk, off_imode,
       off_ipair, off_toff, off_t, off_Jd, off_Hd, off_sJ, off_invSH, off_Ldiag, off_udisk, off_sched,
-      off_lt, off_ltoff;
+      off_lt, off_ltoff, off_lord, off_lpos;
   // circulant form (MUDIFF_TABLES_CIRCULANT)
   size_t off_cL = 0, off_cTo = 0, off_cZo = 0, off_cWo = 0, off_ctw = 0, off_cnear = 0, off_cT = 0;
   int64_t c_tw = 0, c_T = 0;  // twiddles, transformed symbols (complex values)
@@ -276,6 +309,8 @@ Layout make_layout(int B, const int64_t* disk_off, const int32_t* n_modes, int64
   const int64_t lt = lane_layout(B, disk_off, n_modes, &lane_N, nullptr);
   L.off_lt = take(lt * 16);
   L.off_ltoff = take(M * 8);
+  L.off_lord = take(M * 4);
+  L.off_lpos = take(M * 4);
   if (flags & MUDIFF_TABLES_CIRCULANT) {
     for (int b = 0; b < B; ++b) {
       const int64_t Lb = circ_len(n_modes, disk_off[b], disk_off[b + 1]);
@@ -361,10 +396,12 @@ extern "C" int mudiff_tables(int B, const int64_t* disk_off, const double* cente
     for (int64_t p = 0; p < M; ++p)
       if (n_modes[p] > 31) return fail(MUDIFF_ERR_INVALID, "the circulant form needs N_p <= 31");
   // disjointness (sec. 2): b_pq > a_p + a_q inside every instance
+  std::vector<double> dmin(B, HUGE_VAL);
   for (int b = 0; b < B; ++b)
     for (int64_t p = disk_off[b]; p < disk_off[b + 1]; ++p)
       for (int64_t q = p + 1; q < disk_off[b + 1]; ++q) {
         double d = std::hypot(centers[2 * p] - centers[2 * q], centers[2 * p + 1] - centers[2 * q + 1]);
+        dmin[b] = std::min(dmin[b], d);
         if (!(d > radii[p] + radii[q]))
           return fail(MUDIFF_ERR_OVERLAP, "disks " + std::to_string(p) + " and " +
                                                std::to_string(q) + " overlap or touch");
@@ -421,6 +458,13 @@ extern "C" int mudiff_tables(int B, const int64_t* disk_off, const double* cente
     h->ipair[b + 1] = pi;
   }
   h->toff[P_all] = to;
+  // |H_n(x)| <= about (n - 1)! (2 / x)^n / pi for x < n: log below that of 1e300
+  for (int b = 0; b < B; ++b) {
+    int nmax = 1;
+    for (int64_t p = disk_off[b]; p < disk_off[b + 1]; ++p) nmax = std::max(nmax, (int)n_modes[p]);
+    const double n = 2.0 * nmax + 1.0, x = k[b] * dmin[b];
+    if (x < n && std::lgamma(n) + n * std::log(2.0 / x) > 690.0) h->pairs_ok = false;
+  }
 
   char* base = (char*)workspace;
   h->ws = workspace;
@@ -450,7 +494,15 @@ extern "C" int mudiff_tables(int B, const int64_t* disk_off, const double* cente
   v.udisk = (int32_t*)(base + L.off_udisk);
   v.lt = (cplx*)(base + L.off_lt);
   v.ltoff = (int64_t*)(base + L.off_ltoff);
-  lane_layout(B, disk_off, n_modes, &v.lane_N, &h->ltoff);
+  lane_layout(B, disk_off, n_modes, &v.lane_N, &h->ltoff, &h->lord);
+  std::vector<int32_t> lpos(h->lord.size());
+  if (!h->lord.empty()) {
+    v.lord = (const int32_t*)(base + L.off_lord);
+    v.lpos = (const int32_t*)(base + L.off_lpos);
+    for (int b = 0; b < B; ++b)
+      for (int64_t k = disk_off[b]; k < disk_off[b + 1]; ++k)
+        lpos[h->lord[k]] = (int32_t)(k - disk_off[b]);
+  }
   {
     int dev = 0, ncu = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
@@ -542,6 +594,10 @@ extern "C" int mudiff_tables(int B, const int64_t* disk_off, const double* cente
   chk(up(v.ipair, h->ipair.data(), (B + 1) * 8), "upload ipair");
   chk(up(v.toff, h->toff.data(), (P_all + 1) * 8), "upload toff");
   chk(up(v.ltoff, h->ltoff.data(), M * 8), "upload ltoff");
+  if (!h->lord.empty()) {
+    chk(up(v.lord, h->lord.data(), M * 4), "upload lord");
+    chk(up(v.lpos, lpos.data(), M * 4), "upload lpos");
+  }
   if (h->circ) {
     chk(up(v.cL, h->cL.data(), (size_t)B * 4), "upload cL");
     chk(up(v.cTo, cTo.data(), (size_t)B * 8), "upload cTo");
