@@ -11,6 +11,8 @@
 //   e = (i/4) H_m(k r_p) e^{-i m theta_p}  (r_p, theta_p: polar coordinates of s - O_p)
 // in place of e^{i k beta_hat . O_p} e^{i m (pi/2 - beta)}, so that
 // U = sqrt(2 pi a) J_m e as for the plane wave.
+#include <algorithm>
+
 #include "bessel.h"
 #include "common.h"
 
@@ -174,6 +176,126 @@ __global__ __launch_bounds__(FF_TH* FF_DG) void k_farfield(DevView v, int R,
   }
 }
 
+// Far field of several columns: per instance the product
+//   a[r][j] = c sum_{p, m} (s_m rho^p_m[r]) (e^{i m phi_j} e^{-i k theta_j . O_p})
+// of [R x N_b] by [N_b x n_theta] on the FP64 matrix cores (v_mfma_f64_16x16x4f64:
+// lane l holds A[l % 16][l / 16], B[l / 16][l % 16], D[4 v + l / 16][l % 16]).
+// Workgroup: 16 columns x 16 angles, its NW waves splitting the disks; per k step
+// of 4 modes a wave multiplies its densities with two panels [Re | Im] of 8 angles,
+// so a complex product is two real MFMAs.  Nothing of the second factor is stored:
+// e^{i m phi} of the tile's angles is a table in LDS, and e^{-i k theta . O_p} is
+// evaluated once per disk (G = 4: by a lane group per disk, four disks at a time,
+// handed on by lane exchange), so a phase serves 16 columns instead of one.  The
+// wave sums are added in LDS in wave order.  Consecutive workgroups differ in
+// their column tile, so that an XCD keeps meeting the same columns of rho in its L2.
+typedef double ff_d4 __attribute__((ext_vector_type(4)));
+// 256 columns of 1,000 disks at 360 angles (26 GFLOP): k_farfield, where every
+// column forms its own phases, 4,810 us; 8-angle tiles 1,024 us (waiting for the
+// densities, whose 16 columns are 16 separate segments per load); 16-angle tiles
+// 760 us (34 TFLOP/s): 368 workgroups on 256 compute units, so the fuller ones run
+// two, each busy 65% of that time.
+#define FM_R 16
+#define FM_T 16
+#define FF_MFMA_N 127  // the table of phases fits 64 KB of LDS
+
+template <int NW, int G, bool OPF>
+__global__ __launch_bounds__(NW * 64) void k_farfield_mfma(DevView v, int R, const cplx* __restrict__ rho,
+                                                           int n_theta, const double* __restrict__ theta,
+                                                           cplx* __restrict__ a_out, int Nmax, int nct) {
+  extern __shared__ cplx lds[];  // E [2 Nmax + 1][FM_T], then the wave sums [NW][512] (double)
+  const int b = blockIdx.y;
+  const int r0 = (int)(blockIdx.x % nct) * FM_R, t0 = (int)(blockIdx.x / nct) * FM_T;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int j = lane & 15, kq = lane >> 4, tj = j & 7;
+  for (int e = tid; e < (2 * Nmax + 1) * FM_T; e += NW * 64) {
+    const int jt = t0 + (e & (FM_T - 1));
+    lds[e] = cexpi((e / FM_T - Nmax) * ((jt < n_theta ? theta[jt] : 0.0) - 0.5 * PI_D));
+  }
+  __syncthreads();
+  const int64_t d0 = v.idisk[b], d1 = v.idisk[b + 1], i0 = v.imode[b];
+  const double kk = v.kd[d0];
+  double st[2], ct[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    sincos(t0 + 8 * u + tj < n_theta ? theta[t0 + 8 * u + tj] : 0.0, &st[u], &ct[u]);
+  // columns past R read column r0 (their sums are not stored)
+  const cplx* __restrict__ rc = rho + col_base(v.imode, b, R, r0 + j < R ? r0 + j : r0);
+  ff_d4 acc1[2], acc2[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    acc1[u] = ff_d4{0.0, 0.0, 0.0, 0.0};
+    acc2[u] = ff_d4{0.0, 0.0, 0.0, 0.0};
+  }
+  for (int64_t p0 = d0 + G * wave; p0 < d1; p0 += G * NW) {
+    cplx epg[2];  // G = 4: lane group kq evaluates disk p0 + kq
+    const int64_t pe = min(p0 + (G == 4 ? kq : 0), d1 - 1);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) epg[u] = cexpi(-kk * (ct[u] * v.cx[pe] + st[u] * v.cy[pe]));
+#pragma unroll
+    for (int d = 0; d < G; ++d) {
+      const int64_t p = p0 + d;
+      if (p >= d1) break;
+      double eu[2], ew[2];  // this lane's part of E ep: real for j < 8, imaginary else
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const cplx ep = G == 4 ? cmk(__shfl(epg[u].x, 16 * d + j, 64), __shfl(epg[u].y, 16 * d + j, 64)) : epg[u];
+        eu[u] = j < 8 ? ep.x : ep.y;
+        ew[u] = j < 8 ? -ep.y : ep.x;
+      }
+      const int Np = v.N[p], np = 2 * Np + 1;
+      const int64_t o = v.moff[p] + kq;
+      const cplx* __restrict__ E = lds + (Nmax - Np + kq) * FM_T + tj;
+      const cplx* __restrict__ ra = rc + o;
+      const double* __restrict__ sa = v.sJ + i0 + o;
+      const cplx* __restrict__ fa = v.op_ff + i0 + o;
+      auto step = [&](int m0, bool in) {  // modes m0 + kq; `in` false: past the disk's modes
+        const int mm = in ? m0 : -kq;     // (they read mode 0 against a zero)
+        cplx a = ra[mm];
+        double f = in ? 1.0 : 0.0;
+        if constexpr (OPF) a = cmul(a, fa[mm]);
+        else f *= sa[mm];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const cplx e = E[mm * FM_T + 8 * u];
+          const double bv = fma(e.x, eu[u], e.y * ew[u]) * f;
+          acc1[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, bv, acc1[u], 0, 0, 0);
+          acc2[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, bv, acc2[u], 0, 0, 0);
+        }
+      };
+      int m0 = 0;
+#pragma unroll 4
+      for (; m0 + 4 <= np; m0 += 4) step(m0, true);
+      step(m0, m0 + kq < np);  // n_p is odd: the last step is never full
+    }
+  }
+  __syncthreads();  // E is no longer read
+  double* red = reinterpret_cast<double*>(lds);
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double other = __shfl_xor(acc2[u][q], 8, 64);
+      // column 4 q + kq: real part of angle 8 u + j (j < 8), imaginary part of angle 8 u + j - 8
+      red[wave * 512 + (4 * q + kq) * 32 + 16 * u + j] = j < 8 ? acc1[u][q] - other : acc1[u][q] + other;
+    }
+  __syncthreads();
+  if (tid < FM_R * FM_T) {
+    const int jt = tid & (FM_T - 1), r = r0 + tid / FM_T;
+    const double* src = red + (tid / FM_T) * 32 + (jt & 7) + 2 * (jt & 8);
+    cplx sm = cmk(0.0, 0.0);
+    for (int w = 0; w < NW; ++w) sm = cadd(sm, cmk(src[w * 512], src[w * 512 + 8]));
+    const double c = 0.70710678118654752440 / (2.0 * sqrt(kk));  // e^{i pi/4} / (2 sqrt k)
+    if (r < R && t0 + jt < n_theta) a_out[((int64_t)b * R + r) * n_theta + t0 + jt] = cmul(cmk(c, c), sm);
+  }
+}
+
+typedef void (*ff_fn)(DevView, int, const cplx*, int, const double*, cplx*, int, int);
+static ff_fn ff_select(int64_t mmax, bool opf) {
+  if (mmax >= 64) return opf ? k_farfield_mfma<16, 4, true> : k_farfield_mfma<16, 4, false>;
+  if (mmax > 4) return opf ? k_farfield_mfma<16, 1, true> : k_farfield_mfma<16, 1, false>;
+  return opf ? k_farfield_mfma<4, 1, true> : k_farfield_mfma<4, 1, false>;
+}
+
 extern "C" int mudiff_farfield(mudiff_t h, int R, const void* rho, int n_theta, const double* theta,
                                void* a_out, void* stream) {
   if (!h || !rho || !theta || !a_out) return fail(MUDIFF_ERR_INVALID, "NULL argument");
@@ -181,7 +303,22 @@ extern "C" int mudiff_farfield(mudiff_t h, int R, const void* rho, int n_theta, 
   if ((int64_t)h->B * R > 65535) return fail(MUDIFF_ERR_INVALID, "too many instance x RHS columns");
   int64_t mmax = 0;  // disks of the largest instance
   for (int b = 0; b < h->B; ++b) mmax = std::max<int64_t>(mmax, h->idisk[b + 1] - h->idisk[b]);
-  if (mmax >= 64) {
+  const int64_t nct = (R + FM_R - 1) / FM_R, ntt = (n_theta + FM_T - 1) / FM_T;
+  // The matrix-core kernel does the work of 16 columns however few there are, and a
+  // workgroup walks all disks of its instance.  Below 4 columns the other kernel
+  // does less in all; on instances of 64 disks and more it also ends earlier while
+  // its workgroups (column, 16 angles) fit the chip about twice: 1,000 disks, 60
+  // angles, 8 columns (32 workgroups) 158 against 389 us, 30 columns (120) 230
+  // against 391, 256 columns at 360 angles (5,888) 4,810 against 760; 60 disks, 17
+  // columns at 361 angles 38 against 29, 8 disks, 100 columns 26 against 10.
+  const bool many = R >= 4 && (mmax < 64 || (int64_t)h->B * R * ntt >= 512);
+  if (many && h->Nmax <= FF_MFMA_N && nct * ntt < ((int64_t)1 << 31)) {
+    const int nw = mmax > 4 ? 16 : 4;
+    const ff_fn fn = ff_select(mmax, h->dv.op_ff != nullptr);
+    const size_t lds = std::max((size_t)(2 * h->Nmax + 1) * FM_T * 16, (size_t)nw * 512 * 8);
+    hipLaunchKernelGGL(fn, dim3((unsigned)(nct * ntt), (unsigned)h->B), dim3(64 * nw), lds, (hipStream_t)stream,
+                       h->dv, R, (const cplx*)rho, n_theta, theta, (cplx*)a_out, h->Nmax, (int)nct);
+  } else if (mmax >= 64) {
     dim3 grid((n_theta + 15) / 16, h->B * R);
     hipLaunchKernelGGL((k_farfield<16, 64>), grid, dim3(1024), 0, (hipStream_t)stream, h->dv, R,
                        (const cplx*)rho, n_theta, theta, (cplx*)a_out);
