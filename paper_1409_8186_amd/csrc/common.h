@@ -183,7 +183,10 @@ struct MfmaChoice {
 
 // Host schedule of the MFMA apply: work items (p0, rp, tile, q0, q1, partial
 // block) sorted by decreasing cost, the row group of every disk, and per group
-// its first disk, segment count and first partial block.
+// its first disk, segment count and first partial block.  Its arrays go to the
+// device as one block (blob): into the part of the tables workspace kept for
+// schedules, where they stay for the handle's lifetime (resident), or, when that
+// is full or the schedule is a straggler one, into the caller's apply scratch.
 struct MfmaSched {
   int R = 0;
   MfmaChoice c{};
@@ -202,7 +205,9 @@ struct MfmaSched {
   std::vector<int32_t> nptr, nq;
   std::vector<int32_t> rord;  // row disks by decreasing close-pair work (launch order)
   int n_citems = 0, cvar = 0;
-  void* dev_base = nullptr;  // apply scratch the device copy lives in
+  std::vector<char> blob;        // the arrays, packed
+  const char* dev = nullptr;     // the blob's device copy
+  bool resident = false;         // it lies in the tables workspace
 };
 
 struct mudiff_ctx {
@@ -229,7 +234,12 @@ struct mudiff_ctx {
   std::map<int, MfmaChoice> mfma_choice;  // tile choice per R
   std::map<int, float> mfma_time_ms;      // timed apply of the choice (autotuned R only)
   std::map<int, size_t> mfma_bytes;       // apply scratch per R (largest candidate)
-  MfmaSched mfma_sched;                   // current schedule (host copy + upload location)
+  std::map<int, MfmaSched> mfma_scheds;   // schedule per R
+  MfmaSched mfma_tail_sched;              // straggler schedule of the running solve
+  // part of the tables workspace that holds schedules, filled from the front;
+  // nothing in it is overwritten while the handle lives
+  char* res_base = nullptr;
+  size_t res_bytes = 0, res_used = 0;
   hipEvent_t sched_ev = nullptr;          // recorded after the last schedule upload
   // in the straggler phase the circulant form's close pairs run beside its
   // transforms and products: a second stream (default priority) forked after
@@ -407,11 +417,11 @@ int apply_operator_split(mudiff_ctx* h, int R, const cplx* x, cplx* y, int op, c
                          int32_t* counters, const int32_t* active, hipStream_t s,
                          bool* pending);
 size_t apply_scratch_bytes(mudiff_ctx* h, int R);
-// Forget where the MFMA schedule was last uploaded: the next apply uploads it
-// into its scratch again.  Every entry point that takes an apply scratch from
+// Forget MFMA schedules uploaded into an apply scratch: the next apply uploads
+// them into its scratch again.  Every entry point that takes an apply scratch from
 // the caller calls this first, so a buffer whose memory was used for anything
 // else between calls (or a new buffer at a recycled address) never runs on a
-// stale schedule.
+// stale schedule.  (Schedules in the tables workspace stay.)
 void apply_forget_upload(mudiff_ctx* h);
 // Wait until the last schedule upload has read its host vectors (before they
 // are rebuilt or released).
@@ -426,11 +436,14 @@ int64_t lane_layout(int B, const int64_t* disk_off, const int32_t* n_modes, int*
                     std::vector<int64_t>* ltoff, std::vector<int32_t>* lord = nullptr);
 int ensure_plan(mudiff_ctx* h, hipStream_t s);
 // Schedule for R applies made current (one-lane/generic plan, or the MFMA
-// schedule uploaded into `scratch`, the apply scratch later passed as `part`).
+// schedule on the device: in the tables workspace, or in `scratch`, the apply
+// scratch later passed as `part`).
 // On the MFMA path the first use of R times the tile candidates on x -> y
 // (y is overwritten) when x and y are given.  Synchronises; not for use under
 // graph capture.
 int prepare_apply(mudiff_ctx* h, int R, const cplx* x, cplx* y, cplx* scratch, hipStream_t s);
+// Bytes of the tables workspace kept for schedules.
+size_t resident_bytes(int B, const int64_t* disk_off);
 // Switch the MFMA schedule of R between the tuned form and the straggler form
 // (short column segments, only the tiles holding a column c with
 // cols[c] != 0, c = b * R + r); uploads into `scratch` and synchronises.

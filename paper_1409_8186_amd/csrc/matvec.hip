@@ -15,6 +15,7 @@
 // adds them in chunk order, so the result does not depend on scheduling.
 #include "common.h"
 
+#include <cstring>
 #include <mutex>
 
 
@@ -928,7 +929,8 @@ static void mfma_build(const mudiff_ctx* h, int R, const MfmaChoice& c, MfmaSche
                        const std::vector<int32_t>& cols = {}) {
   S.R = R;
   S.c = c;
-  S.dev_base = nullptr;
+  S.dev = nullptr;
+  S.resident = false;
   const int RC = 8 * c.CT;
   S.ntile = (R + RC - 1) / RC;
   const int mt = (2 * h->Nmax + 1 + 15) / 16;
@@ -1093,36 +1095,80 @@ static void mfma_build(const mudiff_ctx* h, int R, const MfmaChoice& c, MfmaSche
   S.n_citems = (int)(S.citems.size() / 4);
 }
 
-// Byte layout of the MFMA schedule inside the apply scratch:
-// [head][items][dgrp][grow][gnseg][gbase][partial blocks][scaled input][drow]
-// [qlist][product items][con][transformed inputs][transformed outputs]
-#define MF_NOFF 17
-static size_t mfma_scratch_layout(const mudiff_ctx* h, const MfmaSched& S, size_t* off) {
+// Device view of a schedule's arrays.
+struct SchedDev {
+  const int32_t *items, *dgrp, *grow, *gnseg, *drow, *qlist, *citems, *con, *nptr, *nq, *rord;
+  const int64_t* gbase;
+};
+template <class F>
+static void sched_arrays(const MfmaSched& S, F&& f) {  // f(vector, pointer of the device view)
+  f(S.items, &SchedDev::items);
+  f(S.dgrp, &SchedDev::dgrp);
+  f(S.grow, &SchedDev::grow);
+  f(S.gnseg, &SchedDev::gnseg);
+  f(S.drow, &SchedDev::drow);
+  f(S.qlist, &SchedDev::qlist);
+  f(S.citems, &SchedDev::citems);
+  f(S.con, &SchedDev::con);
+  f(S.nptr, &SchedDev::nptr);
+  f(S.nq, &SchedDev::nq);
+  f(S.rord, &SchedDev::rord);
+}
+static size_t sched_blob_bytes(const MfmaSched& S) {
+  size_t n = align256(S.gbase.size() * 8);
+  sched_arrays(S, [&](const std::vector<int32_t>& v, auto) { n += align256(v.size() * 4); });
+  return n;
+}
+static void sched_pack(MfmaSched& S) {
+  S.blob.assign(sched_blob_bytes(S), 0);
+  size_t o = align256(S.gbase.size() * 8);
+  if (!S.gbase.empty()) memcpy(S.blob.data(), S.gbase.data(), S.gbase.size() * 8);
+  sched_arrays(S, [&](const std::vector<int32_t>& v, auto) {
+    if (!v.empty()) memcpy(S.blob.data() + o, v.data(), v.size() * 4);
+    o += align256(v.size() * 4);
+  });
+}
+static SchedDev sched_view(const MfmaSched& S) {
+  SchedDev d{};
+  d.gbase = (const int64_t*)S.dev;
+  size_t o = align256(S.gbase.size() * 8);
+  sched_arrays(S, [&](const std::vector<int32_t>& v, auto m) {
+    d.*m = (const int32_t*)(S.dev + o);
+    o += align256(v.size() * 4);
+  });
+  return d;
+}
+
+// Byte layout of the apply scratch on the MFMA path: queue counter, partial
+// blocks, scaled input, transformed inputs and outputs (circulant form), and the
+// schedule when it is not resident.
+struct MfmaScratch {
+  size_t head, part, z, zh, wh, sched, total;
+};
+static MfmaScratch mfma_scratch_layout(const mudiff_ctx* h, const MfmaSched& S) {
+  MfmaScratch L{};
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t r = o;
     o = align256(o + bytes);
     return r;
   };
-  off[0] = take(4);
-  off[1] = take(S.items.size() * 4);
-  off[2] = take((size_t)h->M_all * 4);
-  off[3] = take(S.grow.size() * 4);
-  off[4] = take(S.gnseg.size() * 4);
-  off[5] = take(S.gbase.size() * 8);
-  off[6] = take((size_t)S.n_pb * S.blk * 16);
-  off[7] = take((size_t)S.R * h->N_all * 16);  // the input with its column scale applied
-  off[8] = take((size_t)h->M_all * 4);
-  off[9] = take(S.qlist.size() * 4);
-  off[10] = take(S.citems.size() * 4);
-  off[11] = take((size_t)h->B * 4);
+  L.head = take(4);
+  L.part = take((size_t)S.n_pb * S.blk * 16);
+  L.z = take((size_t)S.R * h->N_all * 16);  // the input with its column scale applied
   const size_t zw = S.c.circ ? (size_t)S.R * h->cZ_all * 16 : 0;
-  off[12] = take(zw);
-  off[13] = take(zw);
-  off[14] = take(S.nptr.size() * 4);  // close lists of the 8-column tiles
-  off[15] = take(S.nq.size() * 4);
-  off[16] = take(S.rord.size() * 4);
-  return o;
+  L.zh = take(zw);
+  L.wh = take(zw);
+  L.sched = take(sched_blob_bytes(S));
+  L.total = o;
+  return L;
+}
+
+// Room for schedules in the tables workspace: a few of the sizes that
+// multi-right-hand-side applies of this batch have (1,000 disks, 256 columns in
+// the circulant form: 0.15 MB; what does not fit is uploaded at every call).
+size_t resident_bytes(int B, const int64_t* disk_off) {
+  return ((size_t)256 << 10) + (size_t)B * 1024 + (size_t)disk_off[B] * 256;
 }
 
 // Candidate tile choices for R right-hand sides (RP * CT waves of 64 lanes).
@@ -1163,43 +1209,50 @@ void sched_wait(mudiff_ctx* h) {
   }
 }
 
-// Upload schedule S into the apply scratch at `base`, asynchronously: the
-// host vectors of S stay untouched until sched_wait (S = the handle's
-// schedule) or a synchronisation of the stream (a local S).  Not for use under
-// graph capture.
-static int mfma_upload(mudiff_ctx* h, MfmaSched& S, char* base, hipStream_t s) {
-  size_t off[MF_NOFF];
-  mfma_scratch_layout(h, S, off);
-  if (!S.qlist.empty())
-    HIP_TRY(hipMemcpyAsync(base + off[9], S.qlist.data(), S.qlist.size() * 4, hipMemcpyHostToDevice, s));
-  if (!S.citems.empty())
-    HIP_TRY(hipMemcpyAsync(base + off[10], S.citems.data(), S.citems.size() * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(base + off[11], S.con.data(), (size_t)h->B * 4, hipMemcpyHostToDevice, s));
-  if (!S.nptr.empty())
-    HIP_TRY(hipMemcpyAsync(base + off[14], S.nptr.data(), S.nptr.size() * 4, hipMemcpyHostToDevice, s));
-  if (!S.nq.empty())
-    HIP_TRY(hipMemcpyAsync(base + off[15], S.nq.data(), S.nq.size() * 4, hipMemcpyHostToDevice, s));
-  if (!S.rord.empty())
-    HIP_TRY(hipMemcpyAsync(base + off[16], S.rord.data(), S.rord.size() * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(base + off[1], S.items.data(), S.items.size() * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(base + off[2], S.dgrp.data(), (size_t)h->M_all * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(base + off[3], S.grow.data(), S.grow.size() * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(base + off[8], S.drow.data(), (size_t)h->M_all * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(base + off[4], S.gnseg.data(), S.gnseg.size() * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(base + off[5], S.gbase.data(), S.gbase.size() * 8, hipMemcpyHostToDevice, s));
+// Upload schedule S into the apply scratch at `scratch`, asynchronously: its blob
+// stays untouched until sched_wait (a schedule of the handle) or a synchronisation
+// of the stream (a local S).  Not for use under graph capture.
+static int mfma_upload(mudiff_ctx* h, MfmaSched& S, char* scratch, hipStream_t s) {
+  char* dst = scratch + mfma_scratch_layout(h, S).sched;
+  HIP_TRY(hipMemcpyAsync(dst, S.blob.data(), S.blob.size(), hipMemcpyHostToDevice, s));
   if (!h->sched_ev) HIP_TRY(hipEventCreateWithFlags(&h->sched_ev, hipEventDisableTiming));
-  if (S.c.circ && !h->aux) {
-    HIP_TRY(hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking));
-    HIP_TRY(hipEventCreateWithFlags(&h->fork_ev, hipEventDisableTiming));
-    HIP_TRY(hipEventCreateWithFlags(&h->join_ev, hipEventDisableTiming));
-  }
   HIP_TRY(hipEventRecord(h->sched_ev, s));
   h->sched_pending = true;
-  S.dev_base = base;
+  S.dev = dst;
   return MUDIFF_OK;
 }
 
-// Enqueue one MFMA apply with schedule S already uploaded at S.dev_base.
+// Put schedule S of the handle on the device: into the resident part of the
+// tables workspace if it fits (once: this waits for the copy, so that applies on
+// any stream find it), else into the apply scratch.  A capturing stream cannot
+// wait: there the scratch takes it.
+static int sched_place(mudiff_ctx* h, MfmaSched& S, char* scratch, hipStream_t s) {
+  if (S.dev && (S.resident || S.dev == scratch + mfma_scratch_layout(h, S).sched)) return MUDIFF_OK;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess) cs = hipStreamCaptureStatusActive;
+  if (cs == hipStreamCaptureStatusNone && &S != &h->mfma_tail_sched &&
+      h->res_used + S.blob.size() <= h->res_bytes) {
+    char* dst = h->res_base + h->res_used;
+    HIP_TRY(hipMemcpyAsync(dst, S.blob.data(), S.blob.size(), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    h->res_used += S.blob.size();
+    S.dev = dst;
+    S.resident = true;
+    return MUDIFF_OK;
+  }
+  return mfma_upload(h, S, scratch, s);
+}
+
+// Second stream and events of the straggler phase.
+static int aux_stream(mudiff_ctx* h) {
+  if (h->aux) return MUDIFF_OK;
+  HIP_TRY(hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking));
+  HIP_TRY(hipEventCreateWithFlags(&h->fork_ev, hipEventDisableTiming));
+  HIP_TRY(hipEventCreateWithFlags(&h->join_ev, hipEventDisableTiming));
+  return MUDIFF_OK;
+}
+
+// Enqueue one MFMA apply with schedule S already on the device (S.dev).
 typedef void (*mf_fn)(DevView, int, const cplx*, const int32_t*, const int32_t*, int, int32_t*,
                       cplx*, int64_t, int, int, int, int, const int32_t*, const int32_t*);
 
@@ -1225,21 +1278,20 @@ static mf_fn mf_select(int mt, int th, int zk, int tk) {
 #undef MF_MT
 #undef MF_TK3
 
-static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, const cplx* x, cplx* y, int op,
+static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, char* base, const cplx* x, cplx* y, int op,
                        const int32_t* active, hipStream_t s, const cplx* shift = nullptr) {
-  size_t off[MF_NOFF];
-  mfma_scratch_layout(h, S, off);
-  char* base = (char*)S.dev_base;
-  int32_t* head = (int32_t*)(base + off[0]);
-  cplx* part = (cplx*)(base + off[6]);
+  const MfmaScratch L = mfma_scratch_layout(h, S);
+  const SchedDev d = sched_view(S);
+  int32_t* head = (int32_t*)(base + L.head);
+  cplx* part = (cplx*)(base + L.part);
   const int mt = S.npad / 16;
   const int kt = (2 * h->Nmax + 1 + 3) / 4;
   const int RC = 8 * S.c.CT;
   const size_t lds = ((size_t)4 * kt * RC + (size_t)S.c.RP * (4 * kt + 16 * mt - 1)) * 16;
   prof_open(h, s);
-  int rc = launch_fill_zero(head, 4, s);
-  if (rc != MUDIFF_OK) return rc;
-  cplx* z = (cplx*)(base + off[7]);
+  int rc = MUDIFF_OK;
+  if (S.n_items > 0 && (rc = launch_fill_zero(head, 4, s)) != MUDIFF_OK) return rc;
+  cplx* z = (cplx*)(base + L.z);
   int64_t nbmax = 0;  // longest instance vector
   for (int b = 0; b < h->B; ++b) nbmax = std::max(nbmax, h->imode[b + 1] - h->imode[b]);
   if ((nbmax + 255) / 256 > 65535) return fail(MUDIFF_ERR_INVALID, "instance too large for the input scaling grid");
@@ -1248,7 +1300,7 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, const cplx* x, cplx* y
   HIP_TRY(hipGetLastError());
   prof_mark(h, s, 1);
   cplx* wh = nullptr;
-  const int32_t* con = (const int32_t*)(base + off[11]);
+  const int32_t* con = d.con;
   // direct-form work (the work queue and the close-pair rows): in the straggler
   // phase of a solve with the circulant form it runs on the second stream,
   // beside the transforms and products, which share none of its outputs (there
@@ -1265,24 +1317,23 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, const cplx* x, cplx* y
   }
   if (S.close_rows && (mt < 1 || mt > 4)) return fail(MUDIFF_ERR_INVALID, "close pairs: orders out of range");
   hipStream_t cs = s;
-  const bool fork = h->mfma_tail && S.c.circ && (S.n_items > 0 || S.close_rows) && h->aux;
+  const bool fork = h->mfma_tail && S.c.circ && (S.n_items > 0 || S.close_rows);
   if (fork) {
+    if ((rc = aux_stream(h)) != MUDIFF_OK) return rc;
     HIP_TRY(hipEventRecord(h->fork_ev, s));
     HIP_TRY(hipStreamWaitEvent(h->aux, h->fork_ev, 0));
     cs = h->aux;
   }
   auto launch_direct = [&]() -> int {
     if (S.n_items > 0) {
-      const int32_t* it = (const int32_t*)(base + off[1]);
       // persistent grid: as many workgroups as are resident at once
       int per_cu = 0;
       if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)fn, S.c.threads, lds) !=
               hipSuccess || per_cu < 1)
         per_cu = 1;
       const int grid = std::max(1, std::min(S.n_items, per_cu * h->n_cu));
-      hipLaunchKernelGGL(fn, dim3(grid), dim3(S.c.threads), lds, cs, h->dv, S.R, (const cplx*)z, active, it,
-                         S.n_items, head, part, S.blk, S.npad, kt, S.c.RP, S.c.CT,
-                         (const int32_t*)(base + off[3]), (const int32_t*)(base + off[9]));
+      hipLaunchKernelGGL(fn, dim3(grid), dim3(S.c.threads), lds, cs, h->dv, S.R, (const cplx*)z, active, d.items,
+                         S.n_items, head, part, S.blk, S.npad, kt, S.c.RP, S.c.CT, d.grow, d.qlist);
       HIP_TRY(hipGetLastError());
     }
     if (S.close_rows) {  // every row of the form writes its segment (zeros without close pairs)
@@ -1293,10 +1344,8 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, const cplx* x, cplx* y
                                          k_apply_close<3, 2>, k_apply_close<4, 2>};
       const unsigned zg = mt > 2 ? 2u : 1u;  // groups of two row tiles
       hipLaunchKernelGGL(kClose[mt], dim3((unsigned)h->M_all, (unsigned)S.ntile, zg), dim3(64), 0, cs, h->dv,
-                         S.R, (const cplx*)z, part, S.blk, S.npad, (const int32_t*)(base + off[2]),
-                         (const int32_t*)(base + off[8]), (const int64_t*)(base + off[5]),
-                         (const int32_t*)(base + off[14]), (const int32_t*)(base + off[15]), con, active,
-                         (const int32_t*)(base + off[16]));
+                         S.R, (const cplx*)z, part, S.blk, S.npad, d.dgrp, d.drow, d.gbase, d.nptr, d.nq, con,
+                         active, d.rord);
       HIP_TRY(hipGetLastError());
     }
     return MUDIFF_OK;
@@ -1306,10 +1355,9 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, const cplx* x, cplx* y
     HIP_TRY(hipEventRecord(h->join_ev, cs));
   }
   if (S.c.circ) {  // well-separated pairs of the marked instances
-    cplx* zh = (cplx*)(base + off[12]);
-    wh = (cplx*)(base + off[13]);
-    rc = circ_launch(h, S.R, z, zh, wh, (const int32_t*)(base + off[10]), S.n_citems, S.cvar, con,
-                     S.con.data(), active, s);
+    cplx* zh = (cplx*)(base + L.zh);
+    wh = (cplx*)(base + L.wh);
+    rc = circ_launch(h, S.R, z, zh, wh, d.citems, S.n_citems, S.cvar, con, S.con.data(), active, s);
     if (rc != MUDIFF_OK) return rc;
   } else {
     prof_mark(h, s, 2);
@@ -1320,18 +1368,14 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, const cplx* x, cplx* y
   prof_mark(h, s, 4);
   if (S.c.circ) {
     rc = circ_finish(h, S.R, x, y, op, (const cplx*)part, S.blk, S.npad, RC,
-                     (const int32_t*)(base + off[2]), (const int32_t*)(base + off[8]),
-                     (const int32_t*)(base + off[4]), (const int64_t*)(base + off[5]), active,
-                     (const cplx*)wh, con, S.con.data(), shift, s);
+                     d.dgrp, d.drow, d.gnseg, d.gbase, active, (const cplx*)wh, con, S.con.data(), shift, s);
     prof_mark(h, s, 5);
     return rc;
   }
   const int64_t total = (int64_t)S.R * h->N_all;
   hipLaunchKernelGGL(k_apply_mfma_finish, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
                      h->dv, S.R, x, y, op, (const cplx*)part, S.blk, S.npad, RC,
-                     (const int32_t*)(base + off[2]), (const int32_t*)(base + off[8]),
-                     (const int32_t*)(base + off[4]), (const int64_t*)(base + off[5]), active,
-                     (const cplx*)wh, con, shift);
+                     d.dgrp, d.drow, d.gnseg, d.gbase, active, (const cplx*)wh, con, shift);
   HIP_TRY(hipGetLastError());
   prof_mark(h, s, 5);
   return MUDIFF_OK;
@@ -1352,8 +1396,7 @@ static size_t mfma_scratch_bytes(mudiff_ctx* h, int R) {
           c.cvar = cv;
           MfmaSched S;
           mfma_build(h, R, c, S);
-          size_t off[MF_NOFF];
-          mx = std::max(mx, mfma_scratch_layout(h, S, off));
+          mx = std::max(mx, mfma_scratch_layout(h, S).total);
         }
       }
   }
@@ -1410,9 +1453,10 @@ static int mfma_autotune(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scr
       hipStream_t st;
       ~Drain() { (void)hipStreamSynchronize(st); }
     } drain{s};
+    sched_pack(S);
     if ((rc = mfma_upload(h, S, scratch, s)) != MUDIFF_OK) return 0.0f;
     (void)hipEventRecord(e0, s);
-    if ((rc = mfma_launch(h, S, x, y, MUDIFF_OP_A, nullptr, s)) != MUDIFF_OK) return 0.0f;  // warm-up
+    if ((rc = mfma_launch(h, S, scratch, x, y, MUDIFF_OP_A, nullptr, s)) != MUDIFF_OK) return 0.0f;  // warm-up
     (void)hipEventRecord(e1, s);
     if (best > 0.0f) {  // a warm-up already twice as slow as the best pair of applies: no contender
       float w = 0.0f;
@@ -1421,7 +1465,7 @@ static int mfma_autotune(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scr
         return 0.0f;
     }
     (void)hipEventRecord(e0, s);
-    for (int k = 0; k < 2 && rc == MUDIFF_OK; ++k) rc = mfma_launch(h, S, x, y, MUDIFF_OP_A, nullptr, s);
+    for (int k = 0; k < 2 && rc == MUDIFF_OK; ++k) rc = mfma_launch(h, S, scratch, x, y, MUDIFF_OP_A, nullptr, s);
     (void)hipEventRecord(e1, s);
     if (rc != MUDIFF_OK) return 0.0f;
     if (hipEventSynchronize(e1) != hipSuccess) {
@@ -1486,31 +1530,45 @@ static int mfma_autotune(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scr
   if (rc != MUDIFF_OK) return rc;
   h->mfma_choice[R] = bc;
   h->mfma_time_ms[R] = best / 2.0f;
-  sched_wait(h);
-  mfma_build(h, R, bc, h->mfma_sched);
-  return mfma_upload(h, h->mfma_sched, scratch, s);
+  return MUDIFF_OK;
 }
 
-// Make the schedule for R current and uploaded at `scratch` (autotuning on
+// Drop the schedule of R (its choice changed): no upload still reads it.
+static void sched_drop(mudiff_ctx* h, int R) {
+  sched_wait(h);
+  h->mfma_scheds.erase(R);
+}
+
+// Make the schedule for R current and place it on the device (autotuning on
 // first use of R when x, y are given, else the default choice).
 static int mfma_prepare(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scratch,
                         hipStream_t s) {
   auto f = h->mfma_choice.find(R);
   if (f == h->mfma_choice.end()) {
-    if (x && y && h->mfma_tune) return mfma_autotune(h, R, x, y, scratch, s);
-    MfmaChoice d = mfma_default(R);
-    d.circ = circ_usable(h, R);
-    h->mfma_choice[R] = d;
+    if (x && y && h->mfma_tune) {
+      const int rc = mfma_autotune(h, R, x, y, scratch, s);
+      if (rc != MUDIFF_OK) return rc;
+    } else {
+      MfmaChoice d = mfma_default(R);
+      d.circ = circ_usable(h, R);
+      h->mfma_choice[R] = d;
+    }
     f = h->mfma_choice.find(R);
   }
   MfmaChoice c = f->second;
   if (h->mfma_tail) c.QS = MFMA_TAIL_QS;
-  if (h->mfma_sched.R != R || !(h->mfma_sched.c == c)) {
+  MfmaSched& S = h->mfma_tail ? h->mfma_tail_sched : h->mfma_scheds[R];
+  if (S.R != R || !(S.c == c)) {
     sched_wait(h);
-    mfma_build(h, R, c, h->mfma_sched, h->mfma_tail ? h->mfma_tail_cols : std::vector<int32_t>{});
+    mfma_build(h, R, c, S, h->mfma_tail ? h->mfma_tail_cols : std::vector<int32_t>{});
+    sched_pack(S);
   }
-  if (h->mfma_sched.dev_base != scratch) return mfma_upload(h, h->mfma_sched, scratch, s);
-  return MUDIFF_OK;
+  return sched_place(h, S, scratch, s);
+}
+
+// The schedule that mfma_prepare made current.
+static const MfmaSched& mfma_current(const mudiff_ctx* h, int R) {
+  return h->mfma_tail ? h->mfma_tail_sched : h->mfma_scheds.at(R);
 }
 
 int apply_set_tail(mudiff_ctx* h, int R, bool tail, cplx* scratch, hipStream_t s,
@@ -1520,7 +1578,9 @@ int apply_set_tail(mudiff_ctx* h, int R, bool tail, cplx* scratch, hipStream_t s
   h->mfma_tail = tail;
   if (tail && cols) h->mfma_tail_cols.assign(cols, cols + (size_t)h->B * R);
   else h->mfma_tail_cols.clear();
-  h->mfma_sched.R = 0;  // rebuild
+  sched_wait(h);
+  h->mfma_tail_sched.R = 0;  // rebuild
+  apply_forget_upload(h);    // the two forms lay out the scratch differently
   return mfma_prepare(h, R, nullptr, nullptr, (char*)scratch, s);
 }
 
@@ -1847,7 +1907,11 @@ size_t apply_scratch_bytes(mudiff_ctx* h, int R) {
   return align256((size_t)R * h->plan_part * 16) + counters;
 }
 
-void apply_forget_upload(mudiff_ctx* h) { h->mfma_sched.dev_base = nullptr; }
+void apply_forget_upload(mudiff_ctx* h) {
+  for (auto& kv : h->mfma_scheds)
+    if (!kv.second.resident) kv.second.dev = nullptr;
+  h->mfma_tail_sched.dev = nullptr;
+}
 
 int prepare_apply(mudiff_ctx* h, int R, const cplx* x, cplx* y, cplx* scratch, hipStream_t s) {
   if (use_mfma(h, R)) return mfma_prepare(h, R, x, y, (char*)scratch, s);
@@ -1893,7 +1957,7 @@ int apply_operator(mudiff_ctx* h, int R, const cplx* x, cplx* y, int op, cplx* p
   if (use_mfma(h, R)) {
     int st = mfma_prepare(h, R, nullptr, nullptr, (char*)part, s);  // no-op when current
     if (st != MUDIFF_OK) return st;
-    return mfma_launch(h, h->mfma_sched, x, y, op, active, s, shift);
+    return mfma_launch(h, mfma_current(h, R), (char*)part, x, y, op, active, s, shift);
   }
   int st = ensure_plan(h, s);
   if (st != MUDIFF_OK) return st;
@@ -1988,7 +2052,7 @@ extern "C" int mudiff_matvec(mudiff_t h, int R, const void* x, void* y, int op, 
   int rc;
   if (use_mfma(h, R)) {
     rc = mfma_prepare(h, R, xin, (cplx*)y, w, s);  // autotunes on first use of R
-    if (rc == MUDIFF_OK) rc = mfma_launch(h, h->mfma_sched, xin, (cplx*)y, aop, nullptr, s);
+    if (rc == MUDIFF_OK) rc = mfma_launch(h, mfma_current(h, R), w, xin, (cplx*)y, aop, nullptr, s);
   } else {
     size_t part_bytes = need - align256((size_t)R * h->M_all * 4);
     int32_t* counters = (int32_t*)(w + part_bytes);  // zero on first use, left zero
@@ -2063,7 +2127,7 @@ extern "C" int mudiff_set_circulant(mudiff_t h, int R, int mode) {
       f->second.circ = mode != 0 && circ_usable(h, R);
     }
   }
-  if (h->mfma_sched.R == R) h->mfma_sched.R = 0;  // rebuild at the next apply
+  sched_drop(h, R);  // rebuild at the next apply
   return MUDIFF_OK;
 }
 
@@ -2104,7 +2168,7 @@ extern "C" int mudiff_set_circulant_tile(mudiff_t h, int R, int rows, int cols, 
       h->mfma_choice[R] = ch;
       h->mfma_time_ms.erase(R);
       h->circ_modes[R] = 1;
-      if (h->mfma_sched.R == R) h->mfma_sched.R = 0;
+      sched_drop(h, R);
       return MUDIFF_OK;
     }
   }

@@ -267,11 +267,11 @@ namespace {
 struct Layout {
   size_t off_cx, off_cy, off_a, off_kd, off_N, off_inst, off_moff, off_dtab, off_idisk, off_imode,
       off_ipair, off_toff, off_t, off_Jd, off_Hd, off_sJ, off_invSH, off_Ldiag, off_udisk, off_sched,
-      off_lt, off_ltoff, off_lord, off_lpos;
+      off_lt, off_ltoff, off_lord, off_lpos, off_res;
   // circulant form (MUDIFF_TABLES_CIRCULANT)
   size_t off_cL = 0, off_cTo = 0, off_cZo = 0, off_cWo = 0, off_ctw = 0, off_cnear = 0, off_cT = 0;
   int64_t c_tw = 0, c_T = 0;  // twiddles, transformed symbols (complex values)
-  size_t sched_bytes, total;
+  size_t sched_bytes, res_bytes, total;
 };
 
 Layout make_layout(int B, const int64_t* disk_off, const int32_t* n_modes, int64_t N_all,
@@ -305,6 +305,8 @@ Layout make_layout(int B, const int64_t* disk_off, const int32_t* n_modes, int64
   L.off_udisk = take(N_all * 4);
   L.sched_bytes = sched_bytes_for(B, disk_off, n_modes);
   L.off_sched = take(L.sched_bytes);
+  L.res_bytes = resident_bytes(B, disk_off);
+  L.off_res = take(L.res_bytes);
   int lane_N;
   const int64_t lt = lane_layout(B, disk_off, n_modes, &lane_N, nullptr);
   L.off_lt = take(lt * 16);
@@ -511,6 +513,8 @@ extern "C" int mudiff_tables(int B, const int64_t* disk_off, const double* cente
   }
   h->sched_base = base + L.off_sched;
   h->sched_bytes = L.sched_bytes;
+  h->res_base = base + L.off_res;
+  h->res_bytes = L.res_bytes;
   std::vector<int64_t> cTo, cWo;
   if (flags & MUDIFF_TABLES_CIRCULANT) {
     h->circ = true;
