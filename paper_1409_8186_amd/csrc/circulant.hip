@@ -97,10 +97,10 @@ __global__ __launch_bounds__(256) void k_circ_symbols(DevView v, const uint8_t* 
 }
 
 // Transformed inputs Z_f[q][r] = sum_k w^{-f k} z^q_k for one column disk q and
-// 32 right-hand sides: the panel z (already scaled by its column factor) is
+// 32 right-hand sides: the panel z (the input times its column factor) is
 // staged in LDS as [k][r], thread (f-lane, r) runs over the frequencies.
 #define CF_R 32
-__global__ __launch_bounds__(256) void k_circ_fwd(DevView v, int R, const cplx* __restrict__ z,
+__global__ __launch_bounds__(256) void k_circ_fwd(DevView v, int R, const cplx* __restrict__ x,
                                                   cplx* __restrict__ zh,
                                                   const int32_t* __restrict__ con,
                                                   const int32_t* __restrict__ active) {
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(256) void k_circ_fwd(DevView v, int R, const cplx* 
   for (int e = tid; e < cw * nq; e += 256) {
     const int r = e / nq, k = e - (e / nq) * nq;
     cplx val = cmk(0.0, 0.0);
-    if (r0 + r < R) val = z[col_base(v.imode, b, R, r0 + r) + mq + k];
+    if (r0 + r < R) val = col_scale(v, v.imode[b] + mq + k, x[col_base(v.imode, b, R, r0 + r) + mq + k]);
     zs[k * cw + r] = val;
   }
   for (int e = tid; e < Lb; e += 256) tw[e] = v.ctw[v.cWo[b] + e];
@@ -276,10 +276,10 @@ __device__ cplx* fft23_lds(cplx* x, cplx* y, const cplx* tw, int L, bool inverse
   return x;
 }
 
-// Forward transforms of the scaled input panels of one column disk q and CR
+// Forward transforms of the input panels (scaled by their column factors) of one column disk q and CR
 // right-hand sides, for instances with L_b = 2^a 3^b <= LM.
 template <int CR, int LM>
-__global__ __launch_bounds__(256) void k_circ_fwd_fft(DevView v, int R, const cplx* __restrict__ z,
+__global__ __launch_bounds__(256) void k_circ_fwd_fft(DevView v, int R, const cplx* __restrict__ x,
                                                       cplx* __restrict__ zh,
                                                       const int32_t* __restrict__ con,
                                                       const int32_t* __restrict__ active) {
@@ -302,7 +302,8 @@ __global__ __launch_bounds__(256) void k_circ_fwd_fft(DevView v, int R, const cp
   for (int e = tid; e < Lb * CR; e += 256) {  // along the modes of a column: coalesced
     const int c = e / Lb, k = e - (e / Lb) * Lb;
     cplx val = cmk(0.0, 0.0);
-    if (k < nq && r0 + c < R) val = z[col_base(v.imode, b, R, r0 + c) + v.moff[q] + k];
+    if (k < nq && r0 + c < R)
+      val = col_scale(v, v.imode[b] + v.moff[q] + k, x[col_base(v.imode, b, R, r0 + c) + v.moff[q] + k]);
     buf[k * CR + c] = val;
   }
   for (int e = tid; e < Lb; e += 256) tw[e] = v.ctw[v.cWo[b] + e];
@@ -631,16 +632,17 @@ __global__ __launch_bounds__(256) void k_circ_finish_mfma(
     __syncthreads();
   }
   const int gr = dgrp[p];
-  const int ns = gnseg[gr];
+  const int ns = gnseg[gr], nsr = drow[p] & ROW_EMPTY ? 0 : ns;
+  const int row = drow[p] & (ROW_EMPTY - 1);
   const int64_t ip = v.imode[b] + v.moff[p];
   for (int e = tid; e < ncol * np; e += 256) {
     const int rr = e / np, m = e - (e / np) * np;
     const int r = r0 + rr;
     if (r >= R || (active && active[b * R + r] == 0)) continue;
     const int t = r / RC, rc = r - (r / RC) * RC;
-    const cplx* pr = part + (gbase[gr] + (int64_t)t * ns) * blk + ((int64_t)drow[p] * npad + m) * RC + rc;
+    const cplx* pr = part + (gbase[gr] + (int64_t)t * ns) * blk + ((int64_t)row * npad + m) * RC + rc;
     cplx w = circ ? ws[rr * ldw + m] : cmk(0.0, 0.0);
-    for (int sg = 0; sg < ns; ++sg) w = cadd(w, pr[(int64_t)sg * blk]);
+    for (int sg = 0; sg < nsr; ++sg) w = cadd(w, pr[(int64_t)sg * blk]);
     const int64_t g = col_base(v.imode, b, R, r) + v.moff[p] + m;
     cplx o = finalize(v, op, ip + m, x[g], w);
     if (shift) o = affine(shift, b * R + r, o, x[g]);
@@ -685,16 +687,17 @@ __global__ __launch_bounds__(256) void k_circ_finish_fft(
   __syncthreads();
   const cplx* res = fft23_lds<CR>(buf, buf + LM * CR, tw, Lb, true);
   const int gr = dgrp[p];
-  const int ns = gnseg[gr];
+  const int ns = gnseg[gr], nsr = drow[p] & ROW_EMPTY ? 0 : ns;
+  const int row = drow[p] & (ROW_EMPTY - 1);
   const int64_t ip = v.imode[b] + v.moff[p];
   for (int e = tid; e < CR * np; e += 256) {
     const int rr = e / np, m = e - (e / np) * np;
     const int r = r0 + rr;
     if (r >= R || (active && active[b * R + r] == 0)) continue;
     const int t = r / RC, rc = r - (r / RC) * RC;
-    const cplx* pr = part + (gbase[gr] + (int64_t)t * ns) * blk + ((int64_t)drow[p] * npad + m) * RC + rc;
+    const cplx* pr = part + (gbase[gr] + (int64_t)t * ns) * blk + ((int64_t)row * npad + m) * RC + rc;
     cplx w = res[m * CR + rr];
-    for (int sg = 0; sg < ns; ++sg) w = cadd(w, pr[(int64_t)sg * blk]);
+    for (int sg = 0; sg < nsr; ++sg) w = cadd(w, pr[(int64_t)sg * blk]);
     const int64_t g = col_base(v.imode, b, R, r) + v.moff[p] + m;
     cplx o = finalize(v, op, ip + m, x[g], w);
     if (shift) o = affine(shift, b * R + r, o, x[g]);
@@ -767,7 +770,8 @@ void circ_var_dims(int var, int* bm, int* bn, int* bk, int* db, int* nt, int* mu
 }
 
 // Enqueue the transforms of the inputs and the per-frequency products.
-// z: inputs scaled by their column factors [B][R][N_b]; zh, wh: [sum_b L_b M_b][R].
+// x: the inputs [B][R][N_b] (scaled by their column factors as they are read);
+// zh, wh: [sum_b L_b M_b][R].
 // Which transform kernels a launch needs: instances in the form with L_b =
 // 2^a 3^b (fast transforms, 8 right-hand sides per workgroup, in two length
 // classes with their own LDS size: *fft for L_b <= 81, *fft_wide for longer
@@ -783,7 +787,7 @@ static void circ_kinds(const mudiff_ctx* h, const int32_t* con_h, bool* fft, boo
   }
 }
 
-int circ_launch(mudiff_ctx* h, int R, const cplx* z, cplx* zh, cplx* wh, const int32_t* citems,
+int circ_launch(mudiff_ctx* h, int R, const cplx* x, cplx* zh, cplx* wh, const int32_t* citems,
                 int n_citems, int var, const int32_t* con, const int32_t* con_h,
                 const int32_t* active, hipStream_t s) {
   bool fft, dft, wide;
@@ -791,13 +795,13 @@ int circ_launch(mudiff_ctx* h, int R, const cplx* z, cplx* zh, cplx* wh, const i
   const int cw = R >= CF_R ? CF_R : (R > 8 ? 16 : 8);
   if (dft)
     hipLaunchKernelGGL(k_circ_fwd, dim3((unsigned)h->M_all, (unsigned)((R + cw - 1) / cw)), dim3(256), 0,
-                       s, h->dv, R, z, zh, con, active);
+                       s, h->dv, R, x, zh, con, active);
   if (fft)
     hipLaunchKernelGGL((k_circ_fwd_fft<8, 81>), dim3((unsigned)h->M_all, (unsigned)((R + 7) / 8)),
-                       dim3(256), 0, s, h->dv, R, z, zh, con, active);
+                       dim3(256), 0, s, h->dv, R, x, zh, con, active);
   if (wide)
     hipLaunchKernelGGL((k_circ_fwd_fft<8, CF_LMAX>), dim3((unsigned)h->M_all, (unsigned)((R + 7) / 8)),
-                       dim3(256), 0, s, h->dv, R, z, zh, con, active);
+                       dim3(256), 0, s, h->dv, R, x, zh, con, active);
   HIP_TRY(hipGetLastError());
   prof_mark(h, s, 2);
   if (n_citems > 0) {

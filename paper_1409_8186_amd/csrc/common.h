@@ -187,23 +187,27 @@ struct MfmaChoice {
 // device as one block (blob): into the part of the tables workspace kept for
 // schedules, where they stay for the handle's lifetime (resident), or, when that
 // is full or the schedule is a straggler one, into the caller's apply scratch.
+#define ROW_EMPTY 256
 struct MfmaSched {
   int R = 0;
   MfmaChoice c{};
   int ntile = 0, n_items = 0, npad = 0;
   int64_t blk = 0, n_pb = 0;
-  std::vector<int32_t> items, dgrp, grow, gnseg, drow;  // grow: RP row disks per group (-1: none)
+  std::vector<int32_t> items, dgrp, grow, gnseg, drow;  // grow: RP row disks per group (-1: none);
+                                                        // drow: row in the group, ROW_EMPTY: no partial sums
   std::vector<int64_t> gbase;
   // circulant form: column lists of the close-pair items ((q << 8) | mask of
   // the group rows close to q), per-frequency product items (instance,
   // frequency, row tile, column tile) and the instances that use the form
   std::vector<int32_t> qlist, citems, con;
-  // 8-column tiles in the circulant form: the close pairs run one wave per
-  // (row disk, tile) over the row's close list (nptr [M_all + 1] offsets into
-  // nq, global disk indices), not as work-queue items
+  // 8-column tiles in the circulant form: the close pairs run on k_apply_close,
+  // not as work-queue items.  crow: per row disk with close pairs (disk, first
+  // record, last + 1, 0), by decreasing work, the first n_long of them the long
+  // lists; crec: per close pair (mode offset of the column disk, its N, symbol
+  // offset of the pair, 1 if the symbols change sign)
   bool close_rows = false;
-  std::vector<int32_t> nptr, nq;
-  std::vector<int32_t> rord;  // row disks by decreasing close-pair work (launch order)
+  std::vector<int32_t> crow, crec;
+  int n_long = 0;
   int n_citems = 0, cvar = 0;
   std::vector<char> blob;        // the arrays, packed
   const char* dev = nullptr;     // the blob's device copy

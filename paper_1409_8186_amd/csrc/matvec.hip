@@ -735,38 +735,92 @@ __global__ __launch_bounds__(THREADS) void k_apply_mfma(
   }
 }
 
-// Close pairs of the instances in the circulant form with 8-column tiles (few
-// right-hand sides): one wave per (row disk p, tile of 8 columns, group of row
-// tiles), no LDS and no barriers.  The wave walks p's close list; per column disk q and k step it
-// loads the input panel element of its lane (B[k][j]: Re or Im of column j & 7
-// at mode 4 kt + k) and per row tile the symbol value of its lane (A[i][k]:
-// t_{(n - N_q) - (m - N_p)}, m = 16 mt + i), straight into the operand layout
-// of v_mfma_f64_16x16x4f64 (two MFMAs per complex product, as k_apply_mfma),
-// and accumulates the whole row in registers; the sum goes to segment 0 of the
-// row's group, which the output pass adds.  In the work queue the same pairs
-// cost two barriers and an LDS staging round per listed column disk, with only
-// the few waves whose row is close to it on the matrix cores.  The kernel is
-// bound by load latency, so the row tiles of a row disk are split over waves
-// (MTW tiles each, blockIdx.z the group): with the accumulators of two tiles
-// the register budget is held to eight waves per SIMD, at one more input load
-// per k step.
+#define CLOSE_LONG 8
+// The close pairs e0, e0 + step, .. < e1 of one row disk: NT row tiles (of MTW
+// accumulators), no branch between the loads of a step.
+template <int NT, int MTW, bool OPC>
+__device__ __forceinline__ void close_walk(const DevView& v, const cplx* __restrict__ xc, int64_t i0,
+                                           const int4* __restrict__ crec, int e0, int e1, int step, int Np,
+                                           int top, int j, int kq, mf_d4 (&acc1)[MTW], mf_d4 (&acc2)[MTW]) {
+  int4 rec = crec[min(e0, e1 - 1)];
+  for (int e = e0; e < e1; e += step) {
+    const int4 cur = rec;
+    rec = crec[min(e + step, e1 - 1)];
+    const int Nq = cur.y, nq_ = 2 * Nq + 1, S = Np + Nq, KT = (nq_ + 3) >> 2;
+    const cplx* __restrict__ trow = v.t + cur.z + S;
+    const cplx* __restrict__ zq = xc + cur.x;
+    const double* __restrict__ sq = v.sJ + i0 + cur.x;
+    const cplx* __restrict__ oq = v.op_col + i0 + cur.x;
+#pragma unroll 4
+    for (int kt = 0; kt < KT; ++kt) {
+      const int n = 4 * kt + kq, nc = min(n, nq_ - 1);
+      const cplx zz = OPC ? cmul(zq[nc], oq[nc]) : cscale(zq[nc], sq[nc]);
+      const double bv = n < nq_ ? (j < 8 ? zz.x : zz.y) : 0.0;
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        // rows past n_p read some symbol of the row (their sums are never read)
+        const int sv = max(-S, (nc - Nq) - (top + 16 * i));
+        cplx a = trow[sv];
+        if (cur.w & sv & 1) a = cmk(-a.x, -a.y);  // t^{pq}_s = (-1)^s t^{qp}_s
+        acc1[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, bv, acc1[i], 0, 0, 0);
+        acc2[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, bv, acc2[i], 0, 0, 0);
+      }
+    }
+  }
+}
+
+// Close pairs of the instances in the circulant form with 8-column tiles: a wave
+// takes (row disk p, tile of 8 columns, MTW row tiles) and walks p's close pairs;
+// per column disk q and k step it loads the input panel element of its lane
+// (B[k][j]: Re or Im of column j & 7 at mode 4 kt + k, times its column factor) and
+// per row tile the symbol value of its lane (A[i][k]: t_{(n - N_q) - (m - N_p)},
+// m = 16 mt + i), straight into the operand layout of v_mfma_f64_16x16x4f64 (two
+// MFMAs per complex product, as k_apply_mfma), no LDS.  The row's sums stay in
+// registers and go to segment 0 of its group, which the output pass adds; rows
+// without close pairs are not launched (ROW_EMPTY).
+// Bound by load latency: a record per pair (read one ahead) names everything its
+// loads need, four k steps of loads are issued together, and lists longer than
+// CLOSE_LONG are split over the four waves of a workgroup, whose sums meet in LDS,
+// so that one long list does not outlast the launch.  Registers for the loads in
+// flight count for more than waves: four waves per SIMD and four steps, against
+// eight waves and one step 78 and 91 us on 48 unequal instances of up to 200 disks
+// with 8 columns, 179 and 207 us on 1,000 disks with 256 (one wave per list, loads
+// behind branches, offsets looked up per pair: 293 and 183 us); a branch on the kind
+// of column factor between the loads costs as much again (121 and 248).
 template <int MT, int MTW>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_apply_close(
-    DevView v, int R, const cplx* __restrict__ z, cplx* __restrict__ part, int64_t blk, int npad,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_apply_close(
+    DevView v, int R, const cplx* __restrict__ x, cplx* __restrict__ part, int64_t blk, int npad,
     const int32_t* __restrict__ dgrp, const int32_t* __restrict__ drow,
-    const int64_t* __restrict__ gbase, const int32_t* __restrict__ nptr,
-    const int32_t* __restrict__ nql, const int32_t* __restrict__ con,
-    const int32_t* __restrict__ active, const int32_t* __restrict__ rord) {
-  // rows by decreasing work, so that the longest lists do not end the launch
-  const int p = rord[blockIdx.x], t = blockIdx.y, lane = threadIdx.x;
-  const int mt0 = MTW * (int)blockIdx.z;  // first row tile of this wave
+    const int64_t* __restrict__ gbase, const int4* __restrict__ crow, const int4* __restrict__ crec,
+    int n_rows, int n_long, int ntile, const int32_t* __restrict__ active) {
+  constexpr int ZG = (MT + MTW - 1) / MTW;  // waves per (row disk, tile): groups of row tiles
+  __shared__ double sums[3][MTW * 8][64];
+  const int wave = (int)threadIdx.x >> 6, lane = threadIdx.x & 63;
+  // Block -> rows and waves (t, zi) of them.  Consecutive blocks are different rows
+  // and the row counts are padded to a multiple of 8, so that all tiles of a row run
+  // on one XCD and meet its symbols in that L2.  Long lists: one (t, zi) a block;
+  // short ones: a block takes wpr = 1, 2 or 4 consecutive (t, zi) of 4 / wpr rows.
+  const int per = ntile * ZG, nlp = (n_long + 7) & ~7;
+  const bool split = (int)blockIdx.x < nlp * per;  // block-uniform
+  int i, tz;
+  if (split) {
+    i = (int)blockIdx.x % nlp;
+    tz = (int)blockIdx.x / nlp;
+    if (i >= n_long) return;
+  } else {
+    const int wpr = per >= 4 ? 4 : per, rpb = 4 / wpr;
+    const int nrb = ((n_rows - n_long + rpb - 1) / rpb + 7) & ~7;
+    const int k = (int)blockIdx.x - nlp * per;
+    i = n_long + (k % nrb) * rpb + wave / wpr;
+    tz = (k / nrb) * wpr + wave % wpr;
+    if (i >= n_rows || tz >= per || wave >= rpb * wpr) return;
+  }
+  const int zi = tz % ZG, t = tz / ZG;
+  const int4 rw = crow[i];
+  const int p = rw.x, mt0 = MTW * zi, c0 = 8 * t;
   const int b = v.inst[p];
-  if (!con[b]) return;
-  const int c0 = 8 * t;
-  if (c0 >= R) return;
   const int Np = v.N[p], np_ = 2 * Np + 1, mtp = (np_ + 15) >> 4;
-  // tiles from 16 mtp on hold no mode of p and are never read
-  if (mt0 >= mtp) return;
+  if (mt0 >= mtp) return;  // no mode of p in these row tiles
   if (active) {
     bool any = false;
     for (int r = c0; r < min(R, c0 + 8); ++r) any |= active[b * R + r] != 0;
@@ -779,65 +833,66 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
     acc1[i] = mf_d4{0.0, 0.0, 0.0, 0.0};
     acc2[i] = mf_d4{0.0, 0.0, 0.0, 0.0};
   }
-  const int col = c0 + (j & 7);
-  const bool colok = col < R;
-  const int64_t cb = colok ? col_base(v.imode, b, R, col) : 0;
-  for (int e = nptr[p]; e < nptr[p + 1]; ++e) {
-    const int q = nql[e];
-    const int Nq = v.N[q], nq_ = 2 * Nq + 1, S = Np + Nq, KT = (nq_ + 3) >> 2;
-    const cplx* __restrict__ trow = v.t + v.toff[pair_index(v.idisk, v.ipair, b, p, q)] + S;
-    const bool flip = p > q;  // t^{pq}_s = (-1)^s t^{qp}_s
-    const cplx* __restrict__ zq = z + cb + v.moff[q];
-    for (int kt = 0; kt < KT; ++kt) {
-      const int n = 4 * kt + kq;
-      double bv = 0.0;
-      if (colok && n < nq_) {
-        const cplx zz = zq[n];
-        bv = j < 8 ? zz.x : zz.y;
-      }
+  // columns past R read column c0 (their sums are never read)
+  const int col = c0 + (j & 7) < R ? c0 + (j & 7) : c0;
+  const cplx* __restrict__ xc = x + col_base(v.imode, b, R, col);
+  const int e0 = rw.y + (split ? wave : 0), step = split ? 4 : 1;
+  const int top = 16 * mt0 + j - Np;  // first mode of this lane's rows
+  if (MTW == 1 || mt0 + 1 >= mtp) {
+    if (v.op_col) close_walk<1, MTW, true>(v, xc, v.imode[b], crec, e0, rw.z, step, Np, top, j, kq, acc1, acc2);
+    else close_walk<1, MTW, false>(v, xc, v.imode[b], crec, e0, rw.z, step, Np, top, j, kq, acc1, acc2);
+  } else {
+    if (v.op_col) close_walk<MTW, MTW, true>(v, xc, v.imode[b], crec, e0, rw.z, step, Np, top, j, kq, acc1, acc2);
+    else close_walk<MTW, MTW, false>(v, xc, v.imode[b], crec, e0, rw.z, step, Np, top, j, kq, acc1, acc2);
+  }
+  if (split) {
+    if (wave > 0) {
 #pragma unroll
-      for (int i = 0; i < MTW; ++i) {
-        const int mt = mt0 + i;
-        if (mt < mtp) {  // wave-uniform
-          const int m = 16 * mt + j;
-          cplx a = cmk(0.0, 0.0);
-          if (m < np_ && n < nq_) {
-            const int sv = (n - Nq) - (m - Np);
-            a = trow[sv];
-            if (flip && (sv & 1)) a = cmk(-a.x, -a.y);
-          }
-          acc1[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, bv, acc1[i], 0, 0, 0);
-          acc2[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, bv, acc2[i], 0, 0, 0);
+      for (int i = 0; i < MTW; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          sums[wave - 1][8 * i + q][lane] = acc1[i][q];
+          sums[wave - 1][8 * i + 4 + q][lane] = acc2[i][q];
         }
-      }
     }
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int w = 0; w < 3; ++w)
+#pragma unroll
+      for (int i = 0; i < MTW; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          acc1[i][q] += sums[w][8 * i + q][lane];
+          acc2[i][q] += sums[w][8 * i + 4 + q][lane];
+        }
   }
   // segment 0 of the group's tile t: [RP][npad][8]
   cplx* pbk = part + (gbase[dgrp[p]] + t) * blk + (int64_t)drow[p] * npad * 8 + (j & 7);
 #pragma unroll
   for (int i = 0; i < MTW; ++i) {
-    const int mt = mt0 + i;
-    if (mt >= MT) break;
 #pragma unroll
     for (int vv = 0; vv < 4; ++vv) {
       const double a1 = acc1[i][vv], a2 = acc2[i][vv];
       const double other = __shfl_xor(a2, 8, 64);
       const double val = j < 8 ? a1 - other : a1 + other;  // Re W (j < 8), Im W (j >= 8)
       const double im = __shfl_xor(val, 8, 64);
-      const int m = 16 * mt + 4 * vv + kq;
-      if (j < 8) pbk[(int64_t)m * 8] = cmk(val, im);
+      const int m = 16 * (mt0 + i) + 4 * vv + kq;
+      if (j < 8 && m < np_) pbk[(int64_t)m * 8] = cmk(val, im);
     }
   }
 }
 
 // z = x scaled by the column factor of its unknown (sqrt(a) J_n, or the
 // operator's column table), once per apply: the MFMA gathers then load one
-// value per panel element.
+// value per panel element.  With `skip`, only the instances not marked in it (the
+// others have no work-queue items).
 __global__ void k_apply_mfma_scale(DevView v, int R, const cplx* __restrict__ x, cplx* __restrict__ z,
-                                   const int32_t* __restrict__ active) {
+                                   const int32_t* __restrict__ active, const int32_t* __restrict__ skip) {
   // blockIdx.x: column (b, r); blockIdx.y: 256-unknown slice of that column
   const int col = blockIdx.x, b = col / R;
   if (active && active[col] == 0) return;  // columns that no longer iterate
+  if (skip && skip[b]) return;
   const int64_t Nb = v.imode[b + 1] - v.imode[b];
   const int64_t k = (int64_t)blockIdx.y * 256 + threadIdx.x;
   if (k >= Nb) return;
@@ -875,11 +930,11 @@ __global__ void k_apply_mfma_finish(DevView v, int R, const cplx* __restrict__ x
   const int64_t m = i - v.imode[b] - v.moff[p];
   const int gr = dgrp[p];
   const int t = r / RC, rc = r - (r / RC) * RC;
-  const int ns = gnseg[gr];
+  const int ns = gnseg[gr], nsr = drow[p] & ROW_EMPTY ? 0 : ns;
   const cplx* pr = part + (gbase[gr] + (int64_t)t * ns) * blk +
-                   ((int64_t)drow[p] * npad + m) * RC + rc;
+                   ((int64_t)(drow[p] & (ROW_EMPTY - 1)) * npad + m) * RC + rc;
   cplx w = cmk(0.0, 0.0);
-  for (int s = 0; s < ns; ++s) w = cadd(w, pr[(int64_t)s * blk]);
+  for (int s = 0; s < nsr; ++s) w = cadd(w, pr[(int64_t)s * blk]);
   if (wh && con[b]) {  // well-separated pairs: w_j += sum_f w^{f j} W_f[p][r]
     const int Lb = v.cL[b];
     const int64_t d0 = v.idisk[b], Mb = v.idisk[b + 1] - d0;
@@ -918,7 +973,7 @@ int circ_finish(mudiff_ctx* h, int R, const cplx* x, cplx* y, int op, const cplx
                 int npad, int RC, const int32_t* dgrp, const int32_t* drow, const int32_t* gnseg,
                 const int64_t* gbase, const int32_t* active, const cplx* wh, const int32_t* con,
                 const int32_t* con_h, const cplx* shift, hipStream_t s);
-int circ_launch(mudiff_ctx* h, int R, const cplx* z, cplx* zh, cplx* wh, const int32_t* citems,
+int circ_launch(mudiff_ctx* h, int R, const cplx* x, cplx* zh, cplx* wh, const int32_t* citems,
                 int n_citems, int var, const int32_t* con, const int32_t* con_h,
                 const int32_t* active, hipStream_t s);
 
@@ -942,9 +997,9 @@ static void mfma_build(const mudiff_ctx* h, int R, const MfmaChoice& c, MfmaSche
   S.gbase.clear();
   S.qlist.clear();
   S.citems.clear();
-  S.nptr.clear();
-  S.nq.clear();
-  S.rord.clear();
+  S.crow.clear();
+  S.crec.clear();
+  S.n_long = 0;
   S.close_rows = c.circ && h->circ && c.CT == 1;
   S.con.assign(h->B, 0);
   S.dgrp.assign(h->M_all, 0);
@@ -1071,21 +1126,34 @@ static void mfma_build(const mudiff_ctx* h, int R, const MfmaChoice& c, MfmaSche
   }
   S.n_pb = pb;
   if (S.close_rows) {
-    S.nptr.assign((size_t)h->M_all + 1, 0);
-    std::vector<int64_t> work((size_t)h->M_all, 0);  // k steps x row tiles of each row's list
+    std::vector<std::pair<int64_t, int32_t>> rows;  // (work: k steps x row tiles, row disk)
     for (int p = 0; p < h->M_all; ++p) {
-      if (S.con[(size_t)h->inst[p]])
-        for (int64_t e = h->near_off[p]; e < h->near_off[p + 1]; ++e) {
-          const int32_t q = h->near[(size_t)e];
-          S.nq.push_back(q);
-          work[(size_t)p] += (int64_t)((2 * h->N[q] + 4) / 4) * ((2 * h->N[p] + 16) / 16);
-        }
-      S.nptr[(size_t)p + 1] = (int32_t)S.nq.size();
+      if (!S.con[(size_t)h->inst[p]]) continue;
+      int64_t work = 0;
+      for (int64_t e = h->near_off[p]; e < h->near_off[p + 1]; ++e)
+        work += (int64_t)((2 * h->N[h->near[(size_t)e]] + 4) / 4) * ((2 * h->N[p] + 16) / 16);
+      if (work > 0) rows.push_back({work, p});
+      else S.drow[p] |= ROW_EMPTY;
     }
-    S.rord.resize((size_t)h->M_all);
-    for (int p = 0; p < h->M_all; ++p) S.rord[(size_t)p] = p;
-    std::stable_sort(S.rord.begin(), S.rord.end(),
-                     [&](int32_t u, int32_t w) { return work[(size_t)u] > work[(size_t)w]; });
+    std::stable_sort(rows.begin(), rows.end(), [&](const auto& u, const auto& w) {
+      const bool lu = h->near_off[u.second + 1] - h->near_off[u.second] > CLOSE_LONG;
+      const bool lw = h->near_off[w.second + 1] - h->near_off[w.second] > CLOSE_LONG;
+      return lu != lw ? lu : u.first > w.first;
+    });
+    for (const auto& rw : rows) {
+      const int p = rw.second, b = h->inst[p];
+      const int e0 = (int)(S.crec.size() / 4);
+      for (int64_t e = h->near_off[p]; e < h->near_off[p + 1]; ++e) {
+        const int q = h->near[(size_t)e];
+        S.crec.push_back((int32_t)h->moff[q]);
+        S.crec.push_back(h->N[q]);
+        S.crec.push_back((int32_t)h->toff[(size_t)pair_index(h->idisk.data(), h->ipair.data(), b, p, q)]);
+        S.crec.push_back(p > q ? 1 : 0);
+      }
+      const int e1 = (int)(S.crec.size() / 4);
+      S.n_long += e1 - e0 > CLOSE_LONG;
+      for (int32_t w : {p, e0, e1, 0}) S.crow.push_back(w);
+    }
   }
   std::stable_sort(its.begin(), its.end(), [](const It& a, const It& b) { return a.cost > b.cost; });
   S.items.resize(its.size() * MF_REC);
@@ -1097,7 +1165,7 @@ static void mfma_build(const mudiff_ctx* h, int R, const MfmaChoice& c, MfmaSche
 
 // Device view of a schedule's arrays.
 struct SchedDev {
-  const int32_t *items, *dgrp, *grow, *gnseg, *drow, *qlist, *citems, *con, *nptr, *nq, *rord;
+  const int32_t *items, *dgrp, *grow, *gnseg, *drow, *qlist, *citems, *con, *crow, *crec;
   const int64_t* gbase;
 };
 template <class F>
@@ -1110,9 +1178,8 @@ static void sched_arrays(const MfmaSched& S, F&& f) {  // f(vector, pointer of t
   f(S.qlist, &SchedDev::qlist);
   f(S.citems, &SchedDev::citems);
   f(S.con, &SchedDev::con);
-  f(S.nptr, &SchedDev::nptr);
-  f(S.nq, &SchedDev::nq);
-  f(S.rord, &SchedDev::rord);
+  f(S.crow, &SchedDev::crow);
+  f(S.crec, &SchedDev::crec);
 }
 static size_t sched_blob_bytes(const MfmaSched& S) {
   size_t n = align256(S.gbase.size() * 8);
@@ -1292,20 +1359,24 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, char* base, const cplx
   int rc = MUDIFF_OK;
   if (S.n_items > 0 && (rc = launch_fill_zero(head, 4, s)) != MUDIFF_OK) return rc;
   cplx* z = (cplx*)(base + L.z);
-  int64_t nbmax = 0;  // longest instance vector
-  for (int b = 0; b < h->B; ++b) nbmax = std::max(nbmax, h->imode[b + 1] - h->imode[b]);
-  if ((nbmax + 255) / 256 > 65535) return fail(MUDIFF_ERR_INVALID, "instance too large for the input scaling grid");
-  hipLaunchKernelGGL(k_apply_mfma_scale, dim3((unsigned)(h->B * S.R), (unsigned)((nbmax + 255) / 256)), dim3(256),
-                     0, s, h->dv, S.R, x, z, active);
-  HIP_TRY(hipGetLastError());
+  if (S.n_items > 0) {  // the work queue's input; the circulant form's kernels scale as they read
+    int64_t nbmax = 0;  // longest instance vector
+    for (int b = 0; b < h->B; ++b) nbmax = std::max(nbmax, h->imode[b + 1] - h->imode[b]);
+    if ((nbmax + 255) / 256 > 65535) return fail(MUDIFF_ERR_INVALID, "instance too large for the input scaling grid");
+    hipLaunchKernelGGL(k_apply_mfma_scale, dim3((unsigned)(h->B * S.R), (unsigned)((nbmax + 255) / 256)),
+                       dim3(256), 0, s, h->dv, S.R, x, z, active, S.close_rows ? d.con : nullptr);
+    HIP_TRY(hipGetLastError());
+  }
   prof_mark(h, s, 1);
   cplx* wh = nullptr;
   const int32_t* con = d.con;
-  // direct-form work (the work queue and the close-pair rows): in the straggler
-  // phase of a solve with the circulant form it runs on the second stream,
-  // beside the transforms and products, which share none of its outputs (there
-  // every launch is small and latency-bound; on a full batch the close-pair
-  // waves would crowd the products and transforms out of the compute units)
+  // direct-form work: in the straggler phase of a solve with the circulant form the
+  // work queue and the close-pair rows run on the second stream, beside the
+  // transforms and products, which share none of their outputs (there every launch
+  // is small and latency-bound; on a full batch the close-pair waves would crowd
+  // the products and transforms out of the compute units).  A short queue, that of
+  // a few instances outside the form, always runs there: it leaves most of the chip
+  // idle for as long as its items take.
   mf_fn fn = nullptr;  // checked before the fork, so that every error leaves the streams joined
   if (S.n_items > 0) {
     const int TL = 4 * kt + 16 * mt - 1;
@@ -1317,14 +1388,15 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, char* base, const cplx
   }
   if (S.close_rows && (mt < 1 || mt > 4)) return fail(MUDIFF_ERR_INVALID, "close pairs: orders out of range");
   hipStream_t cs = s;
-  const bool fork = h->mfma_tail && S.c.circ && (S.n_items > 0 || S.close_rows);
+  const bool fork = S.c.circ && (h->mfma_tail ? S.n_items > 0 || S.close_rows
+                                               : S.close_rows && S.n_items > 0 && S.n_items <= 4 * h->n_cu);
   if (fork) {
     if ((rc = aux_stream(h)) != MUDIFF_OK) return rc;
     HIP_TRY(hipEventRecord(h->fork_ev, s));
     HIP_TRY(hipStreamWaitEvent(h->aux, h->fork_ev, 0));
     cs = h->aux;
   }
-  auto launch_direct = [&]() -> int {
+  auto launch_queue = [&](hipStream_t cs) -> int {
     if (S.n_items > 0) {
       // persistent grid: as many workgroups as are resident at once
       int per_cu = 0;
@@ -1336,35 +1408,44 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, char* base, const cplx
                          S.n_items, head, part, S.blk, S.npad, kt, S.c.RP, S.c.CT, d.grow, d.qlist);
       HIP_TRY(hipGetLastError());
     }
-    if (S.close_rows) {  // every row of the form writes its segment (zeros without close pairs)
-      typedef void (*close_fn)(DevView, int, const cplx*, cplx*, int64_t, int, const int32_t*,
-                               const int32_t*, const int64_t*, const int32_t*, const int32_t*,
-                               const int32_t*, const int32_t*, const int32_t*);
-      static const close_fn kClose[5] = {nullptr, k_apply_close<1, 1>, k_apply_close<2, 2>,
-                                         k_apply_close<3, 2>, k_apply_close<4, 2>};
-      const unsigned zg = mt > 2 ? 2u : 1u;  // groups of two row tiles
-      hipLaunchKernelGGL(kClose[mt], dim3((unsigned)h->M_all, (unsigned)S.ntile, zg), dim3(64), 0, cs, h->dv,
-                         S.R, (const cplx*)z, part, S.blk, S.npad, d.dgrp, d.drow, d.gbase, d.nptr, d.nq, con,
-                         active, d.rord);
-      HIP_TRY(hipGetLastError());
-    }
+    return MUDIFF_OK;
+  };
+  auto launch_close = [&](hipStream_t cs) -> int {
+    const int n_rows = (int)(S.crow.size() / 4);
+    if (n_rows == 0) return MUDIFF_OK;
+    typedef void (*close_fn)(DevView, int, const cplx*, cplx*, int64_t, int, const int32_t*, const int32_t*,
+                             const int64_t*, const int4*, const int4*, int, int, int, const int32_t*);
+    static const close_fn kClose[5] = {nullptr, k_apply_close<1, 1>, k_apply_close<2, 2>,
+                                       k_apply_close<3, 2>, k_apply_close<4, 2>};
+    // the block -> row mapping of the kernel
+    const int64_t per = (int64_t)S.ntile * (mt > 2 ? 2 : 1);  // waves per row
+    const int64_t wpr = std::min<int64_t>(per, 4), rpb = 4 / wpr, n_short = n_rows - S.n_long;
+    const int64_t nb = ((S.n_long + 7) & ~7) * per +
+                       (((n_short + rpb - 1) / rpb + 7) & ~(int64_t)7) * ((per + wpr - 1) / wpr);
+    if (nb >= ((int64_t)1 << 31)) return fail(MUDIFF_ERR_INVALID, "close pairs: too many tiles");
+    hipLaunchKernelGGL(kClose[mt], dim3((unsigned)nb), dim3(256), 0, cs, h->dv, S.R, x, part, S.blk, S.npad,
+                       d.dgrp, d.drow, d.gbase, (const int4*)d.crow, (const int4*)d.crec, n_rows, S.n_long,
+                       S.ntile, active);
+    HIP_TRY(hipGetLastError());
     return MUDIFF_OK;
   };
   if (fork) {
-    if ((rc = launch_direct()) != MUDIFF_OK) return rc;
+    if ((rc = launch_queue(cs)) != MUDIFF_OK) return rc;
+    if (h->mfma_tail && (rc = launch_close(cs)) != MUDIFF_OK) return rc;
     HIP_TRY(hipEventRecord(h->join_ev, cs));
   }
   if (S.c.circ) {  // well-separated pairs of the marked instances
     cplx* zh = (cplx*)(base + L.zh);
     wh = (cplx*)(base + L.wh);
-    rc = circ_launch(h, S.R, z, zh, wh, d.citems, S.n_citems, S.cvar, con, S.con.data(), active, s);
+    rc = circ_launch(h, S.R, x, zh, wh, d.citems, S.n_citems, S.cvar, con, S.con.data(), active, s);
     if (rc != MUDIFF_OK) return rc;
   } else {
     prof_mark(h, s, 2);
     prof_mark(h, s, 3);
   }
+  if (!(fork && h->mfma_tail) && (rc = launch_close(s)) != MUDIFF_OK) return rc;
   if (fork) HIP_TRY(hipStreamWaitEvent(s, h->join_ev, 0));
-  else if ((rc = launch_direct()) != MUDIFF_OK) return rc;
+  else if ((rc = launch_queue(s)) != MUDIFF_OK) return rc;
   prof_mark(h, s, 4);
   if (S.c.circ) {
     rc = circ_finish(h, S.R, x, y, op, (const cplx*)part, S.blk, S.npad, RC,
