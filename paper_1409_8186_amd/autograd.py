@@ -34,7 +34,11 @@ class FarFieldMisfit(torch.autograd.Function):
         inst = [(c[off[b]:off[b + 1]], a[off[b]:off[b + 1]], nm[off[b]:off[b + 1]], kk[b])
                 for b in range(len(off) - 1)]
         dev = centers.device if centers.is_cuda else torch.device("cuda")
-        P = Problem(inst, device=str(dev))
+        # the circulant form carries the solves of 8 and more columns (orders up to 31);
+        # the first apply times it against the direct form
+        R = (betas if isinstance(betas, torch.Tensor) else np.asarray(betas)).reshape(len(inst), -1).shape[1]
+        circulant = R >= 8 and int(nm.max()) <= 31
+        P = Problem(inst, device=str(dev), circulant=circulant)
         loss, dc, da, dk = P.grad(betas, thetas, target, restart=opts.get("restart", 50),
                                   tol=opts.get("tol", 1e-10), maxit=opts.get("maxit", 20000))
         P.close()

@@ -756,6 +756,20 @@ std::vector<int> circ_variants(int R) {
   if (R >= 12) return {5, 6, 11, 20, 29, 30};
   return {6, 7, 21};
 }
+// The variants that are timed on first use of R.  The three-product tiles were the
+// fastest of the above from 12 columns on at every size tried (us, tile rows x
+// columns, K step): 1,000 disks x 256: 128x32 8 2,329, 128x64 8 2,411, 64x32 8 2,741,
+// best four-product tile 2,930; 400 x 32: 64x32 94, 128x32 98 (400 rows fill 7 tiles
+// of 64 but 3.1 of 128); 200 x 32: 128x32 16 32.8, 8 33.4, 64x32 39; 100 x 4 x 64:
+// 128x64 33.7, 128x32 34.5; 1,000 x 16: 128x16 8 265; 300 x 12: 128x16 16 38.  Below 12
+// columns half of a 16-column tile would idle: 64x8 16 and 128x8 8 (1,000 x 8: 268 and
+// 248; 200 x 8: 21 and 26).
+std::vector<int> circ_timed(int R) {
+  if (R >= 48) return {23, 28, 26};
+  if (R >= 24) return {23, 28, 24};
+  if (R >= 12) return {29, 30};
+  return {7, 21};
+}
 void circ_tile(int var, int* bm, int* bn) {
   *bm = kCircVar[var].bm;
   *bn = kCircVar[var].bn;

@@ -967,6 +967,7 @@ static bool use_mfma(const mudiff_ctx* h, int R) {
 
 int circ_variant(int R);
 std::vector<int> circ_variants(int R);
+std::vector<int> circ_timed(int R);
 void circ_tile(int var, int* bm, int* bn);
 void circ_var_dims(int var, int* bm, int* bn, int* bk, int* db, int* nt, int* mult);
 int circ_finish(mudiff_ctx* h, int R, const cplx* x, cplx* y, int op, const cplx* part, int64_t blk,
@@ -1252,6 +1253,49 @@ static std::vector<MfmaChoice> mfma_candidates(int R) {
   return out;
 }
 
+// Column-disk segment of a tile: the longest of 64, 32, .. 4 that cuts the
+// instances in the work queue (all of them, or with the circulant form those
+// outside it) into at least four items per compute unit; 4 when none does, 0 (whole
+// instances) when that already gives as many.  A workgroup spends 4 to 5 us on each
+// column disk of an item whatever the tile (two barriers and a gather that has one
+// disk's time to arrive), so few items leave the chip idle for as long as the
+// longest takes (30 disks, 8 columns: 148 us with whole instances, 34 with segments
+// of 4; 100 disks, 16 columns 190 with segments of 32, 92 of 4), while at two items
+// a compute unit a launch still ends unevenly (200 disks, 64 columns: 847 us with
+// segments of 64, 796 of 32) and ever shorter ones add partial sums.
+static int auto_segment(const mudiff_ctx* h, int R, int CT, int RP, bool circ) {
+  const int64_t tiles = (R + 8 * CT - 1) / (8 * CT), want = 4 * (int64_t)h->n_cu;
+  int64_t mmax = 0;
+  auto items = [&](int64_t qs) {
+    int64_t n = 0;
+    for (int b = 0; b < h->B; ++b) {
+      if (circ && h->circ_on[(size_t)b]) continue;
+      const int64_t M = h->idisk[b + 1] - h->idisk[b];
+      mmax = std::max(mmax, M);
+      n += (M + RP - 1) / RP * tiles * (qs > 0 ? (M + qs - 1) / qs : 1);
+    }
+    return n;
+  };
+  if (items(0) >= want || mmax <= 4) return 0;
+  for (int qs = 64; qs > 4; qs /= 2)
+    if (qs < mmax && items(qs) >= want) return qs;
+  return 4;
+}
+
+// The tiles that are timed on first use of R (mfma_candidates are those that a
+// caller may fix): eight waves, the segment by rule.  Four waves were slower by
+// half wherever the queue was timed (100 disks x 4, 64 columns: 684-739 against
+// 367-458 us).  In the circulant form the queue holds the instances outside it and
+// the close pairs run on k_apply_close, which takes 8-column tiles.
+static std::vector<MfmaChoice> mfma_timed(const mudiff_ctx* h, int R, bool circ) {
+  std::vector<MfmaChoice> out;
+  for (int ct : {1, 2, 4}) {
+    if (ct > 1 && (circ || 8 * (ct / 2) >= R)) continue;
+    out.push_back(MfmaChoice{ct, 8 / ct, auto_segment(h, R, ct, 8 / ct, circ), 512, circ});
+  }
+  return out;
+}
+
 // The circulant form is a candidate when the tables hold it and some
 // instance is worth it (and the caller has not switched it off for R).
 static bool circ_usable(const mudiff_ctx* h, int R) {
@@ -1462,37 +1506,55 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, char* base, const cplx
   return MUDIFF_OK;
 }
 
-// Largest apply scratch any candidate choice needs for R.
+// Apply scratch that covers every choice for R: the tiles that a caller may fix,
+// the timed ones and the straggler schedule, in both forms.  The partial blocks
+// are those of the direct form with its shortest segments (a close-pair item never
+// has more column disks than its instance), the schedule's arrays are bounded.
 static size_t mfma_scratch_bytes(mudiff_ctx* h, int R) {
   auto f = h->mfma_bytes.find(R);
   if (f != h->mfma_bytes.end()) return f->second;
-  size_t mx = 0;
-  for (MfmaChoice c : mfma_candidates(R)) {
-    for (int circ = 0; circ < (h->circ ? 2 : 1); ++circ)
-      for (int qs : {c.QS, MFMA_TAIL_QS}) {  // also the short-segment form used for stragglers
-        c.QS = qs;
-        c.circ = circ != 0;
-        std::vector<int> vars = circ ? circ_variants(R) : std::vector<int>{-1};
-        for (int cv : vars) {
-          c.cvar = cv;
-          MfmaSched S;
-          mfma_build(h, R, c, S);
-          mx = std::max(mx, mfma_scratch_layout(h, S).total);
-        }
-      }
+  const int64_t npad = 16 * ((2 * h->Nmax + 1 + 15) / 16), n_near = (int64_t)h->near.size();
+  int64_t part = 0, items = 0, groups = 0, rows = 0;
+  std::vector<MfmaChoice> cs = mfma_candidates(R);
+  for (MfmaChoice& c : cs) c.QS = MFMA_TAIL_QS;
+  for (const MfmaChoice& c : mfma_timed(h, R, false)) cs.push_back(c);
+  if (h->circ)
+    for (const MfmaChoice& c : mfma_timed(h, R, true)) cs.push_back(c);
+  for (const MfmaChoice& c : cs) {
+    const int64_t tiles = (R + 8 * c.CT - 1) / (8 * c.CT);
+    int64_t n_pb = 0, g = 0;
+    for (int b = 0; b < h->B; ++b) {
+      const int64_t M = h->idisk[b + 1] - h->idisk[b], gb = (M + c.RP - 1) / c.RP;
+      // a timed choice of the circulant form has its short segments outside the form only
+      const bool whole = c.circ && h->circ_on[(size_t)b];
+      n_pb += gb * tiles * (c.QS > 0 && !whole ? (M + c.QS - 1) / c.QS : 1);
+      g += gb;
+    }
+    part = std::max(part, n_pb * c.RP * npad * 8 * c.CT);
+    items = std::max(items, n_pb);
+    groups = std::max(groups, g);
+    rows = std::max(rows, g * c.RP);
   }
+  int64_t citems = 0;
+  const int64_t bn = R < 24 ? 8 : 32;  // narrowest product tile for R (64 rows: the lowest)
+  if (h->circ)
+    for (int b = 0; b < h->B; ++b)
+      citems += (int64_t)h->cL[b] * ((h->idisk[b + 1] - h->idisk[b] + 63) / 64) * ((R + bn - 1) / bn);
+  const size_t zw = h->circ ? (size_t)R * h->cZ_all * 16 : 0;
+  const size_t sched = (size_t)items * MF_REC * 4 + (size_t)groups * 12 + (size_t)rows * 4 +
+                       (size_t)h->M_all * 8 + (size_t)h->B * 4 + (size_t)n_near * 4 + (size_t)citems * 16 +
+                       (h->circ ? (size_t)h->M_all * 16 + (size_t)n_near * 16 : 0) + 16 * 256;
+  const size_t mx = align256(4) + align256((size_t)part * 16) + align256((size_t)R * h->N_all * 16) +
+                    2 * align256(zw) + align256(sched);
   h->mfma_bytes[R] = mx;
   return mx;
 }
 
-// Pick the tile choice for R by timing every candidate on x -> y (outputs
-// are overwritten; the inputs only need to be finite), then leave the chosen
-// schedule uploaded at `scratch`.  Segmented candidates are skipped when no
-// instance has more disks than a segment: their schedule is the unsegmented one.
+// Pick the tile choice for R by timing the mfma_timed tiles and the product
+// variants worth it on x -> y (outputs are overwritten; the inputs only need to be
+// finite).
 static int mfma_autotune(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scratch,
                          hipStream_t s) {
-  int64_t mmax = 0;
-  for (int b = 0; b < h->B; ++b) mmax = std::max(mmax, h->idisk[b + 1] - h->idisk[b]);
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
@@ -1503,13 +1565,10 @@ static int mfma_autotune(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scr
   auto fc = h->circ_modes.find(R);
   const int cmode = fc != h->circ_modes.end() ? fc->second : -1;
   const bool cu = circ_usable(h, R);
-  if (cu)  // the circulant form first: it usually sets the bar the direct tiles then fail
-    for (MfmaChoice c : mfma_candidates(R)) {
-      c.circ = true;
-      cands.push_back(c);
-    }
+  // the circulant form first: it usually sets the bar the direct tiles then fail
+  if (cu) cands = mfma_timed(h, R, true);
   if (cmode != 1 || !cu)
-    for (const MfmaChoice& c : mfma_candidates(R)) cands.push_back(c);
+    for (const MfmaChoice& c : mfma_timed(h, R, false)) cands.push_back(c);
   // The direct form's work (8 flops per complex multiply-add over every
   // ordered pair) at the FP64 matrix-core peak, 78.6 TFLOP/s: no direct tile
   // beats it, so once a candidate's pair of applies is faster than twice that,
@@ -1561,49 +1620,18 @@ static int mfma_autotune(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scr
     }
     return ms;
   };
-  for (const MfmaChoice& c : cands) {
-    if (c.QS > 0 && mmax <= c.QS) continue;
+  const std::vector<int> cvars = circ_timed(R);
+  for (MfmaChoice c : cands) {
     if (!c.circ && best > 0.0f && direct_floor_ms > best) continue;
+    if (c.circ) c.cvar = cvars[0];
     time_one(c);
     if (rc != MUDIFF_OK) break;
   }
-  if (rc == MUDIFF_OK && bc.circ) {  // then the per-frequency product variants on that tile
-    const MfmaChoice base = bc;
-    std::vector<std::pair<float, MfmaChoice>> seen{{best, base}};
-    for (int cv : circ_variants(R)) {
-      if (cv == circ_variant(R)) continue;
-      MfmaChoice c = base;
-      c.cvar = cv;
-      const float ms = time_one(c);
-      if (rc != MUDIFF_OK) break;
-      if (ms > 0.0f) seen.push_back({ms, c});
-    }
-    // variants a few percent apart swap places from one timing to the next:
-    // the three fastest are timed three times more and ranked by their mean
-    if (rc == MUDIFF_OK && seen.size() > 1) {
-      std::stable_sort(seen.begin(), seen.end(),
-                       [](const std::pair<float, MfmaChoice>& a, const std::pair<float, MfmaChoice>& b) {
-                         return a.first < b.first;
-                       });
-      seen.resize(std::min<size_t>(seen.size(), 3));
-      float bmean = 0.0f;
-      MfmaChoice bbest = bc;
-      for (const auto& sc : seen) {
-        float sum = 0.0f;
-        for (int rep = 0; rep < 3 && rc == MUDIFF_OK; ++rep) {
-          best = 0.0f;  // time every repetition in full
-          sum += time_one(sc.second);
-        }
-        if (rc != MUDIFF_OK) break;
-        if (bmean == 0.0f || sum / 3.0f < bmean) {
-          bmean = sum / 3.0f;
-          bbest = sc.second;
-        }
-      }
-      if (rc == MUDIFF_OK) {
-        bc = bbest;
-        best = bmean;
-      }
+  if (rc == MUDIFF_OK && bc.circ) {  // then the other per-frequency product variants
+    MfmaChoice c = bc;
+    for (size_t k = 1; k < cvars.size() && rc == MUDIFF_OK; ++k) {
+      c.cvar = cvars[k];
+      time_one(c);
     }
   }
   (void)hipEventDestroy(e0);

@@ -340,19 +340,31 @@ bool sizes_of(int B, const int64_t* disk_off, const int32_t* n_modes, int64_t* N
   for (int b = 0; b < B; ++b) {
     int64_t d0 = disk_off[b], d1 = disk_off[b + 1];
     if (d1 <= d0) return false;
+    const int64_t M = d1 - d0;
+    int64_t sum = 0;
     for (int64_t p = d0; p < d1; ++p) {
       if (n_modes[p] < 0 || n_modes[p] > MUDIFF_MAX_NP) return false;
-      *N_all += 2 * n_modes[p] + 1;
-      *D_all += n_modes[p] + 2;
-      for (int64_t q = p + 1; q < d1; ++q) {
-        *P_all += 1;
-        *T_all += 2 * (int64_t)(n_modes[p] + n_modes[q]) + 1;
-      }
+      sum += n_modes[p];
     }
+    *N_all += 2 * sum + M;
+    *D_all += sum + 2 * M;
+    *P_all += M * (M - 1) / 2;
+    *T_all += 2 * (M - 1) * sum + M * (M - 1) / 2;  // sum over p < q of 2 (N_p + N_q) + 1
   }
   return true;
 }
 }  // namespace
+
+// Distance of two centers, and its square (relative rounding below PAIR_EPS unless
+// it over- or underflows).
+#define PAIR_EPS 1e-14
+static inline double pair_dist(const double* c, int64_t p, int64_t q) {
+  return std::hypot(c[2 * p] - c[2 * q], c[2 * p + 1] - c[2 * q + 1]);
+}
+static inline double pair_d2(const double* c, int64_t p, int64_t q) {
+  const double dx = c[2 * p] - c[2 * q], dy = c[2 * p + 1] - c[2 * q + 1];
+  return dx * dx + dy * dy;
+}
 
 // ------------------------------------------------------------------ C ABI
 extern "C" size_t mudiff_tables_workspace_size(int B, const int64_t* disk_off,
@@ -397,17 +409,22 @@ extern "C" int mudiff_tables(int B, const int64_t* disk_off, const double* cente
   if (flags & MUDIFF_TABLES_CIRCULANT)
     for (int64_t p = 0; p < M; ++p)
       if (n_modes[p] > 31) return fail(MUDIFF_ERR_INVALID, "the circulant form needs N_p <= 31");
-  // disjointness (sec. 2): b_pq > a_p + a_q inside every instance
+  // disjointness (sec. 2): b_pq > a_p + a_q inside every instance.  Squares settle
+  // all but the pairs within rounding of the bound, which take the distance itself.
   std::vector<double> dmin(B, HUGE_VAL);
-  for (int b = 0; b < B; ++b)
+  for (int b = 0; b < B; ++b) {
+    double d2min = HUGE_VAL;
     for (int64_t p = disk_off[b]; p < disk_off[b + 1]; ++p)
       for (int64_t q = p + 1; q < disk_off[b + 1]; ++q) {
-        double d = std::hypot(centers[2 * p] - centers[2 * q], centers[2 * p + 1] - centers[2 * q + 1]);
-        dmin[b] = std::min(dmin[b], d);
-        if (!(d > radii[p] + radii[q]))
+        const double d2 = pair_d2(centers, p, q), s = radii[p] + radii[q];
+        d2min = std::min(d2min, d2);
+        if (d2 > s * s * (1.0 + PAIR_EPS) && d2 > 1e-280 && d2 < HUGE_VAL) continue;
+        if (!(pair_dist(centers, p, q) > s))
           return fail(MUDIFF_ERR_OVERLAP, "disks " + std::to_string(p) + " and " +
                                                std::to_string(q) + " overlap or touch");
       }
+    dmin[b] = std::sqrt(d2min);
+  }
   int64_t N_all, P_all, T_all, D_all;
   if (!sizes_of(B, disk_off, n_modes, &N_all, &P_all, &T_all, &D_all))
     return fail(MUDIFF_ERR_INVALID, "bad sizes");
@@ -552,8 +569,10 @@ extern "C" int mudiff_tables(int B, const int64_t* disk_off, const double* cente
       double far_w = 0.0, all_w = 0.0;
       for (int64_t p = disk_off[b]; p < disk_off[b + 1]; ++p)
         for (int64_t q = p + 1; q < disk_off[b + 1]; ++q, ++g) {
-          const double d = std::hypot(centers[2 * p] - centers[2 * q], centers[2 * p + 1] - centers[2 * q + 1]);
-          const bool nr = k[b] * d < (double)(n_modes[p] + n_modes[q]);
+          const double x2 = k[b] * k[b] * pair_d2(centers, p, q), S = (double)(n_modes[p] + n_modes[q]);
+          // as for disjointness: near the bound by k b_pq itself
+          const bool nr = x2 > S * S * (1.0 + PAIR_EPS) && x2 < HUGE_VAL && k[b] > 1e-100 ? false
+                          : k[b] * pair_dist(centers, p, q) < S;
           const double w = 2.0 * (2.0 * n_modes[p] + 1) * (2.0 * n_modes[q] + 1);
           all_w += w;
           if (nr) {
