@@ -12,6 +12,7 @@ from __future__ import annotations
 import numpy as np
 import torch
 
+from . import _lib as L
 from .api import Problem
 
 
@@ -39,8 +40,12 @@ class FarFieldMisfit(torch.autograd.Function):
         R = (betas if isinstance(betas, torch.Tensor) else np.asarray(betas)).reshape(len(inst), -1).shape[1]
         circulant = R >= 8 and int(nm.max()) <= 31
         P = Problem(inst, device=str(dev), circulant=circulant)
-        loss, dc, da, dk = P.grad(betas, thetas, target, restart=opts.get("restart", 50),
-                                  tol=opts.get("tol", 1e-10), maxit=opts.get("maxit", 20000))
+        restart = opts.get("restart", 50)
+        # s-step solves for many columns (restarts up to 64): their basis sweeps are half of a
+        # lockstep step (4 x 100 disks x 64 columns: 179 against 249 ms per gradient)
+        flags = L.SSTEP | L.sstep_size(10) if R >= 8 and 20 <= restart <= 64 else 0
+        loss, dc, da, dk = P.grad(betas, thetas, target, restart=restart, tol=opts.get("tol", 1e-10),
+                                  maxit=opts.get("maxit", 20000), flags=flags)
         P.close()
         inst_of = torch.as_tensor(np.repeat(np.arange(len(off) - 1), np.diff(off)), device=dev)
         ctx.save_for_backward(dc, da, dk, inst_of)
