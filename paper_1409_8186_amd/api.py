@@ -176,26 +176,31 @@ class Problem:
         L.check(self.lib.mudiff_set_circulant(self.h, R, mode))
 
     # per-frequency product tiles (rows, cols, kstep, stages, threads, real products per
-    # complex product) timed for R
+    # complex product) that set_circulant_tile takes for R (the library times two or
+    # three of them on first use)
     CIRCULANT_TILES = {48: [(64, 32, 16, 2, 256, 4), (64, 32, 16, 3, 256, 4), (128, 32, 16, 2, 512, 4),
                             (128, 32, 16, 3, 512, 4), (128, 32, 8, 3, 512, 4), (128, 32, 8, 2, 512, 4),
                             (64, 32, 8, 3, 256, 4), (128, 64, 8, 3, 512, 4), (128, 64, 16, 3, 512, 4),
                             (128, 32, 4, 2, 512, 4), (128, 32, 8, 2, 1024, 4), (64, 32, 8, 2, 256, 4),
                             (256, 32, 8, 2, 512, 4), (128, 32, 8, 2, 512, 3), (128, 32, 16, 2, 512, 3),
                             (128, 32, 8, 3, 512, 3), (128, 64, 8, 2, 512, 3), (256, 32, 8, 2, 512, 3),
-                            (64, 32, 8, 2, 256, 3)],
+                            (64, 32, 8, 2, 256, 3), (64, 32, 16, 3, 512, 3), (32, 64, 16, 3, 512, 3),
+                            (64, 32, 8, 2, 512, 3), (32, 32, 16, 3, 256, 3)],
                        24: [(64, 32, 16, 2, 256, 4), (64, 32, 32, 2, 256, 4), (128, 32, 16, 2, 256, 4),
                             (64, 32, 16, 3, 256, 4), (128, 32, 16, 2, 512, 4), (128, 32, 16, 3, 512, 4),
                             (128, 32, 8, 3, 512, 4), (128, 32, 8, 2, 512, 4), (64, 32, 8, 3, 256, 4),
                             (64, 32, 8, 2, 256, 4), (128, 32, 8, 2, 512, 3), (128, 32, 16, 2, 512, 3),
-                            (64, 32, 8, 2, 256, 3)],
+                            (64, 32, 8, 2, 256, 3), (64, 32, 16, 3, 512, 3), (32, 32, 16, 3, 256, 3),
+                            (80, 32, 16, 2, 640, 3), (64, 16, 16, 3, 256, 3)],
                        12: [(128, 16, 16, 2, 256, 4), (128, 8, 16, 2, 256, 4), (128, 16, 16, 3, 256, 4),
-                            (128, 16, 8, 2, 256, 4), (128, 16, 8, 2, 256, 3), (128, 16, 16, 2, 256, 3)],
-                       1: [(128, 8, 16, 2, 256, 4), (64, 8, 16, 2, 256, 4), (128, 8, 8, 2, 256, 4)]}
+                            (128, 16, 8, 2, 256, 4), (128, 16, 8, 2, 256, 3), (128, 16, 16, 2, 256, 3),
+                            (32, 32, 16, 3, 256, 3), (64, 16, 16, 3, 256, 3), (32, 16, 16, 3, 128, 3)],
+                       1: [(128, 8, 16, 2, 256, 4), (64, 8, 16, 2, 256, 4), (128, 8, 8, 2, 256, 4),
+                           (64, 16, 16, 3, 256, 3), (16, 8, 16, 3, 64, 4)]}
 
     @classmethod
     def circulant_tiles(cls, R: int) -> list:
-        """Per-frequency product tiles (rows, cols, kstep, stages, threads) timed for R."""
+        """Per-frequency product tiles (rows, cols, kstep, stages, threads, products) for R."""
         for lo in (48, 24, 12, 1):
             if R >= lo:
                 return cls.CIRCULANT_TILES[lo]

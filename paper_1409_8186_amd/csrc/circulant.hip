@@ -745,30 +745,44 @@ static const CircVariant kCircVar[] = {
     {64, 32, 8, 2, 256, 3, k_circ_gemm<2, 2, 2, 1, 8, true, false, true>},
     {128, 16, 8, 2, 256, 3, k_circ_gemm<4, 1, 2, 1, 8, true, false, true>},
     {128, 16, 16, 2, 256, 3, k_circ_gemm<4, 1, 2, 1, 16, true, false, true>},
+    // one tile per wave: small accumulators, many waves per SIMD
+    {64, 32, 16, 3, 512, 3, k_circ_gemm<4, 2, 1, 1, 16, true, true, true>},
+    {32, 64, 16, 3, 512, 3, k_circ_gemm<2, 4, 1, 1, 16, true, true, true>},
+    {64, 32, 8, 2, 512, 3, k_circ_gemm<4, 2, 1, 1, 8, true, false, true>},
+    {32, 32, 16, 3, 256, 3, k_circ_gemm<2, 2, 1, 1, 16, true, true, true>},
+    {80, 32, 16, 2, 640, 3, k_circ_gemm<5, 2, 1, 1, 16, true, false, true>},
+    {64, 16, 16, 3, 256, 3, k_circ_gemm<4, 1, 1, 1, 16, true, true, true>},
+    {32, 16, 16, 3, 128, 3, k_circ_gemm<2, 1, 1, 1, 16, true, true, true>},
+    {16, 8, 16, 3, 64, 4, k_circ_gemm<1, 1, 1, 1, 16, true, true>},
 };
 #define N_CIRC_VAR ((int)(sizeof(kCircVar) / sizeof(kCircVar[0])))
 
-// Default product variant for R columns, and the variants worth timing.
-int circ_variant(int R) { return R >= 48 ? 2 : (R >= 24 ? 2 : (R >= 12 ? 5 : 6)); }
+// Product variant for R columns where none was timed, and the variants that a caller may fix.
+int circ_variant(int R) { return R >= 48 ? 31 : (R >= 24 ? 34 : (R >= 9 ? 36 : 7)); }
 std::vector<int> circ_variants(int R) {
-  if (R >= 48) return {2, 8, 9, 10, 12, 13, 14, 15, 16, 17, 18, 19, 22, 23, 24, 25, 26, 27, 28};
-  if (R >= 24) return {2, 3, 4, 8, 9, 10, 12, 13, 14, 19, 23, 24, 28};
-  if (R >= 12) return {5, 6, 11, 20, 29, 30};
-  return {6, 7, 21};
+  if (R >= 48) return {2, 8, 9, 10, 12, 13, 14, 15, 16, 17, 18, 19, 22, 23, 24, 25, 26, 27, 28, 31, 32, 33, 34};
+  if (R >= 24) return {2, 3, 4, 8, 9, 10, 12, 13, 14, 19, 23, 24, 28, 31, 34, 35, 36};
+  if (R >= 12) return {5, 6, 11, 20, 29, 30, 34, 36, 37};
+  return {6, 7, 21, 36, 38};
 }
-// The variants that are timed on first use of R.  The three-product tiles were the
-// fastest of the above from 12 columns on at every size tried (us, tile rows x
-// columns, K step): 1,000 disks x 256: 128x32 8 2,329, 128x64 8 2,411, 64x32 8 2,741,
-// best four-product tile 2,930; 400 x 32: 64x32 94, 128x32 98 (400 rows fill 7 tiles
-// of 64 but 3.1 of 128); 200 x 32: 128x32 16 32.8, 8 33.4, 64x32 39; 100 x 4 x 64:
-// 128x64 33.7, 128x32 34.5; 1,000 x 16: 128x16 8 265; 300 x 12: 128x16 16 38.  Below 12
-// columns half of a 16-column tile would idle: 64x8 16 and 128x8 8 (1,000 x 8: 268 and
-// 248; 200 x 8: 21 and 26).
+// The variants that are timed on first use of R, the fastest of the above at the sizes
+// tried.  A tile is a matter of how many workgroups there are for the 256 compute units
+// and of the waves that hide the loads: one 16 x 16 tile per wave, with two K steps of 16
+// in flight, beats two or four per wave nearly everywhere (us, rows x columns of the tile,
+// disks x columns):  1,000 x 256: 64x32 2,292, 128x64 with 2 x 2 tiles per wave 2,410,
+// four-product form 2,930; 1,000 x 64: 32x64 636, 128x64 680; 700 x 100: 32x64 560, 128x64
+// 648; 4 x 100 x 64: 64x32 with K steps of 8 35.1, 128x64 35.3; 400 x 32: 32x32 73, 64x32 80,
+// four waves of 2 x 1 tiles 94; 200 x 32: 80x32 27.2 (243 workgroups; 64x32 324: 32.5,
+// 128x32 162: 33.2); 100 x 32: 64x32 14.7, 2 x 1 tiles 19.7; 40 x 32: 32x32 8.3; 300 x 16:
+// 64x16 30.2, 128x16 36.5; 50 x 20: 32x32 8.9, 64x16 9.6.  Below 9 columns half of a
+// 16-column tile would idle: 16x8, 64x8 and 128x8 are 36.2, 40.0 and 57 at 400 x 8, 250, 267
+// and 248 at 1,000 x 8 (1.3 GB of symbols, 5.2 TB/s); 400 x 10: 64x16 47.5, 64x8 61.
 std::vector<int> circ_timed(int R) {
-  if (R >= 48) return {23, 28, 26};
-  if (R >= 24) return {23, 28, 24};
-  if (R >= 12) return {29, 30};
-  return {7, 21};
+  if (R >= 48) return {31, 32, 33};
+  if (R >= 24) return {34, 35, 31};
+  if (R > 16) return {34, 36};
+  if (R >= 9) return {36, 37};
+  return {7, 21, 38};
 }
 void circ_tile(int var, int* bm, int* bn) {
   *bm = kCircVar[var].bm;

@@ -1536,10 +1536,18 @@ static size_t mfma_scratch_bytes(mudiff_ctx* h, int R) {
     rows = std::max(rows, g * c.RP);
   }
   int64_t citems = 0;
-  const int64_t bn = R < 24 ? 8 : 32;  // narrowest product tile for R (64 rows: the lowest)
-  if (h->circ)
-    for (int b = 0; b < h->B; ++b)
-      citems += (int64_t)h->cL[b] * ((h->idisk[b + 1] - h->idisk[b] + 63) / 64) * ((R + bn - 1) / bn);
+  if (h->circ) {
+    std::vector<int> vars = circ_variants(R);
+    vars.push_back(circ_variant(R));
+    for (int v : vars) {
+      int bm = 0, bn = 0;
+      circ_tile(v, &bm, &bn);
+      int64_t n = 0;
+      for (int b = 0; b < h->B; ++b)
+        n += (int64_t)h->cL[b] * ((h->idisk[b + 1] - h->idisk[b] + bm - 1) / bm) * ((R + bn - 1) / bn);
+      citems = std::max(citems, n);
+    }
+  }
   const size_t zw = h->circ ? (size_t)R * h->cZ_all * 16 : 0;
   const size_t sched = (size_t)items * MF_REC * 4 + (size_t)groups * 12 + (size_t)rows * 4 +
                        (size_t)h->M_all * 8 + (size_t)h->B * 4 + (size_t)n_near * 4 + (size_t)citems * 16 +
