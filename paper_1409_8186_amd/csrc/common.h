@@ -208,6 +208,7 @@ struct MfmaSched {
   bool close_rows = false;
   std::vector<int32_t> crow, crec;
   int n_long = 0;
+  bool close_beside = false;     // the close pairs run beside the products (mfma_launch)
   int n_citems = 0, cvar = 0;
   std::vector<char> blob;        // the arrays, packed
   const char* dev = nullptr;     // the blob's device copy
@@ -245,12 +246,13 @@ struct mudiff_ctx {
   char* res_base = nullptr;
   size_t res_bytes = 0, res_used = 0;
   hipEvent_t sched_ev = nullptr;          // recorded after the last schedule upload
-  // in the straggler phase the circulant form's close pairs run beside its
-  // transforms and products: a second stream (default priority) forked after
-  // the input scaling and joined before the output pass
+  // in the straggler phase and at medium sizes the circulant form's close pairs run
+  // beside its transforms and products: a second stream (default priority) forked
+  // after the input scaling and joined before the output pass
   hipStream_t aux = nullptr;
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   bool sched_pending = false;             // its copies may still read the host vectors
+  bool own_capture = false;               // a solve captures its own cycle
   bool mfma_tail = false;                 // straggler schedule (few columns still iterating)
   std::vector<int32_t> mfma_tail_cols;    // columns of the straggler schedule
   // circulant-embedded form (MUDIFF_TABLES_CIRCULANT): host copies of the

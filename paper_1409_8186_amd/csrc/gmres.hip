@@ -2738,8 +2738,10 @@ extern "C" int mudiff_gmres(mudiff_t h, int R, const double* beta, const void* r
         }
         GmresRun Gc = G;
         Gc.st = cap;
+        h->own_capture = true;
         int e = sb > 0 ? enqueue_bcycle(Gc, 0, false)
                        : (ss > 0 ? enqueue_sscycle(Gc, false) : enqueue_cycle(Gc, 0, false));
+        h->own_capture = false;
         hipError_t ce = hipStreamEndCapture(cap, &graph);
         (void)hipStreamDestroy(cap);
         if (e != MUDIFF_OK || ce != hipSuccess) {

@@ -1162,6 +1162,23 @@ static void mfma_build(const mudiff_ctx* h, int R, const MfmaChoice& c, MfmaSche
     for (int f = 0; f < MF_REC; ++f) S.items[k * MF_REC + f] = its[k].r[f];
   S.n_items = (int)its.size();
   S.n_citems = (int)(S.citems.size() / 4);
+  // Close pairs beside the transforms and products (a fork and a join between two
+  // streams): worth it while the rest lasts long enough to cover the host's 50 us for
+  // six launches and four event calls, and before it fills the chip so well that the
+  // close pairs take as much from the products as they gain.  In between, by the
+  // product's operations and symbol bytes at the rates they reach and 2.2 ns per disk
+  // and column for the transforms (us in turn, beside): 200 x 16 (24 us) 53.2, 57.4; 150 x
+  // 32 (23) 52.0, 54.6; 200 x 32 (36) 61.5, 55.7; 100 x 128 (42) 70.8, 64.8; 400 x 32
+  // (115) 121, 107; 1,000 x 8 (440) 282, 271; 500 x 128 (472) 473, 450; 700 x 64 (494) 413,
+  // 414; 400 x 256 (602) 607, 617; 1,000 x 64 (947) 772, 792.
+  double us = 2.2e-3 * R * h->M_all;
+  if (c.circ)
+    for (int b = 0; b < h->B; ++b)
+      if (S.con[(size_t)b]) {
+        const double M = (double)(h->idisk[b + 1] - h->idisk[b]), t = h->cL[(size_t)b] * M * M;
+        us += t * (6.0 * R / 60e6 + 16.0 / 4.5e6);
+      }
+  S.close_beside = S.close_rows && !S.crow.empty() && us >= 30.0 && us <= 500.0;
 }
 
 // Device view of a schedule's arrays.
@@ -1417,10 +1434,9 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, char* base, const cplx
   // direct-form work: in the straggler phase of a solve with the circulant form the
   // work queue and the close-pair rows run on the second stream, beside the
   // transforms and products, which share none of their outputs (there every launch
-  // is small and latency-bound; on a full batch the close-pair waves would crowd
-  // the products and transforms out of the compute units).  A short queue, that of
-  // a few instances outside the form, always runs there: it leaves most of the chip
-  // idle for as long as its items take.
+  // is small and latency-bound), the close pairs also at medium sizes (close_beside).
+  // A short queue, that of a few instances outside the form, always runs there: it
+  // leaves most of the chip idle for as long as its items take.
   mf_fn fn = nullptr;  // checked before the fork, so that every error leaves the streams joined
   if (S.n_items > 0) {
     const int TL = 4 * kt + 16 * mt - 1;
@@ -1432,8 +1448,21 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, char* base, const cplx
   }
   if (S.close_rows && (mt < 1 || mt > 4)) return fail(MUDIFF_ERR_INVALID, "close pairs: orders out of range");
   hipStream_t cs = s;
+  // the block -> row mapping of the close-pair kernel
+  const int n_close = (int)(S.crow.size() / 4);
+  const int64_t per = (int64_t)S.ntile * (mt > 2 ? 2 : 1);  // waves per row
+  const int64_t wpr = std::min<int64_t>(per, 4), rpb = 4 / wpr, n_short = n_close - S.n_long;
+  const int64_t close_blocks = ((S.n_long + 7) & ~7) * per +
+                               (((n_short + rpb - 1) / rpb + 7) & ~(int64_t)7) * ((per + wpr - 1) / wpr);
+  if (n_close > 0 && close_blocks >= ((int64_t)1 << 31)) return fail(MUDIFF_ERR_INVALID, "close pairs: too many tiles");
+  // (a caller's capture keeps to the caller's stream; a profiled apply keeps its phases apart)
+  bool beside = h->mfma_tail;
+  if (!beside && S.close_beside && h->prof_cur < 0) {
+    hipStreamCaptureStatus cst = hipStreamCaptureStatusNone;
+    beside = h->own_capture || (hipStreamIsCapturing(s, &cst) == hipSuccess && cst == hipStreamCaptureStatusNone);
+  }
   const bool fork = S.c.circ && (h->mfma_tail ? S.n_items > 0 || S.close_rows
-                                               : S.close_rows && S.n_items > 0 && S.n_items <= 4 * h->n_cu);
+                                               : beside || (S.close_rows && S.n_items > 0 && S.n_items <= 4 * h->n_cu));
   if (fork) {
     if ((rc = aux_stream(h)) != MUDIFF_OK) return rc;
     HIP_TRY(hipEventRecord(h->fork_ev, s));
@@ -1455,27 +1484,20 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, char* base, const cplx
     return MUDIFF_OK;
   };
   auto launch_close = [&](hipStream_t cs) -> int {
-    const int n_rows = (int)(S.crow.size() / 4);
-    if (n_rows == 0) return MUDIFF_OK;
+    if (n_close == 0) return MUDIFF_OK;
     typedef void (*close_fn)(DevView, int, const cplx*, cplx*, int64_t, int, const int32_t*, const int32_t*,
                              const int64_t*, const int4*, const int4*, int, int, int, const int32_t*);
     static const close_fn kClose[5] = {nullptr, k_apply_close<1, 1>, k_apply_close<2, 2>,
                                        k_apply_close<3, 2>, k_apply_close<4, 2>};
-    // the block -> row mapping of the kernel
-    const int64_t per = (int64_t)S.ntile * (mt > 2 ? 2 : 1);  // waves per row
-    const int64_t wpr = std::min<int64_t>(per, 4), rpb = 4 / wpr, n_short = n_rows - S.n_long;
-    const int64_t nb = ((S.n_long + 7) & ~7) * per +
-                       (((n_short + rpb - 1) / rpb + 7) & ~(int64_t)7) * ((per + wpr - 1) / wpr);
-    if (nb >= ((int64_t)1 << 31)) return fail(MUDIFF_ERR_INVALID, "close pairs: too many tiles");
-    hipLaunchKernelGGL(kClose[mt], dim3((unsigned)nb), dim3(256), 0, cs, h->dv, S.R, x, part, S.blk, S.npad,
-                       d.dgrp, d.drow, d.gbase, (const int4*)d.crow, (const int4*)d.crec, n_rows, S.n_long,
+    hipLaunchKernelGGL(kClose[mt], dim3((unsigned)close_blocks), dim3(256), 0, cs, h->dv, S.R, x, part, S.blk, S.npad,
+                       d.dgrp, d.drow, d.gbase, (const int4*)d.crow, (const int4*)d.crec, n_close, S.n_long,
                        S.ntile, active);
     HIP_TRY(hipGetLastError());
     return MUDIFF_OK;
   };
   if (fork) {
     if ((rc = launch_queue(cs)) != MUDIFF_OK) return rc;
-    if (h->mfma_tail && (rc = launch_close(cs)) != MUDIFF_OK) return rc;
+    if (beside && (rc = launch_close(cs)) != MUDIFF_OK) return rc;
     HIP_TRY(hipEventRecord(h->join_ev, cs));
   }
   if (S.c.circ) {  // well-separated pairs of the marked instances
@@ -1487,7 +1509,7 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, char* base, const cplx
     prof_mark(h, s, 2);
     prof_mark(h, s, 3);
   }
-  if (!(fork && h->mfma_tail) && (rc = launch_close(s)) != MUDIFF_OK) return rc;
+  if (!(fork && beside) && (rc = launch_close(s)) != MUDIFF_OK) return rc;
   if (fork) HIP_TRY(hipStreamWaitEvent(s, h->join_ev, 0));
   else if ((rc = launch_queue(s)) != MUDIFF_OK) return rc;
   prof_mark(h, s, 4);
