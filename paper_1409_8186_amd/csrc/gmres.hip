@@ -635,6 +635,274 @@ __global__ __launch_bounds__(GS_THREADS) void k_dg_update(GState s, int j) {
   }
 }
 
+// A whole cycle of Arnoldi steps of a small column in one workgroup: N_b rows and the
+// instance's symbols in LDS, one launch instead of three per step.  A step of a few
+// disks is a few thousand multiply-adds; as apply, dots and update kernels it took 14 us
+// of kernels and as much again between launches, nearly all of it latency.  Here the
+// steps are separated by four barriers:
+//   A  w = T z: a wave takes 32 outputs of a row disk, 8 lanes over the modes n of the
+//      column disks times 8 lanes of 4 outputs m, m + 8, .. each, so that the symbol read
+//      for one output serves the next one 8 modes later (1 + 1 reads per 4 multiply-adds)
+//   B  the epilogue of the apply (row n belongs to thread n)
+//   C  V_i^H u, V_i^H w, i <= j, one wave per four vectors (V_j = u)
+//   D  q_j, the next candidate and its scaled z; column j-1 of the Hessenberg matrix
+//   E  the Givens step (last wave) and the tentative column j (the others), beside A
+// with the algebra of k_dg_dots and k_dg_update.  State is left in GState as those
+// kernels leave it, so a cycle ends the same way.  VL: the basis in LDS as well.  SMALL_LDS: what a cycle may take of a compute
+// unit's LDS.
+#define SMALL_THREADS 512
+#define SMALL_WAVES (SMALL_THREADS / 64)
+#define SMALL_DISKS 16
+#define SMALL_LDS (144 * 1024)
+
+#define SMALL_TASKS 32  // (SMALL_THREADS + 31 SMALL_DISKS) / 32 at most
+
+struct SmallGeom {
+  int T, N;  // symbols and rows of the largest instance
+};
+
+__host__ __device__ inline size_t small_lds(int T, int N, int m, bool VL) {  // in complex values
+  return 32 + (size_t)T + (VL ? (size_t)(m + 1) * N : 0) + 3 * (size_t)N + 2 * (m + 1) + (size_t)m * (m + 1) +
+         2 * (m + 1) + m + (m + 1) / 2;
+}
+
+template <bool VL>
+__global__ __launch_bounds__(SMALL_THREADS) void k_small_cycle(GState s, DevView v, SmallGeom sg) {
+  extern __shared__ cplx lds[];
+  __shared__ int s_tb[SMALL_DISKS * SMALL_DISKS], s_off[SMALL_DISKS], s_np[SMALL_DISKS];
+  __shared__ int s_task[SMALL_TASKS];  // row disk, first output
+  __shared__ int s_stop, s_ntask;
+  const int c = blockIdx.x;
+  if (!s.inner[c]) return;
+  const int m = s.m, m1 = m + 1;
+  const int b = c / s.R, r = c - b * s.R;
+  const int64_t d0 = v.idisk[b], i0 = v.imode[b], o0 = col_base(v.imode, b, s.R, r);
+  const int M = (int)(v.idisk[b + 1] - d0), N = (int)(v.imode[b + 1] - i0);
+  const int T = M * (M - 1) / 2 + (M - 1) * (N - M);  // sum over pairs of 2 (N_p + N_q) + 1
+  cplx* tl = lds + 32;  // the last task of a row reads up to 31 entries before its symbols, for outputs it drops
+  cplx* Vl = tl + sg.T;                              // [m + 1][N]
+  cplx* ul = Vl + (VL ? (size_t)m1 * sg.N : 0);
+  cplx* zl = ul + sg.N;
+  cplx* wl = zl + sg.N;
+  cplx* cl = wl + sg.N;                              // s_i, then z_i from m1
+  cplx* Hr = cl + 2 * m1;                            // unrotated columns [k][m1]
+  cplx* ht = Hr + (size_t)m * m1;                    // tentative column
+  cplx* hc = ht + m1;                                // column j - 1
+  cplx* sn = hc + m1;                                // rotations
+  double* cs = reinterpret_cast<double*>(sn + m);
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int64_t t0 = M > 1 ? v.toff[v.ipair[b]] : 0;
+  for (int e = tid; e < M * M; e += SMALL_THREADS) {
+    const int p = e / M, q = e - (e / M) * M;
+    if (p != q)  // index of t^{pq}_0 in tl
+      s_tb[e] = (int)(v.toff[pair_index(v.idisk, v.ipair, b, (int)(d0 + p), (int)(d0 + q))] - t0) +
+                v.N[d0 + p] + v.N[d0 + q];
+  }
+  if (tid < M) {
+    s_off[tid] = (int)v.moff[d0 + tid];
+    s_np[tid] = v.N[d0 + tid];
+  }
+  if (tid == 0) {
+    int k = 0;
+    for (int p = 0; p < M; ++p)
+      for (int m0 = 0; m0 <= 2 * v.N[d0 + p]; m0 += 32) s_task[k++] = p << 16 | m0;
+    s_ntask = k;
+    s_stop = 0;
+  }
+  for (int e = tid; e < T; e += SMALL_THREADS) tl[e] = v.t[t0 + e];
+  // thread n: row n, with its column factor and the epilogue alpha u + beta w
+  const bool own = tid < N;
+  cplx sc = cmk(0.0, 0.0), al = cmk(1.0, 0.0), be = sc;
+  cplx* Vg = s.V + o0;
+  if (own) {
+    const int64_t i = i0 + tid;
+    sc = v.op_col ? v.op_col[i] : cmk(v.sJ[i], 0.0);
+    if (v.op_rowA) {
+      be = s.op == MUDIFF_OP_A ? v.op_rowA[i] : v.op_row[i];
+      if (s.op != MUDIFF_OP_A) al = v.op_diag[i];
+    } else if (s.op == MUDIFF_OP_A) {
+      be = v.invSH[i];
+    } else {
+      be = cmk(0.0, 0.5 * 3.14159265358979323846 * v.sJ[i]);
+      al = v.Ldiag[i];
+    }
+    const cplx u = Vg[tid];
+    ul[tid] = u;
+    zl[tid] = cmul(u, sc);
+    if (VL) Vl[tid] = u;
+  }
+  ArnoldiPre pre{};
+  const bool giv = tid == SMALL_THREADS - 64;  // the Givens steps' thread
+  if (giv) pre = arnoldi_preload(s, c, 0);
+  __syncthreads();
+  cplx* const Vb = VL ? Vl : Vg;
+  const int64_t ldv = VL ? N : s.NT;
+  for (int j = 0; j < m; ++j) {
+    // A
+    for (int e = wv; e < s_ntask; e += SMALL_WAVES) {
+      const int part = lane & 7, p = s_task[e] >> 16, mo = (s_task[e] & 0xffff) + (lane >> 3);
+      const int ld = min(lane, M - 1);  // lane q holds what the loop needs of column disk q
+      const int qN = s_np[ld], qo = s_off[ld], qt = s_tb[p * M + ld];
+      const int Np = __builtin_amdgcn_readlane(qN, p), op = __builtin_amdgcn_readlane(qo, p);
+      cplx w[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) w[k] = cmk(0.0, 0.0);
+      for (int q = 0; q < M; ++q) {
+        const int Nq = __builtin_amdgcn_readlane(qN, q);
+        if (q == p) continue;
+        const int nq = 2 * Nq + 1, full = nq >> 3;
+        const cplx* tq = tl + (__builtin_amdgcn_readlane(qt, q) + Np - Nq - mo + part);
+        const cplx* zq = zl + (__builtin_amdgcn_readlane(qo, q) + part);
+        cplx t1 = tq[-8], t2 = tq[-16], t3 = tq[-24];
+        cplx a[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a[k] = cmk(0.0, 0.0);
+        auto step = [&](int n) {
+          const cplx t = tq[n], z = zq[n];
+          cmac(a[0], t, z);
+          cmac(a[1], t1, z);
+          cmac(a[2], t2, z);
+          cmac(a[3], t3, z);
+          t3 = t2;
+          t2 = t1;
+          t1 = t;
+        };
+        int i = 0;
+        for (; i + 4 <= full; i += 4) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) step(8 * (i + u));
+        }
+        for (; i < full; ++i) step(8 * i);
+        if (part < (nq & 7)) step(8 * full);
+        // s = n + N_p - N_q - m has the parity of part + N_p - N_q - mo for all four
+        const bool neg = p > q && ((part + Np - Nq - mo) & 1);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w[k] = neg ? csub(w[k], a[k]) : cadd(w[k], a[k]);
+      }
+      double val[8];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        val[2 * k] = w[k].x;
+        val[2 * k + 1] = w[k].y;
+      }
+      rs_dpp_step<4, 8>(val, lane);
+      rs_dpp_step<2, 4>(val, lane);
+      rs_dpp_step<1, 2>(val, lane);
+      const int mm = mo + 8 * (part >> 1);  // lane `part` holds value `part`
+      if (mm <= 2 * Np) reinterpret_cast<double*>(wl + op + mm)[part & 1] = val[0];
+    }
+    __syncthreads();
+    if (s_stop) break;
+    // B
+    if (own) wl[tid] = cadd(cmul(al, ul[tid]), cmul(be, wl[tid]));
+    __syncthreads();
+    // C: vectors i = wv + SMALL_WAVES k, four at a time
+    for (int ib = wv; ib <= j; ib += 4 * SMALL_WAVES) {
+      cplx au[4], aw[4];
+      const cplx* vi[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        au[k] = cmk(0.0, 0.0);
+        aw[k] = au[k];
+        const int i = min(ib + k * SMALL_WAVES, j);  // past j: V_j again, unused
+        vi[k] = i == j ? ul : Vb + (int64_t)i * ldv;
+      }
+      for (int n = lane; n < N; n += 64) {
+        const cplx un = ul[n], wn = wl[n];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const cplx vn = vi[k][n];
+          cmacc(au[k], vn, un);
+          cmacc(aw[k], vn, wn);
+        }
+      }
+      double val[16];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        val[4 * k] = au[k].x;
+        val[4 * k + 1] = au[k].y;
+        val[4 * k + 2] = aw[k].x;
+        val[4 * k + 3] = aw[k].y;
+      }
+      lane_reduce_scatter<16>(val, lane);
+      if ((lane & 3) == 0) {
+        const int k = lane >> 4, comp = (lane >> 2) & 3, i = ib + k * SMALL_WAVES;
+        if (i <= j) reinterpret_cast<double*>(cl + (comp < 2 ? i : m1 + i))[comp & 1] = val[0];
+      }
+    }
+    __syncthreads();
+    // D
+    double ssq = 0.0;
+    cplx sz = cmk(0.0, 0.0);
+    for (int i = lane; i < j; i += 64) {
+      ssq += cabs2(cl[i]);
+      cmacc(sz, cl[i], cl[m1 + i]);
+    }
+    ssq = wave_sum(ssq);
+    sz = cmk(wave_sum(sz.x), wave_sum(sz.y));
+    const double rho2 = cl[j].x - ssq;
+    const double rho = sqrt(rho2 > 0.0 ? rho2 : 0.0);
+    const double inv = 1.0 / rho;  // rho == 0: breakdown, the column stops below
+    const cplx gj = cscale(csub(cl[m1 + j], sz), inv);
+    if (own) {
+      cplx a = ul[tid], w = wl[tid];
+      const cplx* vn = Vb + tid;
+#pragma unroll 4
+      for (int i = 0; i < j; ++i) {
+        const cplx t = vn[i * ldv];
+        a = csub(a, cmul(cl[i], t));
+        w = csub(w, cmul(cl[m1 + i], t));
+      }
+      const cplx q = cscale(a, inv);
+      w = cscale(csub(w, cmul(gj, q)), inv);
+      Vg[(int64_t)j * s.NT + tid] = q;
+      if (VL) {
+        Vl[j * N + tid] = q;
+        Vl[(j + 1) * N + tid] = w;
+      }
+      if (!VL || j == m - 1) Vg[(int64_t)(j + 1) * s.NT + tid] = w;
+      ul[tid] = w;
+      zl[tid] = cmul(w, sc);
+    }
+    if (j >= 1) {
+      cplx* hg = s.Hraw + (int64_t)c * m1 * m + (int64_t)(j - 1) * m1;
+      for (int i = tid; i <= j; i += SMALL_THREADS) {
+        const cplx h = i < j ? cadd(ht[i], cl[i]) : cmk(rho, 0.0);
+        hc[i] = h;
+        Hr[(j - 1) * m1 + i] = h;
+        hg[i] = h;
+      }
+    }
+    __syncthreads();
+    // E
+    if (wv == SMALL_WAVES - 1) {
+      if (j >= 1 && giv) {
+        ArnoldiPre nx{};
+        if (arnoldi_step(s, c, j - 1, hc, cs, sn, rho, pre, &nx, cs + (j - 1), sn + (j - 1))) s_stop = 1;
+        pre = nx;
+      }
+    } else {  // from the waves that A uses last
+      const int kl = lane & 3;
+      for (int ib = 0; ib <= j; ib += (SMALL_WAVES - 1) * 16) {
+        const int i = ib + (SMALL_WAVES - 2 - wv) * 16 + (lane >> 2);
+        cplx hs = cmk(0.0, 0.0);
+        if (i <= j)
+          for (int k = (i > 0 ? i - 1 : 0) + kl; k < j; k += 4) hs = cadd(hs, cmul(Hr[k * m1 + i], cl[k]));
+#pragma unroll
+        for (int o = 1; o < 4; o <<= 1) {
+          hs.x += __shfl_xor(hs.x, o, 64);
+          hs.y += __shfl_xor(hs.y, o, 64);
+        }
+        if (kl == 0 && i <= j) {
+          const cplx h = cscale(csub(i < j ? cl[m1 + i] : gj, hs), inv);
+          ht[i] = h;
+          if (j == m - 1) s.htent[(int64_t)c * m1 + i] = h;
+        }
+      }
+    }
+  }
+}
+
 // End of a cycle (after m steps): column m-1 is finalised from the last
 // candidate u = V[m]: s = V^H u, rho = sqrt(u^H u - ||s||^2).  One workgroup
 // per column.
@@ -2205,6 +2473,28 @@ static int compact_columns(GmresRun& G, const std::vector<int32_t>& run, int n_r
   return apply_set_tail(G.h, G.s.R, true, G.apply_part, G.st, run.data());
 }
 
+// Whether the cycles of this solve run on k_small_cycle: few columns (from 8 on the
+// apply is on the matrix cores), every instance within a workgroup's threads and LDS.  It
+// was the faster one wherever it fits (whole solves, us, three kernels per step against
+// this one): 4 disks of 31 modes 740, 292; 2 x 25 416, 220; 10 x 25 1,410, 811; 14 x 25
+// 2,495, 2,415; 10 disks of 33 modes (basis in global memory) 1,986, 1,634; 12 of them, 7
+// columns 1,940, 1,905; batches: 256 instances of 4 x 25, 7 columns each, 2,531, 1,028; 64 of
+// 12 mixed disks, 7 columns, 11,677, 5,658.
+static bool small_cycle(const mudiff_ctx* h, const GState& s, SmallGeom* g, bool* vl) {
+  if (s.R >= 8) return false;
+  int T = 0, N = 0;
+  for (int b = 0; b < h->B; ++b) {
+    const int64_t M = h->idisk[b + 1] - h->idisk[b], n = h->imode[b + 1] - h->imode[b];
+    if (M > SMALL_DISKS || n > SMALL_THREADS) return false;
+    T = std::max(T, (int)(M * (M - 1) / 2 + (M - 1) * (n - M)));
+    N = std::max(N, (int)n);
+  }
+  g->T = T;
+  g->N = N;
+  *vl = small_lds(T, N, s.m, true) * 16 <= SMALL_LDS;
+  return *vl || small_lds(T, N, s.m, false) * 16 <= SMALL_LDS;
+}
+
 // One restart cycle (Arnoldi steps + solution update + true residual).
 static int enqueue_cycle(GmresRun& G, int check_every, bool host_checks) {
   GState& s = G.s;
@@ -2212,7 +2502,15 @@ static int enqueue_cycle(GmresRun& G, int check_every, bool host_checks) {
   const unsigned eb = (unsigned)((s.NT + 255) / 256);
   hipLaunchKernelGGL(k_scale_v0, dim3(eb), dim3(256), 0, G.st, s, s.NT, G.d_rowcol);
   HIP_TRY(hipGetLastError());
-  for (int j = 0; j < s.m; ++j) {
+  SmallGeom sg;
+  bool vl = false;
+  const bool small = small_cycle(G.h, s, &sg, &vl);
+  if (small) {
+    hipLaunchKernelGGL(vl ? k_small_cycle<true> : k_small_cycle<false>, dim3(s.C), dim3(SMALL_THREADS),
+                       small_lds(sg.T, sg.N, s.m, vl) * 16, G.st, s, G.h->dv, sg);
+    HIP_TRY(hipGetLastError());
+  }
+  for (int j = 0; !small && j < s.m; ++j) {
     bool pending = false;
     int rc = apply_operator_split(G.h, s.R, s.V + (int64_t)j * s.NT,
                                   s.V + (int64_t)(j + 1) * s.NT, s.op, G.apply_part,
