@@ -19,12 +19,14 @@ import torch
 from . import _lib as L
 
 
-def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+def _p(t):  # (an int: the signatures convert it, at a third of a c_void_p's cost)
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream's handle without the Stream object: 0.3 us of a launch instead
+    # of 2.8, a third of what the smallest apply takes
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _host(a, dtype):

@@ -154,6 +154,8 @@ struct MatvecPlan {
   size_t lds_bytes = 0;
   int64_t part_total = 0;       // complex partials per right-hand side
   int64_t row_part = 0;         // the same for the LDS-staged kernel's chunks
+  int few = 0;                  // > 0: k_apply_few, ints per task in d_items
+  int few_cols = 0, few_z = 0;  // its LDS: column disks per wave, entries of an input panel
   int32_t* d_items = nullptr;   // [n_items][4] : p, chunk, q_begin, q_end (generic);
                                 // [n_items][LANE_ITEM_INTS] (LANE_UNIFORM),
                                 // [n_items][PAIRS_ITEM_INTS] (LANE_PAIRS)
@@ -313,6 +315,19 @@ __device__ __forceinline__ cplx finalize(const DevView& v, int op, int64_t i, cp
 // pair of column c in ab.
 __device__ __forceinline__ cplx affine(const cplx* __restrict__ ab, int c, cplx y, cplx x) {
   return cadd(cmul(ab[2 * c], y), cmul(ab[2 * c + 1], x));
+}
+
+// The same as alpha x + beta w, for kernels that load the factors early; false when
+// alpha is 1 (MUDIFF_OP_A).  Not for OP_RAW_W.
+__device__ __forceinline__ bool row_factors(const DevView& v, int op, int64_t i, cplx* al, cplx* be) {
+  *al = cmk(1.0, 0.0);
+  if (op == MUDIFF_OP_A) {
+    *be = v.op_rowA ? v.op_rowA[i] : v.invSH[i];
+    return false;
+  }
+  *al = v.op_rowA ? v.op_diag[i] : v.Ldiag[i];
+  *be = v.op_rowA ? v.op_row[i] : cmk(0.0, 0.5 * 3.14159265358979323846 * v.sJ[i]);
+  return true;
 }
 
 // Input x_n scaled by the column factor of unknown i: sqrt(a_q) J_n(k a_q)

@@ -712,20 +712,13 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_cycle(GState s, DevView
   for (int e = tid; e < T; e += SMALL_THREADS) tl[e] = v.t[t0 + e];
   // thread n: row n, with its column factor and the epilogue alpha u + beta w
   const bool own = tid < N;
-  cplx sc = cmk(0.0, 0.0), al = cmk(1.0, 0.0), be = sc;
+  bool one = true;
+  cplx sc = cmk(0.0, 0.0), al = sc, be = sc;
   cplx* Vg = s.V + o0;
   if (own) {
     const int64_t i = i0 + tid;
     sc = v.op_col ? v.op_col[i] : cmk(v.sJ[i], 0.0);
-    if (v.op_rowA) {
-      be = s.op == MUDIFF_OP_A ? v.op_rowA[i] : v.op_row[i];
-      if (s.op != MUDIFF_OP_A) al = v.op_diag[i];
-    } else if (s.op == MUDIFF_OP_A) {
-      be = v.invSH[i];
-    } else {
-      be = cmk(0.0, 0.5 * 3.14159265358979323846 * v.sJ[i]);
-      al = v.Ldiag[i];
-    }
+    one = !row_factors(v, s.op, i, &al, &be);
     const cplx u = Vg[tid];
     ul[tid] = u;
     zl[tid] = cmul(u, sc);
@@ -794,7 +787,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_cycle(GState s, DevView
     __syncthreads();
     if (s_stop) break;
     // B
-    if (own) wl[tid] = cadd(cmul(al, ul[tid]), cmul(be, wl[tid]));
+    if (own) wl[tid] = cadd(one ? ul[tid] : cmul(al, ul[tid]), cmul(be, wl[tid]));
     __syncthreads();
     // C: vectors i = wv + SMALL_WAVES k, four at a time
     for (int ib = wv; ib <= j; ib += 4 * SMALL_WAVES) {

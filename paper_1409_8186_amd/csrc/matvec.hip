@@ -190,6 +190,115 @@ __global__ __launch_bounds__(APPLY_THREADS) void k_apply(
   }
 }
 
+// ------------------------------------------------------------------ few disks
+// Instances of up to FEW_DISKS disks, few right-hand sides: bound by latency, the chain
+// of loads from the schedule to the symbols and the launch itself.  A workgroup takes 32
+// outputs of a row disk and every column disk of its instance, so there are no partial
+// sums.  What it needs to know of the column disks stands in its task, so that two rounds
+// of loads come before the arithmetic (the LDS-staged kernel has six, through the tables).
+// Wave w stages column disks w, w + 4, .. (scaled inputs z and the symbols of the 32
+// outputs) and sums over them, 8 lanes over the modes n times 8 lanes of the outputs m,
+// m + 8, m + 16, m + 24: a symbol read for one output serves the next one 8 modes later.
+// 4 disks of 31 modes: 6.35 us as LDS-staged rows, 3.5 so.
+#define FEW_THREADS 256
+#define FEW_WAVES (FEW_THREADS / 64)
+#define FEW_DISKS 16
+#define FEW_HDR 16  // instance, first output, N_p, column disks, unknown of mode -N_p, imode, N_b, M
+#define FEW_COL 8   // offset in the instance vector, N_q, symbol t^{pq}_0, 1: times (-1)^s
+#define FEW_PAD 31  // window entries before output m0's, for the outputs after it
+
+// The tables it reads, for the operator and op of the launch: y = alpha x + beta w
+// (al NULL: alpha is 1; be NULL: beta = (i pi / 2) sJ; raw: y = w).
+struct FewView {
+  const cplx *t, *col, *al, *be;  // col NULL: the column factors are sJ
+  const double* sJ;
+  bool raw;
+};
+
+__global__ __launch_bounds__(FEW_THREADS) void k_apply_few(
+    FewView v, int R, const cplx* __restrict__ x, cplx* __restrict__ y,
+    const int32_t* __restrict__ tasks, int stride, const int32_t* __restrict__ active,
+    const cplx* __restrict__ shift, int cols, int zcap) {
+  extern __shared__ cplx lds[];  // [FEW_WAVES][cols][zcap z, zcap + FEW_PAD symbols]
+  __shared__ double red[FEW_WAVES][64];
+  const int r = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int32_t* it = tasks + (int64_t)stride * blockIdx.x;
+  const int b = it[0], m0 = it[1], Np = it[2], nc = it[3];
+  const int64_t ip = *reinterpret_cast<const int64_t*>(it + 4), im = *reinterpret_cast<const int64_t*>(it + 6);
+  const int64_t cb = (int64_t)R * im + (int64_t)r * *reinterpret_cast<const int64_t*>(it + 8);
+  if (active && active[b * R + r] == 0) return;
+  cplx xv = cmk(0.0, 0.0), al = xv, be = xv;
+  const bool out = tid < 32 && m0 + tid <= 2 * Np;
+  if (out) {
+    const int64_t i = ip + m0 + tid;
+    xv = x[cb + (i - im)];
+    be = v.be ? v.be[i] : cmk(0.0, 0.5 * 3.14159265358979323846 * v.sJ[i]);
+    if (v.al) al = v.al[i];
+  }
+  cplx* base = lds + (size_t)wv * cols * (2 * zcap + FEW_PAD);
+  int k = 0;
+  for (int c = wv; c < nc; c += FEW_WAVES, ++k) {
+    const int32_t* rec = it + FEW_HDR + FEW_COL * c;
+    const int qo = rec[0], Nq = rec[1], neg = rec[4];
+    const cplx* __restrict__ t = v.t + *reinterpret_cast<const int64_t*>(rec + 2);
+    cplx* zl = base + (size_t)k * (2 * zcap + FEW_PAD);
+    cplx* tl = zl + zcap;
+    const int nq = 2 * Nq + 1, s0 = Np - Nq - m0 - FEW_PAD;  // window entry u holds t_{u + s0}
+    for (int n = lane; n < nq; n += 64) zl[n] = v.col ? cmul(x[cb + qo + n], v.col[im + qo + n]) : cscale(x[cb + qo + n], v.sJ[im + qo + n]);
+    for (int u = lane; u < nq + FEW_PAD; u += 64) {
+      const int sy = u + s0;
+      cplx e = sy >= -(Np + Nq) ? t[sy] : cmk(0.0, 0.0);  // below: outputs past 2 N_p
+      if (neg && (sy & 1)) e = cmk(-e.x, -e.y);
+      tl[u] = e;
+    }
+  }
+  __syncthreads();
+  const int part = lane & 7, mi = lane >> 3;
+  cplx a[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a[i] = cmk(0.0, 0.0);
+  k = 0;
+  for (int c = wv; c < nc; c += FEW_WAVES, ++k) {
+    const int nq = 2 * it[FEW_HDR + FEW_COL * c + 1] + 1, full = nq >> 3;
+    const cplx* zq = base + (size_t)k * (2 * zcap + FEW_PAD) + part;
+    const cplx* tq = zq + zcap + FEW_PAD - mi;
+    cplx t1 = tq[-8], t2 = tq[-16], t3 = tq[-24];
+    auto step = [&](int n) {
+      const cplx t = tq[n], z = zq[n];
+      cmac(a[0], t, z);
+      cmac(a[1], t1, z);
+      cmac(a[2], t2, z);
+      cmac(a[3], t3, z);
+      t3 = t2;
+      t2 = t1;
+      t1 = t;
+    };
+#pragma unroll 4
+    for (int i = 0; i < full; ++i) step(8 * i);
+    if (part < (nq & 7)) step(8 * full);
+  }
+  double val[8];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    val[2 * i] = a[i].x;
+    val[2 * i + 1] = a[i].y;
+  }
+  rs_dpp_step<4, 8>(val, lane);
+  rs_dpp_step<2, 4>(val, lane);
+  rs_dpp_step<1, 2>(val, lane);
+  red[wv][lane] = val[0];  // lane (mi, part): Re, Im of output mi + 8 (part / 2)
+  __syncthreads();
+  if (!out) return;
+  cplx w = cmk(0.0, 0.0);
+  const int l = 8 * (tid & 7) + 2 * (tid >> 3);
+#pragma unroll
+  for (int i = 0; i < FEW_WAVES; ++i) w = cadd(w, cmk(red[i][l], red[i][l + 1]));
+  cplx o = w;
+  if (!v.raw) o = cadd(v.al ? cmul(al, xv) : xv, cmul(be, w));
+  if (shift) o = affine(shift, b * R + r, o, xv);
+  y[cb + (ip - im) + m0 + tid] = o;
+}
+
 // ------------------------------------------------------------------ one lane per pair
 // Uniform N_p = N (<= 12), few right-hand sides.  A work item is one wave: row
 // disk p, one right-hand side and a chunk of up to 64 column disks q, one
@@ -1785,6 +1894,7 @@ struct PlanHost {
   int bt = 4, nspec = -1, zs = 0, ts = 0, ppcap = 1;
   size_t lds = 0;
   int64_t part = 0;
+  int few = 0, few_cols = 0, few_z = 0;
   int64_t row_part = 0;  // partial sums of the LDS-staged kernel (bounds mudiff_matvec_noalloc)
   std::vector<int32_t> items, nch, tasks;
   std::vector<int64_t> poff;
@@ -1984,6 +2094,72 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
   }
 }
 
+// Tasks of k_apply_few in place of the plan's items, for batches of small instances
+// whose panels fit its LDS.  The rest of the plan stays: the scratch it asks for is what
+// the entry points check.  us per apply, the kernels before and this one: mixed orders of
+// about 33 modes, 10 disks, one column 9.7, 8.7 (the host's part); 256 x 10 61, 29; 64 x 16, 4
+// columns 110, 65; 1,000 x 10, 7 columns 1,446, 643.  Uniform orders (25 modes), where one
+// lane per pair is the other way: 2 disks 11.9, 8.6; 1,000 x 4 44, 11.5; 256 x 8, 4 columns
+// 72, 34; 256 x 12 80, 71, but 256 x 14 93, 98, 256 x 16 105, 117; 64 x 16 31, 29.
+#define FEW_LDS (64 * 1024)
+
+static size_t few_lds(int cols, int zcap) { return (size_t)FEW_WAVES * cols * (2 * zcap + FEW_PAD) * 16; }
+
+static void make_few(int B, const int64_t* idisk, const int32_t* N, PlanHost& P) {
+  int64_t mmax = 0;
+  int nmax = 0;
+  for (int b = 0; b < B; ++b) mmax = std::max(mmax, idisk[b + 1] - idisk[b]);
+  for (int64_t p = 0; p < idisk[B]; ++p) nmax = std::max(nmax, (int)N[p]);
+  const int cols = (int)(mmax - 1 + FEW_WAVES - 1) / FEW_WAVES, zcap = 2 * nmax + 1;
+  if (mmax > FEW_DISKS || few_lds(cols, zcap) > FEW_LDS) return;
+  if (P.lane == LANE_UNIFORM && mmax > 12 && idisk[B] > 1024) return;
+  P.few = FEW_HDR + FEW_COL * (int)(mmax - 1);
+  P.few_cols = cols;
+  P.few_z = zcap;
+  P.items.clear();
+  int64_t i0 = 0, t0 = 0;  // first unknown and symbol of the instance
+  for (int b = 0; b < B; ++b) {
+    const int64_t d0 = idisk[b];
+    const int M = (int)(idisk[b + 1] - d0);
+    int64_t off[FEW_DISKS + 1] = {0}, sym[FEW_DISKS][FEW_DISKS], t = t0;
+    for (int p = 0; p < M; ++p) {
+      off[p + 1] = off[p] + 2 * N[d0 + p] + 1;
+      for (int q = p + 1; q < M; ++q) {
+        const int64_t S = N[d0 + p] + N[d0 + q];
+        sym[p][q] = sym[q][p] = t + S;
+        t += 2 * S + 1;
+      }
+    }
+    for (int p = 0; p < M; ++p)
+      for (int m0 = 0; m0 <= 2 * N[d0 + p]; m0 += 32) {
+        const size_t w = P.items.size();
+        P.items.resize(w + P.few, 0);
+        int32_t* it = P.items.data() + w;
+        auto put64 = [&](int k, int64_t x) {
+          it[k] = (int32_t)(x & 0xffffffff);
+          it[k + 1] = (int32_t)(x >> 32);
+        };
+        it[0] = b;
+        it[1] = m0;
+        it[2] = N[d0 + p];
+        it[3] = M - 1;
+        put64(4, i0 + off[p]);
+        put64(6, i0);
+        put64(8, off[M]);
+        for (int q = 0, k = FEW_HDR; q < M; ++q) {
+          if (q == p) continue;
+          it[k] = (int32_t)off[q];
+          it[k + 1] = N[d0 + q];
+          put64(k + 2, sym[p][q]);
+          it[k + 4] = p > q;
+          k += FEW_COL;
+        }
+      }
+    i0 += off[M];
+    t0 = t;
+  }
+}
+
 size_t plan_sched_bytes(const PlanHost& P, int M) {
   return align256(P.items.size() * 4) + align256((size_t)M * 4) + align256((size_t)M * 8) +
          align256(P.tasks.size() * 4) + 256;
@@ -1995,6 +2171,8 @@ size_t sched_bytes_for(int B, const int64_t* disk_off, const int32_t* n_modes) {
     PlanHost H;
     make_plan(B, disk_off, n_modes, pairs, H);
     bytes = std::max(bytes, plan_sched_bytes(H, (int)disk_off[B]));
+    make_few(B, disk_off, n_modes, H);
+    bytes = std::max(bytes, plan_sched_bytes(H, (int)disk_off[B]));
   }
   return bytes;
 }
@@ -2003,6 +2181,7 @@ int ensure_plan(mudiff_ctx* h, hipStream_t s) {
   if (h->plan.ready) return MUDIFF_OK;
   PlanHost H;
   make_plan(h->B, h->idisk.data(), h->N.data(), h->pairs_ok, H);
+  make_few(h->B, h->idisk.data(), h->N.data(), H);
   if (H.lds > (H.lane ? 80 : 64) * 1024) return fail(MUDIFF_ERR_INVALID, "operator rows too long for LDS");
   if (plan_sched_bytes(H, h->M_all) > h->sched_bytes)
     return fail(MUDIFF_ERR_INVALID, "schedule area too small");
@@ -2028,7 +2207,10 @@ int ensure_plan(mudiff_ctx* h, hipStream_t s) {
   P.wide = H.wide;
   P.row_part = H.lane == LANE_PAIRS ? H.row_part : H.part;
   P.lds_bytes = H.lds;
-  P.n_items = (int)(H.items.size() / H.item_ints);
+  P.few = H.few;
+  P.few_cols = H.few_cols;
+  P.few_z = H.few_z;
+  P.n_items = (int)(H.items.size() / (H.few ? H.few : H.item_ints));
   P.ready = true;
   return MUDIFF_OK;
 }
@@ -2083,7 +2265,7 @@ int apply_operator_split(mudiff_ctx* h, int R, const cplx* x, cplx* y, int op, c
   int st = ensure_plan(h, s);
   if (st != MUDIFF_OK) return st;
   const MatvecPlan& P = h->plan;
-  if (P.lane) {
+  if (P.lane && !P.few) {
     if ((st = launch_lanes(h, R, x, part, active, s)) != MUDIFF_OK) return st;
     *pending = true;  // the chunk sums still have to be added and finalised
     return MUDIFF_OK;
@@ -2105,6 +2287,19 @@ int apply_operator(mudiff_ctx* h, int R, const cplx* x, cplx* y, int op, cplx* p
   prof_mark(h, s, 1);
   prof_mark(h, s, 2);
   prof_mark(h, s, 3);
+  if (P.few) {
+    const DevView& v = h->dv;
+    FewView fv{v.t, v.op_col, nullptr, v.invSH, v.sJ, op == OP_RAW_W};
+    if (v.op_rowA) fv.be = op == MUDIFF_OP_A ? v.op_rowA : v.op_row;
+    else if (op != MUDIFF_OP_A) fv.be = nullptr;
+    if (op != MUDIFF_OP_A) fv.al = v.op_rowA ? v.op_diag : v.Ldiag;
+    hipLaunchKernelGGL(k_apply_few, dim3(P.n_items, R), dim3(FEW_THREADS), few_lds(P.few_cols, P.few_z), s, fv, R,
+                       x, y, P.d_items, P.few, active, shift, P.few_cols, P.few_z);
+    HIP_TRY(hipGetLastError());
+    prof_mark(h, s, 4);
+    prof_mark(h, s, 5);
+    return MUDIFF_OK;
+  }
   if (P.lane) {
     if ((st = launch_lanes(h, R, x, part, active, s)) != MUDIFF_OK) return st;
     prof_mark(h, s, 4);
