@@ -117,11 +117,14 @@ struct DevView {
 
 #define LANE_CHUNK 64
 #define LANE_REC 4   // complex values per pair record
-// One-lane work item, int32 words: p, chunk, q_begin, q_end, instance b, its
-// first disk, then int64 at word 6: first unknown of b, unknowns of b, record
-// offset of (p, chunk) in lt, partial-sum offset of (p, chunk); word 14: 0.
+// One-lane work item, int32 words: first row disk p, row disks, q_begin, q_end,
+// instance b, its first disk, then int64 at word 6: first unknown of b, unknowns of b,
+// record offset of (p, chunk) in lt, partial-sum offset of (p, chunk), and what the two
+// advance by per row disk.
 // All the kernel needs before its vector loads comes from this one record.
-#define LANE_ITEM_INTS 16
+#define LANE_ITEM_INTS 18
+#define LANE_ROWS 4   // row disks per workgroup of k_apply_lane
+#define LANE_MIN 12   // lanes of a wave that work at least
 #define LANE_NMAX 12
 // Largest order of the one-lane-per-pair kernel for any orders: its input panel
 // [2 N + 1][65] of 64 column disks fits 64 KB of LDS.

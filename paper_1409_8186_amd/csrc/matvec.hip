@@ -300,10 +300,12 @@ __global__ __launch_bounds__(FEW_THREADS) void k_apply_few(
 }
 
 // ------------------------------------------------------------------ one lane per pair
-// Uniform N_p = N (<= 12), few right-hand sides.  A work item is one wave: row
-// disk p, one right-hand side and a chunk of up to 64 column disks q, one
+// Uniform N_p = N (<= 12), few right-hand sides.  A wave takes a row disk p, one
+// right-hand side and a chunk of up to 64 column disks q, one
 // lane per ordered pair (p, q), with all n = 2N+1 outputs of the pair in
-// registers.  Each pair is read as one lane-interleaved record (H_0, H_1,
+// registers; a workgroup is four row disks on the same chunk, whose scaled inputs
+// it loads once, coalesced, and hands to the lanes through LDS (loaded lane by lane,
+// n entries apart, they took 25 loads of 64 cache lines each).  Each pair is read as one lane-interleaved record (H_0, H_1,
 // e^{i alpha_pq}, 2 / (k b_pq)): the orders H_nu(k b_pq), nu <= 2N, follow by
 // the upward recurrence H_{nu+1} = (2 nu / x) H_nu - H_{nu-1}, whose rounding
 // error stays at the level of eps |H_nu| (the growing Y part dominates |H_nu|
@@ -313,43 +315,74 @@ __global__ __launch_bounds__(FEW_THREADS) void k_apply_few(
 // inputs z in registers.  The 2n real outputs are summed over the lanes by a
 // reduce-scatter butterfly (lane l ends with the sum of value l >> sh) and
 // stored as the chunk's partial sum; k_apply_finish adds the chunks of each
-// row in order.  Single-wave items keep every SIMD busy to the end of the
-// launch (rows of unequal cost or rows fewer than the compute units would
-// leave whole workgroups idle), and the two launches need no counters or
-// memory fences.
+// row in order; the two launches need no counters or memory fences.
+// Bound by FP64 issue: 3,000 vector instructions per wave at N = 12, 2.7 waves per
+// SIMD at 400 disks, so 3 rounds of 5.6 us.  us per apply, single-wave workgroups and
+// these: 400 x 12 28.2, 25.9; 700 67.9, 61.4; 1,000 120, 114; 400, 7 columns 139, 133; 48
+// x 50, 4 columns 73.5, 69.7.
 template <int N, bool OPC>
-__global__ __launch_bounds__(64) void k_apply_lane(
+__global__ __launch_bounds__(64 * LANE_ROWS, 2) void k_apply_lane(
     DevView v, int R, const cplx* __restrict__ x, cplx* __restrict__ part, int64_t part_total,
     const int32_t* __restrict__ items, const int32_t* __restrict__ active) {
   constexpr int n = 2 * N + 1, S = 2 * N;
   constexpr int NV = 2 * n <= 8 ? 8 : (2 * n <= 16 ? 16 : (2 * n <= 32 ? 32 : 64));
   constexpr int SH = NV == 8 ? 3 : (NV == 16 ? 2 : (NV == 32 ? 1 : 0));  // 6 - log2 NV
-  const int r = blockIdx.y;
+  __shared__ cplx zl[(LANE_CHUNK + 1) * n];
+  const int r = blockIdx.y, tid = threadIdx.x;
   const int32_t* itp = items + (int64_t)LANE_ITEM_INTS * blockIdx.x;
-  const int p = itp[0], jb = itp[2], je = itp[3], b = itp[4];
+  const int p0 = itp[0], rows = itp[1], jb = itp[2], je = itp[3], b = itp[4];
   if (active && active[b * R + r] == 0) return;
-  const int lane = threadIdx.x;
+  const int lane = tid & 63, wv = tid >> 6;
   const int64_t d0 = itp[5];
   const int64_t i0 = *reinterpret_cast<const int64_t*>(itp + 6);
   const int64_t cb = (int64_t)R * i0 + (int64_t)r * *reinterpret_cast<const int64_t*>(itp + 8);
-  const int64_t recb = *reinterpret_cast<const int64_t*>(itp + 10);
-  const int64_t pb = *reinterpret_cast<const int64_t*>(itp + 12);
-  const int j = jb + lane;
+  const int p = p0 + wv, j = jb + lane;
+  // at least LANE_MIN lanes work, those past the last column on its record and zeros: waves of
+  // 2 to 8 active lanes run half as fast (200 disks, whose last chunk has 7: 19 us, 11 so)
+  const bool live = wv < rows && lane < max(je - jb, LANE_MIN);
+  cplx h0, H, E;
+  double r2 = 0.0;
+  if (live) {
+    // records and partial sums of consecutive rows lie at a fixed distance
+    const cplx* __restrict__ rec = v.lt + *reinterpret_cast<const int64_t*>(itp + 10) +
+                                   wv * *reinterpret_cast<const int64_t*>(itp + 14) + min(lane, je - jb - 1);
+    h0 = rec[0];
+    H = rec[LANE_CHUNK];
+    E = rec[2 * LANE_CHUNK];
+    r2 = rec[3 * LANE_CHUNK].x;
+  }
+  // column disks jb .. je of the instance (those of a row skip the row itself), scaled
+  const int64_t e0 = (int64_t)jb * n;
+  const int ne = (je - jb + 1) * n;
+  constexpr int NE = ((LANE_CHUNK + 1) * n + 64 * LANE_ROWS - 1) / (64 * LANE_ROWS);
+  cplx xe[NE], fe[OPC ? NE : 1];
+  double se[OPC ? 1 : NE];
+#pragma unroll
+  for (int u = 0; u < NE; ++u) {  // every load in flight before the first is used
+    const int64_t e = e0 + min(tid + u * 64 * LANE_ROWS, ne - 1);
+    xe[u] = x[cb + e];
+    if constexpr (OPC) fe[u] = v.op_col[i0 + e];
+    else se[u] = v.sJ[i0 + e];
+  }
+#pragma unroll
+  for (int u = 0; u < NE; ++u) {
+    const int e = tid + u * 64 * LANE_ROWS;
+    cplx z;
+    if constexpr (OPC) z = cmul(xe[u], fe[u]);
+    else z = cscale(xe[u], se[u]);
+    if (e < ne) zl[e] = z;
+    else if (e < (LANE_MIN + 1) * n) zl[e] = cmk(0.0, 0.0);
+  }
+  __syncthreads();
+  if (wv >= rows) return;
   cplx acc[n];
 #pragma unroll
   for (int m = 0; m < n; ++m) acc[m] = cmk(0.0, 0.0);
-  if (j < je) {
-    const int q = (int)(d0 + j + ((d0 + j) >= p ? 1 : 0));
-    const cplx* __restrict__ rec = v.lt + recb + lane;
-    const int64_t iq = (int64_t)(q - d0) * n;  // uniform N: moff[q] = (q - d0) n
-    const cplx h0 = rec[0];
-    cplx H = rec[LANE_CHUNK];
-    const cplx E = rec[2 * LANE_CHUNK];
-    const double r2 = rec[3 * LANE_CHUNK].x;
+  if (live) {
+    const cplx* zq = zl + (lane + (d0 + j >= p ? 1 : 0)) * n;
     cplx z[n];
 #pragma unroll
-    for (int k = 0; k < n; ++k)
-      z[k] = OPC ? cmul(x[cb + iq + k], v.op_col[i0 + iq + k]) : cscale(x[cb + iq + k], v.sJ[i0 + iq + k]);
+    for (int k = 0; k < n; ++k) z[k] = zq[k];
 #pragma unroll
     for (int m = 0; m < n; ++m) cmac(acc[m], h0, z[m]);
     cplx Hm = h0;
@@ -377,7 +410,9 @@ __global__ __launch_bounds__(64) void k_apply_lane(
   lane_reduce_scatter<NV>(val, lane);
   const int vi = lane >> SH;
   if ((lane & ((1 << SH) - 1)) == 0 && vi < 2 * n) {
-    double* pr = reinterpret_cast<double*>(part + (int64_t)r * part_total + pb);
+    double* pr = reinterpret_cast<double*>(part + (int64_t)r * part_total +
+                                           *reinterpret_cast<const int64_t*>(itp + 12) +
+                                           wv * (int64_t)itp[16]);
     pr[vi] = val[0];
   }
 }
@@ -2024,10 +2059,13 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
         P.nch[p] = (int32_t)n;
         P.poff[p] = P.part;
         P.part += std::max<int64_t>(n, 1) * np;
+      }
+      const int64_t rec = n * (int64_t)(LANE_CHUNK * LANE_REC);  // records of a row
+      for (int64_t p = d0; p < d0 + Mb; p += LANE_ROWS)
         for (int64_t c = 0; c < n; ++c) {
           const int64_t jb = c * LANE_CHUNK, je = std::min<int64_t>(jb + LANE_CHUNK, Mb - 1);
           P.items.push_back((int32_t)p);
-          P.items.push_back((int32_t)c);
+          P.items.push_back((int32_t)std::min<int64_t>(LANE_ROWS, d0 + Mb - p));
           P.items.push_back((int32_t)jb);
           P.items.push_back((int32_t)je);
           P.items.push_back(b);
@@ -2036,9 +2074,9 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
           push64(Mb * np);
           push64(ltoff[p] + c * (int64_t)(LANE_CHUNK * LANE_REC));
           push64(P.poff[p] + c * np);
-          push64(0);
+          push64(rec);
+          push64(std::max<int64_t>(n, 1) * np);  // partial sums of a row
         }
-      }
       i0 += Mb * np;
     }
     return;
@@ -2250,7 +2288,7 @@ static int launch_lanes(mudiff_ctx* h, int R, const cplx* x, cplx* part, const i
   } else {
     const LaneVariant* lv = find_lane(P.spec_N);
     if (!lv) return fail(MUDIFF_ERR_INVALID, "no operator kernel variant");
-    hipLaunchKernelGGL(h->dv.op_col ? lv->fn_op : lv->fn, dim3(P.n_items, R), dim3(64), 0, s, h->dv, R,
+    hipLaunchKernelGGL(h->dv.op_col ? lv->fn_op : lv->fn, dim3(P.n_items, R), dim3(64 * LANE_ROWS), 0, s, h->dv, R,
                        x, part, P.part_total, P.d_items, active);
   }
   HIP_TRY(hipGetLastError());
