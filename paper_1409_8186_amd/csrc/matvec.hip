@@ -2228,12 +2228,16 @@ int ensure_plan(mudiff_ctx* h, hipStream_t s) {
   P.d_nchunk = (int32_t*)(h->sched_base + align256(H.items.size() * 4));
   P.d_partoff = (int64_t*)((char*)P.d_nchunk + align256(h->M_all * 4));
   P.d_tasks = (int32_t*)((char*)P.d_partoff + align256((size_t)h->M_all * 8));
-  if (!H.tasks.empty())
-    HIP_TRY(hipMemcpyAsync(P.d_tasks, H.tasks.data(), H.tasks.size() * 4, hipMemcpyHostToDevice, s));
-  if (!H.items.empty())
-    HIP_TRY(hipMemcpyAsync(P.d_items, H.items.data(), H.items.size() * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(P.d_nchunk, H.nch.data(), h->M_all * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(P.d_partoff, H.poff.data(), h->M_all * 8, hipMemcpyHostToDevice, s));
+  // one copy of all four (a copy from pageable memory takes the host some 5 us)
+  std::vector<char> blob((char*)P.d_tasks - h->sched_base + H.tasks.size() * 4);
+  auto put = [&](const void* d, const void* src, size_t n) {
+    if (n) memcpy(blob.data() + ((const char*)d - h->sched_base), src, n);
+  };
+  put(P.d_items, H.items.data(), H.items.size() * 4);
+  put(P.d_nchunk, H.nch.data(), (size_t)h->M_all * 4);
+  put(P.d_partoff, H.poff.data(), (size_t)h->M_all * 8);
+  put(P.d_tasks, H.tasks.data(), H.tasks.size() * 4);
+  HIP_TRY(hipMemcpyAsync(h->sched_base, blob.data(), blob.size(), hipMemcpyHostToDevice, s));
   HIP_TRY(hipStreamSynchronize(s));  // the host vectors are released on return
   P.lane = H.lane;
   P.Bt = H.bt;
