@@ -27,6 +27,7 @@
 namespace {
 
 constexpr int NF_THREADS = 256;
+constexpr int NF_WAVES = NF_THREADS / 64;
 constexpr int NF_RC = 4;
 // disks whose coefficients are staged at a time: as many as fit this LDS, which
 // leaves room for the workgroups that the registers allow
@@ -122,13 +123,17 @@ __device__ __forceinline__ void hankel01_near(double x, cplx* H0, cplx* H1) {
 // RC right-hand sides per workgroup; the coefficients of D disks at a time in LDS:
 // with c_m = (i sqrt(pi/8)) F_m rho_m, per order m >= 0 the pair
 // (c_m + (-1)^m c_{-m}, i (c_m - (-1)^m c_{-m})), (c_0, 0) at m = 0.
-template <int RC>
+// SPLIT: 64 points per workgroup, wave w taking every NF_WAVES-th of the staged disks,
+// the waves' sums added in their order.
+template <int RC, bool SPLIT>
 __global__ __launch_bounds__(NF_THREADS, 4) void k_nearfield(DevView v, int R, const cplx* __restrict__ rho,
                                                              int n_pts, const double* __restrict__ pts,
                                                              const double* __restrict__ beta, int point,
                                                              cplx* __restrict__ out, int Nmax, int D) {
-  extern __shared__ cplx lds[];  // [D][Nmax + 1][2][RC]
-  const int P = blockIdx.x * NF_THREADS + threadIdx.x;
+  extern __shared__ cplx lds[];  // [D][Nmax + 1][2][RC]; SPLIT: then the sums [RC][NF_THREADS]
+  __shared__ int s_in[SPLIT ? NF_THREADS : 1];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int P = SPLIT ? blockIdx.x * 64 + (threadIdx.x & 63) : blockIdx.x * NF_THREADS + threadIdx.x;
   const int nchunk = (R + RC - 1) / RC;
   const int b = blockIdx.y / nchunk;
   const int r0 = (blockIdx.y - b * nchunk) * RC;
@@ -170,7 +175,7 @@ __global__ __launch_bounds__(NF_THREADS, 4) void k_nearfield(DevView v, int R, c
       cf[RC] = cmk(-df.y, df.x);
     }
     __syncthreads();
-    for (int dd = 0; dd < nd; ++dd) {
+    for (int dd = SPLIT ? wv : 0; dd < nd; dd += SPLIT ? NF_WAVES : 1) {
       const int64_t p = pd + dd;
       const int Np = v.N[p];
       const cplx* cf = lds + 2 * dd * per;
@@ -219,6 +224,19 @@ __global__ __launch_bounds__(NF_THREADS, 4) void k_nearfield(DevView v, int R, c
       }
     }
   }
+  if constexpr (SPLIT) {
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < RC; ++c) lds[c * NF_THREADS + threadIdx.x] = acc[c];
+    s_in[threadIdx.x] = inside;
+    __syncthreads();
+    if (wv > 0) return;
+    for (int w = 1; w < NF_WAVES; ++w) {
+      inside |= s_in[w * 64 + threadIdx.x] != 0;
+#pragma unroll
+      for (int c = 0; c < RC; ++c) acc[c] = cadd(acc[c], lds[c * NF_THREADS + w * 64 + threadIdx.x]);
+    }
+  }
   if (P >= n_pts) return;
 #pragma unroll
   for (int c = 0; c < RC; ++c) {
@@ -250,12 +268,27 @@ extern "C" int mudiff_nearfield(mudiff_t h, int R, const void* rho, int n_pts, c
   if ((int64_t)h->B * nchunk > 65535) return fail(MUDIFF_ERR_INVALID, "too many instance x RHS columns");
   const int rc = R == 1 ? 1 : (R == 2 ? 2 : NF_RC);  // right-hand sides that share a Hankel evaluation
   typedef void (*fn_t)(DevView, int, const cplx*, int, const double*, const double*, int, cplx*, int, int);
-  const fn_t fn = rc == 1 ? k_nearfield<1> : (rc == 2 ? k_nearfield<2> : k_nearfield<NF_RC>);
   const size_t disk = (size_t)(h->Nmax + 1) * 2 * rc * 16;  // LDS of a disk's coefficients
-  const int D = (int)std::max<size_t>(1, std::min<size_t>(NF_DISKS, NF_LDS / disk));
-  dim3 grid((unsigned)((n_pts + NF_THREADS - 1) / NF_THREADS), (unsigned)(h->B * nchunk));
-  hipLaunchKernelGGL(fn, grid, dim3(NF_THREADS), D * disk, (hipStream_t)stream, h->dv, R, (const cplx*)rho,
-                     n_pts, pts, beta, (flags & MUDIFF_POINT_SOURCE) ? 1 : 0, (cplx*)out, h->Nmax, D);
+  // Fewer workgroups of 256 points than are resident at once (a quarter of that with few
+  // disks): 64 points each, the disks split over the waves.  us without and with: 20 disks,
+  // 1,000 points 107, 45; 100 disks, 1,000 points 466, 161; 300 disks, 2,000 points, 5
+  // columns 1,968, 608; 100 disks, 200,000 points, 2 columns 611, 534; 400 disks, 250,000
+  // points 1,728, 1,623; 4 disks, 50,000 points 35, 26, but 200,000 47, 53; 5 disks, 100,000
+  // points, 2 columns 39.5, 41.0.
+  const int64_t wgs = (int64_t)((n_pts + NF_THREADS - 1) / NF_THREADS) * h->B * nchunk;
+  int D = (int)std::max<size_t>(1, std::min<size_t>(NF_DISKS, NF_LDS / disk));
+  const int DS = (int)std::min<size_t>(NF_DISKS, 2 * NF_LDS / disk) / NF_WAVES * NF_WAVES;
+  const bool split = DS > 0 && h->M_all >= 2 * h->B &&
+                     wgs < (int64_t)h->n_cu * (h->M_all >= 8 * h->B ? 4 : 1);
+  if (split) D = DS;
+  const size_t lds = std::max(D * disk, split ? (size_t)NF_THREADS * rc * 16 : 0);
+  static const fn_t kFn[2][3] = {{k_nearfield<1, false>, k_nearfield<2, false>, k_nearfield<NF_RC, false>},
+                                 {k_nearfield<1, true>, k_nearfield<2, true>, k_nearfield<NF_RC, true>}};
+  const int pts_wg = split ? 64 : NF_THREADS;
+  dim3 grid((unsigned)((n_pts + pts_wg - 1) / pts_wg), (unsigned)(h->B * nchunk));
+  hipLaunchKernelGGL(kFn[split][rc == 1 ? 0 : (rc == 2 ? 1 : 2)], grid, dim3(NF_THREADS), lds,
+                     (hipStream_t)stream, h->dv, R, (const cplx*)rho, n_pts, pts, beta,
+                     (flags & MUDIFF_POINT_SOURCE) ? 1 : 0, (cplx*)out, h->Nmax, D);
   HIP_TRY(hipGetLastError());
   return MUDIFF_OK;
 }

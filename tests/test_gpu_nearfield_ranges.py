@@ -56,3 +56,22 @@ def test_ranges(M, N, ka, R):
     err = np.max(np.abs(u - ref) / size)
     print(M, N, ka, R, "err %.2e" % err, flush=True)
     assert err < 1e-12
+
+
+@pytest.mark.parametrize("M,R", [(2, 1), (9, 3), (40, 2)])
+def test_few_points_as_many(M, R):
+    """The same points alone (disks split over the waves) and among 300,000 (not split)."""
+    from paper_1409_8186_amd import Problem
+    rng = np.random.default_rng(M)
+    side = int(np.ceil(np.sqrt(M)))
+    cen = 3.0 * np.stack(np.meshgrid(np.arange(side), np.arange(side)), -1).reshape(-1, 2)[:M]
+    cl = synth.Cluster(cen, np.full(M, 0.8), rng.integers(3, 12, M).astype(np.int32), 5.0)
+    pr = Problem.from_cluster(cl)
+    rho = torch.tensor(rng.normal(size=R * cl.n_tot) + 1j * rng.normal(size=R * cl.n_tot), device="cuda")
+    pts = rng.uniform(-2.0, 3.0 * side, (300000, 2))
+    pick = np.sort(rng.choice(len(pts), 333, replace=False))
+    many = pr.nearfield(rho, pts, R=R).cpu().numpy()[:, pick]
+    few = pr.nearfield(rho, pts[pick], R=R).cpu().numpy()
+    assert np.array_equal(many == 0.0, few == 0.0)
+    # sums of the same terms in another order: eps times the terms, some of which cancel
+    assert np.max(np.abs(many - few)) < 1e-12 * np.max(np.abs(many))
