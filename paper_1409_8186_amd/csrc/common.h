@@ -124,6 +124,7 @@ struct DevView {
 // All the kernel needs before its vector loads comes from this one record.
 #define LANE_ITEM_INTS 18
 #define LANE_ROWS 4   // row disks per workgroup of k_apply_lane
+#define LANE_FEW_WAVES 400
 #define LANE_MIN 12   // lanes of a wave that work at least
 #define LANE_NMAX 12
 // Largest order of the one-lane-per-pair kernel for any orders: its input panel
@@ -158,6 +159,7 @@ struct MatvecPlan {
   int64_t part_total = 0;       // complex partials per right-hand side
   int64_t row_part = 0;         // the same for the LDS-staged kernel's chunks
   int few = 0;                  // > 0: k_apply_few, ints per task in d_items
+  int lane_rows = LANE_ROWS;    // LANE_UNIFORM: row disks per workgroup
   int few_cols = 0, few_z = 0;  // its LDS: column disks per wave, entries of an input panel
   int32_t* d_items = nullptr;   // [n_items][4] : p, chunk, q_begin, q_end (generic);
                                 // [n_items][LANE_ITEM_INTS] (LANE_UNIFORM),

@@ -319,15 +319,17 @@ __global__ __launch_bounds__(FEW_THREADS) void k_apply_few(
 // Bound by FP64 issue: 3,000 vector instructions per wave at N = 12, 2.7 waves per
 // SIMD at 400 disks, so 3 rounds of 5.6 us.  us per apply, single-wave workgroups and
 // these: 400 x 12 28.2, 25.9; 700 67.9, 61.4; 1,000 120, 114; 400, 7 columns 139, 133; 48
-// x 50, 4 columns 73.5, 69.7.
-template <int N, bool OPC>
-__global__ __launch_bounds__(64 * LANE_ROWS, 2) void k_apply_lane(
+// x 50, 4 columns 73.5, 69.7.  Below LANE_FEW_WAVES waves a workgroup is one row (ROWS 1)
+// whose lanes load their inputs themselves: the hop through LDS would only lengthen the
+// chain (solves, ms: 50 disks 9.6, 10.0; 100 disks 16.5, 16.7; 150 disks, 450 waves, 29.2, 29.1).
+template <int N, bool OPC, int ROWS = LANE_ROWS>
+__global__ __launch_bounds__(64 * ROWS, 2) void k_apply_lane(
     DevView v, int R, const cplx* __restrict__ x, cplx* __restrict__ part, int64_t part_total,
     const int32_t* __restrict__ items, const int32_t* __restrict__ active) {
   constexpr int n = 2 * N + 1, S = 2 * N;
   constexpr int NV = 2 * n <= 8 ? 8 : (2 * n <= 16 ? 16 : (2 * n <= 32 ? 32 : 64));
   constexpr int SH = NV == 8 ? 3 : (NV == 16 ? 2 : (NV == 32 ? 1 : 0));  // 6 - log2 NV
-  __shared__ cplx zl[(LANE_CHUNK + 1) * n];
+  __shared__ cplx zl[ROWS > 1 ? (LANE_CHUNK + 1) * n : 1];
   const int r = blockIdx.y, tid = threadIdx.x;
   const int32_t* itp = items + (int64_t)LANE_ITEM_INTS * blockIdx.x;
   const int p0 = itp[0], rows = itp[1], jb = itp[2], je = itp[3], b = itp[4];
@@ -339,7 +341,7 @@ __global__ __launch_bounds__(64 * LANE_ROWS, 2) void k_apply_lane(
   const int p = p0 + wv, j = jb + lane;
   // at least LANE_MIN lanes work, those past the last column on its record and zeros: waves of
   // 2 to 8 active lanes run half as fast (200 disks, whose last chunk has 7: 19 us, 11 so)
-  const bool live = wv < rows && lane < max(je - jb, LANE_MIN);
+  const bool live = wv < rows && lane < (ROWS > 1 ? max(je - jb, LANE_MIN) : je - jb);
   cplx h0, H, E;
   double r2 = 0.0;
   if (live) {
@@ -351,38 +353,47 @@ __global__ __launch_bounds__(64 * LANE_ROWS, 2) void k_apply_lane(
     E = rec[2 * LANE_CHUNK];
     r2 = rec[3 * LANE_CHUNK].x;
   }
-  // column disks jb .. je of the instance (those of a row skip the row itself), scaled
-  const int64_t e0 = (int64_t)jb * n;
-  const int ne = (je - jb + 1) * n;
-  constexpr int NE = ((LANE_CHUNK + 1) * n + 64 * LANE_ROWS - 1) / (64 * LANE_ROWS);
-  cplx xe[NE], fe[OPC ? NE : 1];
-  double se[OPC ? 1 : NE];
+  if constexpr (ROWS > 1) {
+    // column disks jb .. je of the instance (those of a row skip the row itself), scaled
+    const int64_t e0 = (int64_t)jb * n;
+    const int ne = (je - jb + 1) * n;
+    constexpr int NE = ((LANE_CHUNK + 1) * n + 64 * ROWS - 1) / (64 * ROWS);
+    cplx xe[NE], fe[OPC ? NE : 1];
+    double se[OPC ? 1 : NE];
 #pragma unroll
-  for (int u = 0; u < NE; ++u) {  // every load in flight before the first is used
-    const int64_t e = e0 + min(tid + u * 64 * LANE_ROWS, ne - 1);
-    xe[u] = x[cb + e];
-    if constexpr (OPC) fe[u] = v.op_col[i0 + e];
-    else se[u] = v.sJ[i0 + e];
-  }
+    for (int u = 0; u < NE; ++u) {  // every load in flight before the first is used
+      const int64_t e = e0 + min(tid + u * 64 * ROWS, ne - 1);
+      xe[u] = x[cb + e];
+      if constexpr (OPC) fe[u] = v.op_col[i0 + e];
+      else se[u] = v.sJ[i0 + e];
+    }
 #pragma unroll
-  for (int u = 0; u < NE; ++u) {
-    const int e = tid + u * 64 * LANE_ROWS;
-    cplx z;
-    if constexpr (OPC) z = cmul(xe[u], fe[u]);
-    else z = cscale(xe[u], se[u]);
-    if (e < ne) zl[e] = z;
-    else if (e < (LANE_MIN + 1) * n) zl[e] = cmk(0.0, 0.0);
+    for (int u = 0; u < NE; ++u) {
+      const int e = tid + u * 64 * ROWS;
+      cplx z;
+      if constexpr (OPC) z = cmul(xe[u], fe[u]);
+      else z = cscale(xe[u], se[u]);
+      if (e < ne) zl[e] = z;
+      else if (e < (LANE_MIN + 1) * n) zl[e] = cmk(0.0, 0.0);
+    }
+    __syncthreads();
   }
-  __syncthreads();
   if (wv >= rows) return;
   cplx acc[n];
 #pragma unroll
   for (int m = 0; m < n; ++m) acc[m] = cmk(0.0, 0.0);
   if (live) {
-    const cplx* zq = zl + (lane + (d0 + j >= p ? 1 : 0)) * n;
+    const int jl = lane + (d0 + j >= p ? 1 : 0);
     cplx z[n];
+    if constexpr (ROWS > 1) {
 #pragma unroll
-    for (int k = 0; k < n; ++k) z[k] = zq[k];
+      for (int k = 0; k < n; ++k) z[k] = zl[jl * n + k];
+    } else {
+      const int64_t iq = (int64_t)(jb + jl) * n;
+#pragma unroll
+      for (int k = 0; k < n; ++k)
+        z[k] = OPC ? cmul(x[cb + iq + k], v.op_col[i0 + iq + k]) : cscale(x[cb + iq + k], v.sJ[i0 + iq + k]);
+    }
 #pragma unroll
     for (int m = 0; m < n; ++m) cmac(acc[m], h0, z[m]);
     cplx Hm = h0;
@@ -1893,24 +1904,24 @@ const Variant* find_variant(int bt, int nspec) {
 
 struct LaneVariant {
   int n;
-  lane_fn fn;     // single-layer column factors (real)
-  lane_fn fn_op;  // column factors of an operator set by mudiff_set_operator
+  lane_fn fn[2];     // single-layer column factors (real): LANE_ROWS rows per workgroup, one row
+  lane_fn fn_op[2];  // column factors of an operator set by mudiff_set_operator
 };
 
 // one-lane-per-pair kernels (uniform N)
 const LaneVariant kLane[] = {
-    {1, k_apply_lane<1, false>, k_apply_lane<1, true>},
-    {2, k_apply_lane<2, false>, k_apply_lane<2, true>},
-    {3, k_apply_lane<3, false>, k_apply_lane<3, true>},
-    {4, k_apply_lane<4, false>, k_apply_lane<4, true>},
-    {5, k_apply_lane<5, false>, k_apply_lane<5, true>},
-    {6, k_apply_lane<6, false>, k_apply_lane<6, true>},
-    {7, k_apply_lane<7, false>, k_apply_lane<7, true>},
-    {8, k_apply_lane<8, false>, k_apply_lane<8, true>},
-    {9, k_apply_lane<9, false>, k_apply_lane<9, true>},
-    {10, k_apply_lane<10, false>, k_apply_lane<10, true>},
-    {11, k_apply_lane<11, false>, k_apply_lane<11, true>},
-    {12, k_apply_lane<12, false>, k_apply_lane<12, true>},
+    {1, {k_apply_lane<1, false>, k_apply_lane<1, false, 1>}, {k_apply_lane<1, true>, k_apply_lane<1, true, 1>}},
+    {2, {k_apply_lane<2, false>, k_apply_lane<2, false, 1>}, {k_apply_lane<2, true>, k_apply_lane<2, true, 1>}},
+    {3, {k_apply_lane<3, false>, k_apply_lane<3, false, 1>}, {k_apply_lane<3, true>, k_apply_lane<3, true, 1>}},
+    {4, {k_apply_lane<4, false>, k_apply_lane<4, false, 1>}, {k_apply_lane<4, true>, k_apply_lane<4, true, 1>}},
+    {5, {k_apply_lane<5, false>, k_apply_lane<5, false, 1>}, {k_apply_lane<5, true>, k_apply_lane<5, true, 1>}},
+    {6, {k_apply_lane<6, false>, k_apply_lane<6, false, 1>}, {k_apply_lane<6, true>, k_apply_lane<6, true, 1>}},
+    {7, {k_apply_lane<7, false>, k_apply_lane<7, false, 1>}, {k_apply_lane<7, true>, k_apply_lane<7, true, 1>}},
+    {8, {k_apply_lane<8, false>, k_apply_lane<8, false, 1>}, {k_apply_lane<8, true>, k_apply_lane<8, true, 1>}},
+    {9, {k_apply_lane<9, false>, k_apply_lane<9, false, 1>}, {k_apply_lane<9, true>, k_apply_lane<9, true, 1>}},
+    {10, {k_apply_lane<10, false>, k_apply_lane<10, false, 1>}, {k_apply_lane<10, true>, k_apply_lane<10, true, 1>}},
+    {11, {k_apply_lane<11, false>, k_apply_lane<11, false, 1>}, {k_apply_lane<11, true>, k_apply_lane<11, true, 1>}},
+    {12, {k_apply_lane<12, false>, k_apply_lane<12, false, 1>}, {k_apply_lane<12, true>, k_apply_lane<12, true, 1>}},
 };
 
 const LaneVariant* find_lane(int n) {
@@ -1929,7 +1940,7 @@ struct PlanHost {
   int bt = 4, nspec = -1, zs = 0, ts = 0, ppcap = 1;
   size_t lds = 0;
   int64_t part = 0;
-  int few = 0, few_cols = 0, few_z = 0;
+  int few = 0, few_cols = 0, few_z = 0, lane_rows = LANE_ROWS;
   int64_t row_part = 0;  // partial sums of the LDS-staged kernel (bounds mudiff_matvec_noalloc)
   std::vector<int32_t> items, nch, tasks;
   std::vector<int64_t> poff;
@@ -2051,6 +2062,10 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
       P.items.push_back((int32_t)(v & 0xffffffff));
       P.items.push_back((int32_t)(v >> 32));
     };
+    int64_t waves = 0;
+    for (int b = 0; b < B; ++b)
+      waves += (idisk[b + 1] - idisk[b]) * ((idisk[b + 1] - idisk[b] - 1 + LANE_CHUNK - 1) / LANE_CHUNK);
+    P.lane_rows = waves < LANE_FEW_WAVES ? 1 : LANE_ROWS;
     int64_t i0 = 0;  // first unknown of instance b
     for (int b = 0; b < B; ++b) {
       const int64_t d0 = idisk[b], Mb = idisk[b + 1] - d0;
@@ -2061,11 +2076,11 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
         P.part += std::max<int64_t>(n, 1) * np;
       }
       const int64_t rec = n * (int64_t)(LANE_CHUNK * LANE_REC);  // records of a row
-      for (int64_t p = d0; p < d0 + Mb; p += LANE_ROWS)
+      for (int64_t p = d0; p < d0 + Mb; p += P.lane_rows)
         for (int64_t c = 0; c < n; ++c) {
           const int64_t jb = c * LANE_CHUNK, je = std::min<int64_t>(jb + LANE_CHUNK, Mb - 1);
           P.items.push_back((int32_t)p);
-          P.items.push_back((int32_t)std::min<int64_t>(LANE_ROWS, d0 + Mb - p));
+          P.items.push_back((int32_t)std::min<int64_t>(P.lane_rows, d0 + Mb - p));
           P.items.push_back((int32_t)jb);
           P.items.push_back((int32_t)je);
           P.items.push_back(b);
@@ -2250,6 +2265,7 @@ int ensure_plan(mudiff_ctx* h, hipStream_t s) {
   P.row_part = H.lane == LANE_PAIRS ? H.row_part : H.part;
   P.lds_bytes = H.lds;
   P.few = H.few;
+  P.lane_rows = H.lane_rows;
   P.few_cols = H.few_cols;
   P.few_z = H.few_z;
   P.n_items = (int)(H.items.size() / (H.few ? H.few : H.item_ints));
@@ -2292,7 +2308,7 @@ static int launch_lanes(mudiff_ctx* h, int R, const cplx* x, cplx* part, const i
   } else {
     const LaneVariant* lv = find_lane(P.spec_N);
     if (!lv) return fail(MUDIFF_ERR_INVALID, "no operator kernel variant");
-    hipLaunchKernelGGL(h->dv.op_col ? lv->fn_op : lv->fn, dim3(P.n_items, R), dim3(64 * LANE_ROWS), 0, s, h->dv, R,
+    hipLaunchKernelGGL((h->dv.op_col ? lv->fn_op : lv->fn)[P.lane_rows == 1], dim3(P.n_items, R), dim3(64 * P.lane_rows), 0, s, h->dv, R,
                        x, part, P.part_total, P.d_items, active);
   }
   HIP_TRY(hipGetLastError());

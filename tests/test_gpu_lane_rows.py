@@ -1,4 +1,5 @@
-"""Uniform orders, one lane per pair, four row disks per workgroup: against the oracle's
+"""Uniform orders, one lane per pair, one row disk or (from 400 waves, 135 disks, on) four
+per workgroup: against the oracle's
 dense matrix at row counts with every remainder of four and chunks of 64 column disks
 whose last has 1, 2, 7, 8, 11, 12, 13 and 64 of them; several instances, columns and a
 set operator's complex column factors.  1e-12 as for the applies elsewhere."""
@@ -21,7 +22,9 @@ def _cluster(M, N, seed):
 
 
 @pytest.mark.parametrize("Ms,N,R", [([65], 1, 1), ([66], 3, 2), ([67], 12, 1), ([72, 17], 12, 3), ([73], 7, 1),
-                                    ([76], 5, 7), ([77], 12, 1), ([78, 1, 20], 2, 2), ([129], 4, 1), ([130], 4, 1)])
+                                    ([76], 5, 7), ([77], 12, 1), ([78, 1, 20], 2, 2), ([129], 4, 1), ([130], 4, 1), ([135], 1, 2),
+                                    ([136], 4, 1), ([137], 12, 1), ([140], 2, 7), ([141], 6, 2), ([142], 3, 1),
+                                    ([100, 101, 103, 66], 5, 3)])
 def test_matches_dense(Ms, N, R):
     from paper_1409_8186_amd import Problem
     cls = [_cluster(M, N, M) for M in Ms]
@@ -41,7 +44,7 @@ def test_matches_dense(Ms, N, R):
 def test_operator():
     """Against the matrix-core apply of eight columns."""
     from paper_1409_8186_amd import Problem
-    c = _cluster(71, 6, 1)
+    c = _cluster(138, 6, 1)
     pr = Problem.from_cluster(c)
     pr.set_operator("bwie")
     rng = np.random.default_rng(0)
