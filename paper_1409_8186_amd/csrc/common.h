@@ -173,7 +173,8 @@ enum { LANE_UNIFORM = 1, LANE_PAIRS = 2 };
 
 // MFMA apply tile choice: CT sub-tiles of 8 right-hand sides, RP row disks per
 // work item (RP * CT waves), column-disk segment length QS (0: whole
-// instance), workgroup size.
+// instance; QS_RULE: by rule for the form that runs), workgroup size.
+#define QS_RULE (-1)
 // circ: well-separated pairs of the instances marked in the schedule go
 // through the circulant-embedded form, their close pairs through the MFMA
 // items (column lists).

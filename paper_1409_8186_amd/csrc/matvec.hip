@@ -1133,6 +1133,8 @@ int circ_launch(mudiff_ctx* h, int R, const cplx* x, cplx* zh, cplx* wh, const i
                 int n_citems, int var, const int32_t* con, const int32_t* con_h,
                 const int32_t* active, hipStream_t s);
 
+static int segment(const mudiff_ctx* h, int R, const MfmaChoice& c);
+
 // Host schedule of the MFMA apply for one tile choice.  With c.circ, the
 // instances marked circ_on keep only their close pairs in the MFMA items
 // (column lists) and get per-frequency product items instead.
@@ -1142,7 +1144,7 @@ static void mfma_build(const mudiff_ctx* h, int R, const MfmaChoice& c, MfmaSche
   S.c = c;
   S.dev = nullptr;
   S.resident = false;
-  const int RC = 8 * c.CT;
+  const int RC = 8 * c.CT, QS = segment(h, R, c);
   S.ntile = (R + RC - 1) / RC;
   const int mt = (2 * h->Nmax + 1 + 15) / 16;
   S.npad = 16 * mt;
@@ -1179,7 +1181,7 @@ static void mfma_build(const mudiff_ctx* h, int R, const MfmaChoice& c, MfmaSche
     const int64_t d0 = h->idisk[b], d1 = h->idisk[b + 1], Mb = d1 - d0;
     const bool circ = c.circ && h->circ && h->circ_on[b];
     S.con[b] = circ ? 1 : 0;
-    const int64_t qs = c.QS > 0 ? c.QS : Mb;
+    const int64_t qs = QS > 0 ? QS : Mb;
     // row disks ordered by their number of 16-row tiles (stable), in groups of
     // RP; for the column lists of the circulant form, by a Z-order (Morton)
     // code of their centers within each tile class, so that a group's rows are
@@ -1242,7 +1244,7 @@ static void mfma_build(const mudiff_ctx* h, int R, const MfmaChoice& c, MfmaSche
         }
         ncol = (int64_t)mask.size();
       }
-      const int64_t qsg = circ ? (c.QS > 0 ? c.QS : std::max<int64_t>(ncol, 1)) : qs;
+      const int64_t qsg = circ ? (QS > 0 ? QS : std::max<int64_t>(ncol, 1)) : qs;
       const int nseg = (circ && S.close_rows) ? 1 : (int)((ncol + qsg - 1) / qsg);
       S.gnseg.push_back(nseg);
       S.gbase.push_back(pb);
@@ -1454,16 +1456,26 @@ static int auto_segment(const mudiff_ctx* h, int R, int CT, int RP, bool circ) {
   return 4;
 }
 
+// Segment length of a choice.  A timed one holds no length but the rule, so that the
+// length follows the form when set_circulant or set_circulant_tile changes it: that of
+// the circulant form counts only the instances outside it, and its short segments over
+// whole instances would make more partial sums than the scratch is sized for.  With
+// tiles of more than 8 columns the form's close pairs are in the queue too, as lists no
+// longer than their instance, and take the direct form's length.
+static int segment(const mudiff_ctx* h, int R, const MfmaChoice& c) {
+  return c.QS == QS_RULE ? auto_segment(h, R, c.CT, c.RP, c.circ && c.CT == 1) : c.QS;
+}
+
 // The tiles that are timed on first use of R (mfma_candidates are those that a
 // caller may fix): eight waves, the segment by rule.  Four waves were slower by
 // half wherever the queue was timed (100 disks x 4, 64 columns: 684-739 against
 // 367-458 us).  In the circulant form the queue holds the instances outside it and
 // the close pairs run on k_apply_close, which takes 8-column tiles.
-static std::vector<MfmaChoice> mfma_timed(const mudiff_ctx* h, int R, bool circ) {
+static std::vector<MfmaChoice> mfma_timed(int R, bool circ) {
   std::vector<MfmaChoice> out;
   for (int ct : {1, 2, 4}) {
     if (ct > 1 && (circ || 8 * (ct / 2) >= R)) continue;
-    out.push_back(MfmaChoice{ct, 8 / ct, auto_segment(h, R, ct, 8 / ct, circ), 512, circ});
+    out.push_back(MfmaChoice{ct, 8 / ct, QS_RULE, 512, circ});
   }
   return out;
 }
@@ -1694,17 +1706,18 @@ static size_t mfma_scratch_bytes(mudiff_ctx* h, int R) {
   int64_t part = 0, items = 0, groups = 0, rows = 0;
   std::vector<MfmaChoice> cs = mfma_candidates(R);
   for (MfmaChoice& c : cs) c.QS = MFMA_TAIL_QS;
-  for (const MfmaChoice& c : mfma_timed(h, R, false)) cs.push_back(c);
+  cs.push_back(mfma_default(R));
+  for (const MfmaChoice& c : mfma_timed(R, false)) cs.push_back(c);
   if (h->circ)
-    for (const MfmaChoice& c : mfma_timed(h, R, true)) cs.push_back(c);
+    for (const MfmaChoice& c : mfma_timed(R, true)) cs.push_back(c);
   for (const MfmaChoice& c : cs) {
-    const int64_t tiles = (R + 8 * c.CT - 1) / (8 * c.CT);
+    const int64_t tiles = (R + 8 * c.CT - 1) / (8 * c.CT), QS = segment(h, R, c);
     int64_t n_pb = 0, g = 0;
     for (int b = 0; b < h->B; ++b) {
       const int64_t M = h->idisk[b + 1] - h->idisk[b], gb = (M + c.RP - 1) / c.RP;
       // a timed choice of the circulant form has its short segments outside the form only
       const bool whole = c.circ && h->circ_on[(size_t)b];
-      n_pb += gb * tiles * (c.QS > 0 && !whole ? (M + c.QS - 1) / c.QS : 1);
+      n_pb += gb * tiles * (QS > 0 && !whole ? (M + QS - 1) / QS : 1);
       g += gb;
     }
     part = std::max(part, n_pb * c.RP * npad * 8 * c.CT);
@@ -1735,6 +1748,15 @@ static size_t mfma_scratch_bytes(mudiff_ctx* h, int R) {
   return mx;
 }
 
+// Whether schedule S keeps to the scratch that was asked for (mfma_scratch_bytes covers
+// every choice; this is what stands between a choice it misses and memory that is not ours).
+static int scratch_check(mudiff_ctx* h, const MfmaSched& S) {
+  const size_t need = mfma_scratch_layout(h, S).total, have = mfma_scratch_bytes(h, S.R);
+  if (need <= have) return MUDIFF_OK;
+  return fail(MUDIFF_ERR_NOMEM, "this apply's schedule needs " + std::to_string(need) + " bytes of scratch, more than the " +
+                                    std::to_string(have) + " of its workspace");
+}
+
 // Pick the tile choice for R by timing the mfma_timed tiles and the product
 // variants worth it on x -> y (outputs are overwritten; the inputs only need to be
 // finite).
@@ -1751,9 +1773,9 @@ static int mfma_autotune(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scr
   const int cmode = fc != h->circ_modes.end() ? fc->second : -1;
   const bool cu = circ_usable(h, R);
   // the circulant form first: it usually sets the bar the direct tiles then fail
-  if (cu) cands = mfma_timed(h, R, true);
+  if (cu) cands = mfma_timed(R, true);
   if (cmode != 1 || !cu)
-    for (const MfmaChoice& c : mfma_timed(h, R, false)) cands.push_back(c);
+    for (const MfmaChoice& c : mfma_timed(R, false)) cands.push_back(c);
   // The direct form's work (8 flops per complex multiply-add over every
   // ordered pair) at the FP64 matrix-core peak, 78.6 TFLOP/s: no direct tile
   // beats it, so once a candidate's pair of applies is faster than twice that,
@@ -1774,6 +1796,7 @@ static int mfma_autotune(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scr
   auto time_one = [&](const MfmaChoice& c) -> float {
     MfmaSched S;
     mfma_build(h, R, c, S);
+    if ((rc = scratch_check(h, S)) != MUDIFF_OK) return 0.0f;
     struct Drain {  // the local schedule's copies finish before it is released
       hipStream_t st;
       ~Drain() { (void)hipStreamSynchronize(st); }
@@ -1837,11 +1860,11 @@ static void sched_drop(mudiff_ctx* h, int R) {
 // first use of R when x, y are given, else the default choice).
 static int mfma_prepare(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scratch,
                         hipStream_t s) {
+  int rc = MUDIFF_OK;
   auto f = h->mfma_choice.find(R);
   if (f == h->mfma_choice.end()) {
     if (x && y && h->mfma_tune) {
-      const int rc = mfma_autotune(h, R, x, y, scratch, s);
-      if (rc != MUDIFF_OK) return rc;
+      if ((rc = mfma_autotune(h, R, x, y, scratch, s)) != MUDIFF_OK) return rc;
     } else {
       MfmaChoice d = mfma_default(R);
       d.circ = circ_usable(h, R);
@@ -1855,6 +1878,10 @@ static int mfma_prepare(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scra
   if (S.R != R || !(S.c == c)) {
     sched_wait(h);
     mfma_build(h, R, c, S, h->mfma_tail ? h->mfma_tail_cols : std::vector<int32_t>{});
+    if ((rc = scratch_check(h, S)) != MUDIFF_OK) {
+      S.R = 0;  // not a schedule that a later call may run
+      return rc;
+    }
     sched_pack(S);
   }
   return sched_place(h, S, scratch, s);
@@ -2470,7 +2497,7 @@ extern "C" int mudiff_apply_config(mudiff_t h, int R, int* kind, int* ct, int* r
     if (ch.circ) k = 3;
     c = ch.CT;
     r = ch.RP;
-    q = ch.QS;
+    q = segment(h, R, ch);
     t = ch.threads;
     auto g = h->mfma_time_ms.find(R);
     if (g != h->mfma_time_ms.end()) tm = g->second;

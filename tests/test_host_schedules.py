@@ -1,0 +1,105 @@
+"""Schedules of the operator apply on the host alone (tests/native/build_host.py: kernels are
+recorded, not run): what the launches are given lies inside the workspace whose size the library
+asks for, for every tile that the setters can lead to."""
+import ctypes
+import os
+import sys
+
+import numpy as np
+import pytest
+
+sys.path.insert(0, os.path.join(os.path.dirname(os.path.abspath(__file__)), "native"))
+import build_host  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def host():
+    return build_host.Host()
+
+
+def grid(M, spacing, orders, k=5.0):
+    """M unit disks on a square grid, with orders taken in turn."""
+    w = int(np.ceil(np.sqrt(M)))
+    c = np.array([(i % w, i // w) for i in range(M)], float) * spacing
+    return c, np.ones(M), np.resize(orders, M), k
+
+
+ORDERS = [16, 23, 19, 21]
+
+
+def mixed(M, m):
+    """A sparse instance of M disks (in the circulant form) and a dense one of m (outside it:
+    all its pairs are close)."""
+    return [grid(M, 10.0, ORDERS), grid(m, 2.1, ORDERS)]
+
+
+class Applies:
+    """Applies of one handle, each in a workspace of the size that the library names; notes the
+    largest end of the work queue's partial sums, relative to that workspace."""
+
+    def __init__(self, host, h, R):
+        self.host, self.h, self.R = host, h, R
+        n = (ctypes.c_int64 * 2)()
+        host.check(host.lib.mudiff_sizes(h, n))
+        self.x = host.array(16 * R * sum(n))
+        self.y = host.array(16 * R * sum(n))
+        self.bytes = host.lib.mudiff_matvec_workspace_size(h, R)
+        self.ws = host.array(self.bytes)
+        self.end, self.queues = 0, 0
+        host.hooks["k_apply_mfmaI"] = self.queue
+
+    def queue(self, read, blocks):
+        # (view, R, x, active, items, n_items, head, part, blk, ...)
+        n = read(5, ctypes.c_int32)
+        items = np.ctypeslib.as_array(ctypes.cast(read(4, ctypes.c_void_p), ctypes.POINTER(ctypes.c_int32)), (n, 7))
+        part, blk = read(7, ctypes.c_void_p), read(8, ctypes.c_int64)
+        self.end = max(self.end, part + (int(items[:, 5].max()) + 1) * blk * 16 - self.ws.base)
+        self.queues += 1
+
+    def run(self):
+        self.host.check(self.host.lib.mudiff_matvec(self.h, self.R, self.x.base, self.y.base, 1,
+                                                    self.ws.base, self.bytes, None))
+        assert self.end <= self.bytes, (self.end, self.bytes)
+
+    def tile(self):
+        v = [ctypes.c_int(0) for _ in range(6)]
+        self.host.check(self.host.lib.mudiff_circulant_tile(self.h, self.R, *[ctypes.byref(x) for x in v]))
+        return [x.value for x in v]
+
+    def config(self):
+        v = [ctypes.c_int(0) for _ in range(5)]
+        self.host.check(self.host.lib.mudiff_apply_config(self.h, self.R, *[ctypes.byref(x) for x in v], None))
+        return [x.value for x in v]
+
+
+@pytest.mark.parametrize("M,m,R", [(200, 10, 64), (400, 20, 32), (60, 17, 9), (90, 3, 130)])
+def test_partial_sums_inside_the_workspace_when_the_form_changes(host, M, m, R):
+    """A timed choice of the circulant form, its tile fixed, the form switched off and on again:
+    the work queue's segments suit the form that runs."""
+    h = host.tables(mixed(M, m), circulant=True)
+    lib = host.lib
+    for first in (0, 1):  # the first candidate (circulant form) or the last one (direct) is the fastest
+        a = Applies(host, h, R)
+        t = iter(range(1000, 0, -1))
+        host.clock(lambda: float(next(t)) if first else 1.0)
+        host.check(lib.mudiff_set_circulant(h, R, -1))
+        a.run()
+        if a.config()[0] == 3:
+            host.check(lib.mudiff_set_circulant_tile(h, R, *a.tile()))
+            a.run()
+        host.check(lib.mudiff_set_circulant(h, R, 0))
+        a.run()
+        host.check(lib.mudiff_set_circulant(h, R, 1))
+        a.run()
+        for ct in (1, 2, 4):  # direct tiles that a caller may fix, in both forms
+            for waves in (4, 8):
+                for qs in (0, 32):
+                    if ct > max(1, -(-R // 8)):
+                        continue
+                    if lib.mudiff_set_apply_config(h, R, ct, waves // ct, qs, 64 * waves):
+                        continue
+                    for mode in (1, 0):
+                        host.check(lib.mudiff_set_circulant(h, R, mode))
+                        a.run()
+        assert a.queues > 0
+    host.check(lib.mudiff_destroy(h))
