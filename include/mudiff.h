@@ -30,12 +30,13 @@
  *               outputs are valid after the stream is synchronised.
  *               mudiff_gmres and mudiff_grad synchronise `stream` themselves
  *               (once per restart cycle) to test convergence.  On the
- *               circulant form, in the straggler phase of a solve and at medium
- *               sizes, part of an apply runs on a second stream of the handle,
- *               forked from and joined back into `stream` by events (so still
- *               ordered with the caller's work; while the caller captures
- *               `stream`, medium sizes stay on it); a handle is used by one
- *               host thread at a time.
+ *               circulant form, in the straggler phase of a solve, at medium
+ *               sizes and for a few instances outside the form, part of an
+ *               apply runs on a second stream of the handle, forked from and
+ *               joined back into `stream` by events (so still ordered with the
+ *               caller's work; an apply that the caller captures, or that is
+ *               profiled, stays on `stream`); a handle is used by one host
+ *               thread at a time.
  *   batching    B independent instances (own disks, own k) share one handle.
  *               Instance b owns disks [disk_off[b], disk_off[b+1]).  Vectors
  *               are packed [B][R][N_b] with N_b = sum_{p in b} (2 N_p + 1):

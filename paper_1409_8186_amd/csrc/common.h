@@ -254,8 +254,9 @@ struct mudiff_ctx {
   char* res_base = nullptr;
   size_t res_bytes = 0, res_used = 0;
   hipEvent_t sched_ev = nullptr;          // recorded after the last schedule upload
-  // in the straggler phase and at medium sizes the circulant form's close pairs run
-  // beside its transforms and products: a second stream (default priority) forked
+  // in the straggler phase and at medium sizes the circulant form's close pairs, and at
+  // all sizes a short queue of the instances outside it, run beside its transforms and
+  // products: a second stream (default priority) forked
   // after the input scaling and joined before the output pass
   hipStream_t aux = nullptr;
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;

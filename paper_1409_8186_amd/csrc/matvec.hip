@@ -1538,7 +1538,7 @@ static int sched_place(mudiff_ctx* h, MfmaSched& S, char* scratch, hipStream_t s
   return mfma_upload(h, S, scratch, s);
 }
 
-// Second stream and events of the straggler phase.
+// Second stream of the handle (straggler phase, medium sizes, short queues) and its events.
 static int aux_stream(mudiff_ctx* h) {
   if (h->aux) return MUDIFF_OK;
   HIP_TRY(hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking));
@@ -1602,7 +1602,7 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, char* base, const cplx
   // work queue and the close-pair rows run on the second stream, beside the
   // transforms and products, which share none of their outputs (there every launch
   // is small and latency-bound), the close pairs also at medium sizes (close_beside).
-  // A short queue, that of a few instances outside the form, always runs there: it
+  // A short queue, that of a few instances outside the form, runs there at all sizes: it
   // leaves most of the chip idle for as long as its items take.
   mf_fn fn = nullptr;  // checked before the fork, so that every error leaves the streams joined
   if (S.n_items > 0) {
@@ -1623,13 +1623,13 @@ static int mfma_launch(mudiff_ctx* h, const MfmaSched& S, char* base, const cplx
                                (((n_short + rpb - 1) / rpb + 7) & ~(int64_t)7) * ((per + wpr - 1) / wpr);
   if (n_close > 0 && close_blocks >= ((int64_t)1 << 31)) return fail(MUDIFF_ERR_INVALID, "close pairs: too many tiles");
   // (a caller's capture keeps to the caller's stream; a profiled apply keeps its phases apart)
-  bool beside = h->mfma_tail;
-  if (!beside && S.close_beside && h->prof_cur < 0) {
+  bool beside = h->mfma_tail, fork = S.c.circ && beside && (S.n_items > 0 || S.close_rows);
+  const bool short_queue = S.c.circ && S.close_rows && S.n_items > 0 && S.n_items <= 4 * h->n_cu;
+  if (!beside && (S.close_beside || short_queue) && h->prof_cur < 0) {
     hipStreamCaptureStatus cst = hipStreamCaptureStatusNone;
-    beside = h->own_capture || (hipStreamIsCapturing(s, &cst) == hipSuccess && cst == hipStreamCaptureStatusNone);
+    fork = h->own_capture || (hipStreamIsCapturing(s, &cst) == hipSuccess && cst == hipStreamCaptureStatusNone);
+    beside = fork && S.close_beside;
   }
-  const bool fork = S.c.circ && (h->mfma_tail ? S.n_items > 0 || S.close_rows
-                                               : beside || (S.close_rows && S.n_items > 0 && S.n_items <= 4 * h->n_cu));
   if (fork) {
     if ((rc = aux_stream(h)) != MUDIFF_OK) return rc;
     HIP_TRY(hipEventRecord(h->fork_ev, s));

@@ -103,3 +103,33 @@ def test_partial_sums_inside_the_workspace_when_the_form_changes(host, M, m, R):
                         a.run()
         assert a.queues > 0
     host.check(lib.mudiff_destroy(h))
+
+
+@pytest.mark.parametrize("R", [8, 64])
+def test_second_stream_only_outside_captures_and_profiles(host, R):
+    """A batch with a short queue beside the circulant form: the queue runs on the handle's second
+    stream, but not while the caller captures the apply or an apply is profiled (its phases are
+    timed between events of the caller's stream)."""
+    h = host.tables(mixed(200, 10), circulant=True)
+    host.clock(lambda: 1.0)
+    a = Applies(host, h, R)
+    a.run()
+
+    def streams():
+        host.launches.clear()
+        n = a.queues
+        a.run()
+        assert a.queues == n + 1  # a queue there is
+        return {s for *_, s in host.launches}
+
+    assert len(streams()) == 2
+    host.lib.host_capturing(1)
+    assert streams() == {None}
+    host.lib.host_capturing(0)
+    host.check(host.lib.mudiff_profile_begin(h, 1))
+    assert streams() == {None}
+    assert len(streams()) == 2  # past the profiled applies
+    n, ms = ctypes.c_int(0), (ctypes.c_double * 5)()
+    host.check(host.lib.mudiff_profile_end(h, ctypes.byref(n), ms))
+    assert n.value == 1
+    host.check(host.lib.mudiff_destroy(h))
