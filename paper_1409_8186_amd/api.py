@@ -198,7 +198,7 @@ class Problem:
                             (128, 16, 8, 2, 256, 4), (128, 16, 8, 2, 256, 3), (128, 16, 16, 2, 256, 3),
                             (32, 32, 16, 3, 256, 3), (64, 16, 16, 3, 256, 3), (32, 16, 16, 3, 128, 3)],
                        1: [(128, 8, 16, 2, 256, 4), (64, 8, 16, 2, 256, 4), (128, 8, 8, 2, 256, 4),
-                           (64, 16, 16, 3, 256, 3), (16, 8, 16, 3, 64, 4)]}
+                           (64, 16, 16, 3, 256, 3), (32, 16, 16, 3, 128, 3), (16, 8, 16, 3, 64, 4)]}
 
     @classmethod
     def circulant_tiles(cls, R: int) -> list:

@@ -763,7 +763,7 @@ std::vector<int> circ_variants(int R) {
   if (R >= 48) return {2, 8, 9, 10, 12, 13, 14, 15, 16, 17, 18, 19, 22, 23, 24, 25, 26, 27, 28, 31, 32, 33, 34};
   if (R >= 24) return {2, 3, 4, 8, 9, 10, 12, 13, 14, 19, 23, 24, 28, 31, 34, 35, 36};
   if (R >= 12) return {5, 6, 11, 20, 29, 30, 34, 36, 37};
-  return {6, 7, 21, 36, 38};
+  return {6, 7, 21, 36, 37, 38};
 }
 // The variants that are timed on first use of R, the fastest of the above at the sizes
 // tried.  A tile is a matter of how many workgroups there are for the 256 compute units

@@ -1729,6 +1729,7 @@ static size_t mfma_scratch_bytes(mudiff_ctx* h, int R) {
   if (h->circ) {
     std::vector<int> vars = circ_variants(R);
     vars.push_back(circ_variant(R));
+    for (int v : circ_timed(R)) vars.push_back(v);
     for (int v : vars) {
       int bm = 0, bn = 0;
       circ_tile(v, &bm, &bn);

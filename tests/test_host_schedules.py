@@ -133,3 +133,33 @@ def test_second_stream_only_outside_captures_and_profiles(host, R):
     host.check(host.lib.mudiff_profile_end(h, ctypes.byref(n), ms))
     assert n.value == 1
     host.check(host.lib.mudiff_destroy(h))
+
+
+def pick(host, win):
+    """Clock under which timed candidate number `win` is the fastest."""
+    n = iter(range(10 ** 6))
+    host.clock(lambda: 1.0 if next(n) == win else 2.0)
+
+
+def test_timed_product_tiles_can_be_fixed(host):
+    """Every product tile that first use may choose is one that set_circulant_tile takes, and that
+    Problem.circulant_tiles lists."""
+    from paper_1409_8186_amd.api import Problem
+    h = host.tables([grid(30, 10.0, ORDERS)], circulant=True)
+    for R in range(8, 70):
+        seen = set()
+        for win in range(6):  # timed pairs, and the warm-ups between them
+            host.check(host.lib.mudiff_set_circulant(h, R, 1))
+            pick(host, win)
+            a = Applies(host, h, R)
+            a.run()
+            seen.add(tuple(a.tile()))
+            # timed again at the next round: back to no choice
+            host.check(host.lib.mudiff_set_circulant(h, R, 1))
+        for t in seen:
+            assert t in Problem.circulant_tiles(R), (R, t)
+        for t in Problem.circulant_tiles(R):
+            host.check(host.lib.mudiff_set_circulant_tile(h, R, *t))
+        host.check(host.lib.mudiff_destroy(h))
+        h = host.tables([grid(30, 10.0, ORDERS)], circulant=True)
+    host.check(host.lib.mudiff_destroy(h))
