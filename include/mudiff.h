@@ -267,7 +267,7 @@ int mudiff_matvec_noalloc(mudiff_t h, int R, const void* x, void* y, int op, voi
  *   threads    MFMA workgroup size
  *   ms         timed duration of one apply when the MFMA tile was autotuned
  *              (the first mudiff_matvec / mudiff_gmres / mudiff_grad with this
- *              R times every candidate on the real data), else 0
+ *              R times a few tiles on the real data), else 0
  * Fields that do not apply to `kind` are set to 0.  Before the first call
  * with this R, the MFMA fields hold the default tile. */
 int mudiff_apply_config(mudiff_t h, int R, int* kind, int* ct, int* rp, int* qs, int* threads,
@@ -275,7 +275,9 @@ int mudiff_apply_config(mudiff_t h, int R, int* kind, int* ct, int* rp, int* qs,
 
 /* Fixes the MFMA tile of the R-column apply on this handle instead of timing
  * the candidates (ct in {1,2,4} with ct <= max(1, ceil(R/8)), rp = waves/ct
- * with waves in {4, 8} and threads = 64 * waves, qs in {0, 32}).  Returns
+ * with waves in {4, 8} and threads = 64 * waves, qs in {0, 32}; or what
+ * mudiff_apply_config reports of a timed apply of this batch, whose qs then
+ * follows the form that runs).  Returns
  * MUDIFF_ERR_INVALID for a tile outside that set or when the R-column apply
  * does not run on MFMA.  Takes effect at the next call with this R. */
 int mudiff_set_apply_config(mudiff_t h, int R, int ct, int rp, int qs, int threads);

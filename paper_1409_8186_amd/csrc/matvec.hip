@@ -15,6 +15,7 @@
 // adds them in chunk order, so the result does not depend on scheduling.
 #include "common.h"
 
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
@@ -2521,7 +2522,17 @@ extern "C" int mudiff_set_apply_config(mudiff_t h, int R, int ct, int rp, int qs
   if (R < 1) return fail(MUDIFF_ERR_INVALID, "R < 1");
   if (!use_mfma(h, R)) return fail(MUDIFF_ERR_INVALID, "this apply does not run on MFMA");
   MfmaChoice want{ct, rp, qs, threads, false};
-  for (const MfmaChoice& c : mfma_candidates(R))
+  std::vector<MfmaChoice> cands = mfma_candidates(R);
+  if (std::find(cands.begin(), cands.end(), want) == cands.end())
+    // a timed configuration, as mudiff_apply_config reports it in either form
+    for (MfmaChoice c : mfma_timed(R, false)) {
+      const bool tile = ct == c.CT && rp == c.RP && threads == c.threads;
+      if (tile && (qs == segment(h, R, c) || (h->circ && ct == 1 && qs == auto_segment(h, R, ct, rp, true)))) {
+        want.QS = c.QS;
+        cands.push_back(c);
+      }
+    }
+  for (const MfmaChoice& c : cands)
     if (c == want) {
       auto f = h->circ_modes.find(R);
       want.circ = circ_usable(h, R) && (f == h->circ_modes.end() || f->second != 0);

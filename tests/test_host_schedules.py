@@ -163,3 +163,29 @@ def test_timed_product_tiles_can_be_fixed(host):
         host.check(host.lib.mudiff_destroy(h))
         h = host.tables([grid(30, 10.0, ORDERS)], circulant=True)
     host.check(host.lib.mudiff_destroy(h))
+
+
+@pytest.mark.parametrize("instances", [[grid(30, 10.0, ORDERS)], [grid(30, 2.1, [8, 3])], mixed(50, 10)],
+                         ids=["sparse", "dense", "mixed"])
+def test_timed_configuration_can_be_fixed(host, instances):
+    """What apply_config reports of a timed apply is taken by set_apply_config, here and on another
+    handle of the same batch, and reported again; other lengths are refused."""
+    for R in (8, 11, 16, 24, 33, 64):
+        for win in range(6):
+            pick(host, win)
+            h = host.tables(instances, circulant=True)
+            Applies(host, h, R).run()
+            a = Applies(host, h, R)
+            found = a.config()
+            host.check(host.lib.mudiff_destroy(h))
+            h = host.tables(instances, circulant=True)
+            a = Applies(host, h, R)
+            for _ in range(2):
+                host.check(host.lib.mudiff_set_circulant(h, R, int(found[0] == 3)))
+                host.check(host.lib.mudiff_set_apply_config(h, R, *found[1:]))
+                assert a.config() == found
+                a.run()
+            for qs in (1, 5, 31, 128):
+                assert host.lib.mudiff_set_apply_config(h, R, *found[1:3], qs, found[4]) == 1
+            assert a.config() == found
+            host.check(host.lib.mudiff_destroy(h))
