@@ -312,8 +312,9 @@ extern "C" int mudiff_farfield(mudiff_t h, int R, const void* rho, int n_theta, 
   // against 391, 256 columns at 360 angles (5,888) 4,810 against 760; 60 disks, 17
   // columns at 361 angles 38 against 29, 8 disks, 100 columns 26 against 10.
   const bool many = R >= 4 && (mmax < 64 || (int64_t)h->B * R * ntt >= 512);
-  if (many && h->Nmax <= FF_MFMA_N && nct * ntt < ((int64_t)1 << 31)) {
-    const int nw = mmax > 4 ? 16 : 4;
+  const int nw = mmax > 4 ? 16 : 4;
+  // (a launch has fewer than 2^32 threads along x; the other kernel has its columns along y)
+  if (many && h->Nmax <= FF_MFMA_N && nct * ntt * 64 * nw < ((int64_t)1 << 32)) {
     const ff_fn fn = ff_select(mmax, h->dv.op_ff != nullptr);
     const size_t lds = std::max((size_t)(2 * h->Nmax + 1) * FM_T * 16, (size_t)nw * 512 * 8);
     hipLaunchKernelGGL(fn, dim3((unsigned)(nct * ntt), (unsigned)h->B), dim3(64 * nw), lds, (hipStream_t)stream,
