@@ -16,13 +16,53 @@ from . import _lib as L
 from .api import Problem
 
 
+def _misfit_grad(inst, device, betas, thetas, target, opts):
+    """Problem.grad of the instances, in the form and with the solver that suit the columns."""
+    R = (betas if isinstance(betas, torch.Tensor) else np.asarray(betas)).reshape(len(inst), -1).shape[1]
+    restart = opts.get("restart", 50)
+    circulant, sstep = opts.get("circulant"), opts.get("sstep")
+    # The circulant form carries the solves of 8 and more columns (orders up to 31); the
+    # first apply times it against the direct form.  Its tables are two to three times the
+    # direct form's, so where they do not fit the direct form solves alone.
+    auto_circulant = circulant is None
+    if auto_circulant:
+        circulant = R >= 8 and max(int(np.max(n)) for _, _, n, _ in inst) <= 31
+    # s-step solves for many columns (restarts up to 64): their basis sweeps are half of a
+    # lockstep step (4 x 100 disks x 64 columns: 179 against 249 ms per gradient).  Where
+    # one stagnates, one-vector cycles solve.
+    auto_sstep = sstep is None
+    if auto_sstep:
+        sstep = 10 if R >= 8 and 20 <= restart <= 64 else 0
+    while True:
+        P = None
+        try:
+            P = Problem(inst, device=device, circulant=circulant)
+            return P.grad(betas, thetas, target, restart=restart, tol=opts.get("tol", 1e-10),
+                          maxit=opts.get("maxit", 20000), flags=L.SSTEP | L.sstep_size(sstep) if sstep else 0)
+        except torch.OutOfMemoryError:
+            if not (auto_circulant and circulant or auto_sstep and sstep):
+                raise
+            circulant = circulant and not auto_circulant
+            sstep = 0 if auto_sstep else sstep
+        except L.MudiffError as e:
+            if L.STATUS.get(e.status) != "NOT_CONVERGED" or not (auto_sstep and sstep):
+                raise
+            sstep = 0
+        finally:
+            if P is not None:
+                P.close()
+
+
 class FarFieldMisfit(torch.autograd.Function):
     """loss[b] = sum_{r, j} |a_b(theta_j; beta_{b,r}) - target_{b,r,j}|^2.
 
     Arguments: centers [M,2] float64, radii [M] float64, k [B] float64 (the
     differentiable inputs), then n_modes [M] (int), disk_off [B+1] (int),
     betas [B,R], thetas [n_rec], target [B*R, n_rec] complex128 and a dict of
-    solver options (restart, tol, maxit)."""
+    solver options: restart, tol, maxit; circulant (True or False: tables with or
+    without the circulant form) and sstep (Newton vectors per block of s-step
+    solves, 0 for one-vector ones), both chosen by the number of columns when
+    absent or None."""
 
     @staticmethod
     def forward(ctx, centers, radii, k, n_modes, disk_off, betas, thetas, target, opts=None):
@@ -35,19 +75,8 @@ class FarFieldMisfit(torch.autograd.Function):
         inst = [(c[off[b]:off[b + 1]], a[off[b]:off[b + 1]], nm[off[b]:off[b + 1]], kk[b])
                 for b in range(len(off) - 1)]
         dev = centers.device if centers.is_cuda else torch.device("cuda")
-        # the circulant form carries the solves of 8 and more columns (orders up to 31);
-        # the first apply times it against the direct form
-        R = (betas if isinstance(betas, torch.Tensor) else np.asarray(betas)).reshape(len(inst), -1).shape[1]
-        circulant = R >= 8 and int(nm.max()) <= 31
-        P = Problem(inst, device=str(dev), circulant=circulant)
-        restart = opts.get("restart", 50)
-        # s-step solves for many columns (restarts up to 64): their basis sweeps are half of a
-        # lockstep step (4 x 100 disks x 64 columns: 179 against 249 ms per gradient)
-        flags = L.SSTEP | L.sstep_size(10) if R >= 8 and 20 <= restart <= 64 else 0
-        loss, dc, da, dk = P.grad(betas, thetas, target, restart=restart, tol=opts.get("tol", 1e-10),
-                                  maxit=opts.get("maxit", 20000), flags=flags)
-        P.close()
-        inst_of = torch.as_tensor(np.repeat(np.arange(len(off) - 1), np.diff(off)), device=dev)
+        loss, dc, da, dk = _misfit_grad(inst, str(dev), betas, thetas, target, opts)
+        inst_of = torch.as_tensor(np.repeat(np.arange(len(off) - 1), np.diff(off)), device=dc.device)
         ctx.save_for_backward(dc, da, dk, inst_of)
         return loss.to(centers.device)
 
