@@ -23,10 +23,16 @@ def _p(t):  # (an int: the signatures convert it, at a third of a c_void_p's cos
     return None if t is None else t.data_ptr()
 
 
+# the current stream's handle without the Stream object: 0.3 us of a launch instead of
+# 2.8, a third of what the smallest apply takes (torch keeps it for its own compiled
+# code; without it the public way)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    # the current stream's handle without the Stream object: 0.3 us of a launch instead
-    # of 2.8, a third of what the smallest apply takes
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _host(a, dtype):
