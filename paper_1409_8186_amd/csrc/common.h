@@ -130,6 +130,8 @@ struct DevView {
 // Largest order of the one-lane-per-pair kernel for any orders: its input panel
 // [2 N + 1][65] of 64 column disks fits 64 KB of LDS.
 #define PAIRS_NMAX 31
+// Largest instance of k_apply_few.
+#define FEW_DISKS 16
 
 // Column c = b * R + r of a packed [B][R][N_b] vector starts at
 // R * imode[b] + r * N_b.

@@ -203,7 +203,6 @@ __global__ __launch_bounds__(APPLY_THREADS) void k_apply(
 // 4 disks of 31 modes: 6.35 us as LDS-staged rows, 3.5 so.
 #define FEW_THREADS 256
 #define FEW_WAVES (FEW_THREADS / 64)
-#define FEW_DISKS 16
 #define FEW_HDR 16  // instance, first output, N_p, column disks, unknown of mode -N_p, imode, N_b, M
 #define FEW_COL 8   // offset in the instance vector, N_q, symbol t^{pq}_0, 1: times (-1)^s
 #define FEW_PAD 31  // window entries before output m0's, for the outputs after it
@@ -1995,6 +1994,64 @@ static void choose_variant(int M, const int32_t* N, int* bt, int* nspec) {
 
 #define APPLY_LDS_BUDGET (64 * 1024)
 
+// Column disks that the LDS-staged kernel passes over at a time, for a row of np modes
+// in a batch whose largest order is nmax.
+static int lds_cols(int np, int nmax, int bt) {
+  const int zs = (2 * nmax + 1 + bt - 1) / bt * bt;
+  const int cap = std::max(1, (int)(APPLY_LDS_BUDGET / ((size_t)(3 * zs - 1) * 16)));
+  return std::max(1, std::min(APPLY_THREADS / ((np + bt - 1) / bt), cap));
+}
+
+// Batches of k_apply_pairs: every N_p <= PAIRS_NMAX, and the faster one of the two by an
+// estimate.  A wave of k_apply_pairs fills its 64 lanes with the disks of one instance and
+// issues the same instructions however few they are; the LDS-staged kernel spreads one
+// pair over many threads, but pays for every pass over its rows' columns, for every
+// workgroup, and for the fences of rows that span several.  One column, us (fitted to 124
+// batches of 18 to 8,700 disks, orders 1..4, 13..20 and 24..31, within 12% and 8% in the
+// mean):
+//   LDS-staged   5.9 + 0.096 passes (2N+1) + 9.5 (some row spans workgroups) + 0.010 a
+//                workgroup + 0.92 (1.16 in rows that span) per 10^6 multiply-adds
+//   k_apply_pairs   6.8 + 0.144 (2N+1) + 2.33 per 10^6 wave instructions + 0.00107 a task
+// Measured, LDS-staged against k_apply_pairs: orders 13..20, 100 instances of 5 to 12 disks
+// and one of 24 24.5, 31.7, and one of 200 143, 52; 1,000 and one of 24 188, 235; 300 of 2
+// to 4 and one of 24 22.4, 36.4; one instance of 26 19.1, 14.7, 8 of 64 148, 27; orders
+// 24..31, 1,000 of 5 to 12 and one of 24 297, 483; orders 1..4, one of 26 7.9, 9.4.
+#define PAIRS_MARGIN 1.05
+bool pairs_batch(int B, const int64_t* idisk, const int32_t* N) {
+  int64_t mmax = 0;
+  int nmax = 0;
+  for (int b = 0; b < B; ++b) mmax = std::max(mmax, idisk[b + 1] - idisk[b]);
+  for (int64_t p = 0; p < idisk[B]; ++p) nmax = std::max(nmax, (int)N[p]);
+  if (nmax > PAIRS_NMAX || !(mmax >= 24 || (mmax > FEW_DISKS && idisk[B] >= 2048))) return false;
+  double passes = 0.0, wgs = 0.0, macs = 0.0, macs_span = 0.0, instr = 0.0, tasks = 0.0;
+  for (int b = 0; b < B; ++b) {
+    const int64_t d0 = idisk[b], d1 = idisk[b + 1], M = d1 - d0;
+    if (M < 2) continue;
+    double sum = 0.0;
+    int nb = 0;  // largest order of the instance
+    for (int64_t p = d0; p < d1; ++p) {
+      sum += 2 * N[p] + 1;
+      nb = std::max(nb, (int)N[p]);
+    }
+    const double chunks = (double)((M + LANE_CHUNK - 1) / LANE_CHUNK);
+    for (int64_t p = d0; p < d1; ++p) {
+      const int np = 2 * N[p] + 1, cols = lds_cols(np, nmax, 4);
+      const int64_t items = (M - 1 + APPLY_NPASS * cols - 1) / (APPLY_NPASS * cols);
+      passes = std::max(passes, (double)((M - 1 + cols - 1) / cols));
+      wgs += (double)items;
+      macs += np * (sum - np);
+      if (items > 1) macs_span += np * (sum - np);
+      const int blocks = (np + PAIRS_BT_WIDE - 1) / PAIRS_BT_WIDE, w = std::max((np + blocks - 1) / blocks, 7);
+      tasks += chunks * blocks;
+      instr += chunks * blocks * (2 * nb + w) * (4 * w + 12);
+    }
+  }
+  const double n = 2.0 * nmax + 1.0;
+  const double lds = 5.9 + 0.096 * passes * n + (macs_span > 0.0 ? 9.5 : 0.0) + 0.010 * wgs + 0.92e-6 * macs + 0.24e-6 * macs_span;
+  const double pairs = 6.8 + 0.144 * n + 2.33e-6 * instr + 0.00107 * tasks;
+  return PAIRS_MARGIN * pairs < lds;
+}
+
 // Schedule of k_apply_pairs.  Tasks: the rows of an instance by decreasing N, each
 // cut into blocks of equal width, at most PAIRS_BT_WIDE outputs, or
 // PAIRS_BT_NARROW where wide blocks make fewer tasks than the 3,072 waves that
@@ -2135,10 +2192,7 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
   P.ts = P.zs + P.zs - 1;
   P.ppcap = std::max(1, (int)(APPLY_LDS_BUDGET / ((size_t)(P.zs + P.ts) * 16)));
   // column disks per item of a row of np modes
-  auto cols_of = [&](int np) {
-    const int L = (np + bt - 1) / bt;
-    return (int64_t)std::max(1, std::min(APPLY_THREADS / L, P.ppcap)) * APPLY_NPASS;
-  };
+  auto cols_of = [&](int np) { return (int64_t)lds_cols(np, nmax, bt) * APPLY_NPASS; };
   if (pairs && pairs_batch(B, idisk, N)) {
     make_pairs_plan(B, idisk, N, cols_of(1), P);
     P.row_part = 0;

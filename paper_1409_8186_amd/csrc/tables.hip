@@ -183,21 +183,6 @@ __global__ void k_pair_tables(DevView v, int64_t P_all) {
 // ------------------------------------------------------------------ layout
 size_t sched_bytes_for(int B, const int64_t* disk_off, const int32_t* n_modes);
 
-// Batches of k_apply_pairs: every N_p <= PAIRS_NMAX, and enough pairs per wave.
-// A wave fills its 64 lanes with the disks of one instance and pays the same
-// latency however few they are; below 24 disks the LDS-staged kernel, which
-// spreads one pair over many threads, is the faster one (one right-hand side:
-// 8.4 against 23 us at 6 disks, 13.4 against 14.1 at 20, 19.7 against 14.6 at
-// 28), unless the batch has so many rows that throughput counts (300 instances
-// of up to 20 disks: 168 against 120 us; 100 of up to 12: 32 against 38).
-bool pairs_batch(int B, const int64_t* disk_off, const int32_t* n_modes) {
-  int64_t mmax = 0;
-  for (int b = 0; b < B; ++b) mmax = std::max(mmax, disk_off[b + 1] - disk_off[b]);
-  for (int64_t p = 0; p < disk_off[B]; ++p)
-    if (n_modes[p] > PAIRS_NMAX) return false;
-  return mmax >= 24 || (mmax >= 15 && disk_off[B] >= 2048);
-}
-
 // Lane-interleaved pair records of a batch with one N for all disks (1 <= N <=
 // LANE_NMAX: the columns of a row are the other disks in order) or any orders
 // up to PAIRS_NMAX (the columns are all disks by decreasing N).

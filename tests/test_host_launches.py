@@ -30,3 +30,43 @@ def test_farfield_grid_within_the_launch_limit(host, M, R, n_theta):
     (name, (gx, gy, _), threads, _, _), = host.launches
     assert gx * threads < GRID_THREADS and gy <= 65535, (name, gx, threads)
     host.check(host.lib.mudiff_destroy(h))
+
+
+def batch(sizes, lo, hi):
+    """Instances of the given numbers of disks, on grids, with orders lo..hi in turn."""
+    out = []
+    for M in sizes:
+        w = int(np.ceil(np.sqrt(M)))
+        c = np.array([(i % w, i // w) for i in range(M)], float) * 4.0
+        out.append((c, np.ones(M), lo + np.arange(M) * 7 % (hi - lo + 1), 5.0))
+    return out
+
+
+SMALL, TINY = [5 + i % 8 for i in range(1000)], [2 + i % 3 for i in range(300)]
+
+
+@pytest.mark.parametrize("sizes,orders,kernel", [
+    # a large instance among small ones: by what the whole batch takes (us, LDS-staged and one lane
+    # per pair, below)
+    (SMALL[:100] + [24], (13, 20), "k_apply"),         # 24.5, 31.7
+    (SMALL + [24], (13, 20), "k_apply"),               # 188, 235
+    (SMALL + [24] * 5, (24, 31), "k_apply"),           # 307, 483
+    (TINY + [24], (24, 31), "k_apply"),                # 38.9, 84
+    (TINY + [24] * 5, (13, 20), "k_apply"),            # 26.9, 37.8
+    (SMALL[:100] + [200], (13, 20), "k_apply_pairs"),  # 143, 52
+    (SMALL + [24], (1, 4), "k_apply_pairs"),           # 97, 33
+    # one size
+    ([26], (1, 4), "k_apply"),                         # 7.9, 9.4
+    ([28], (13, 20), "k_apply_pairs"),                 # 19.7, 14.6
+    ([64] * 8, (13, 20), "k_apply_pairs"),             # 148, 27
+    ([400], (13, 20), "k_apply_pairs"),
+    ([40], (24, 31), "k_apply_pairs"),                 # 41, 20
+    ([40], (24, 32), "k_apply"),                       # orders beyond the kernel's
+])
+def test_kernel_of_mixed_orders(host, sizes, orders, kernel):
+    h = host.tables(batch(sizes, *orders))
+    size = host.lib.mudiff_matvec_workspace_size(h, 1)
+    host.launches.clear()
+    host.check(host.lib.mudiff_matvec(h, 1, 256, 512, 1, 1024, size, None))
+    assert kernel + "IL" in host.launches[0][0], host.launches[0][0]
+    host.check(host.lib.mudiff_destroy(h))
