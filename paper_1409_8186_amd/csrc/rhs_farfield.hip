@@ -309,9 +309,20 @@ extern "C" int mudiff_farfield(mudiff_t h, int R, const void* rho, int n_theta, 
   // does less in all; on instances of 64 disks and more it also ends earlier while
   // its workgroups (column, 16 angles) fit the chip about twice: 1,000 disks, 60
   // angles, 8 columns (32 workgroups) 158 against 389 us, 30 columns (120) 230
-  // against 391, 256 columns at 360 angles (5,888) 4,810 against 760; 60 disks, 17
-  // columns at 361 angles 38 against 29, 8 disks, 100 columns 26 against 10.
-  const bool many = R >= 4 && (mmax < 64 || (int64_t)h->B * R * ntt >= 512);
+  // against 391, 256 columns at 360 angles (5,888) 4,810 against 760.
+  bool many = R >= 4 && (mmax < 64 || (int64_t)h->B * R * ntt >= 512);
+  // Instances of 5 to 63 disks with orders up to 8: a k step of 4 modes fills badly, so that
+  // launches that fill the chip several times over need 5 or 6 columns (64 x 12 disks of order 2
+  // at 360 angles: 4 columns 23.5 against 30.0 us, 5 columns 28, 28, 6 columns 34, 30; of order
+  // 12 4 columns 44.8, 44.1; 64 x 20 of order 8 at 3,600 4 columns 1.03, of order 4 1.20 times
+  // as long), and a launch of one round ends earlier on the other kernel from some 40 disks
+  // and up to order 4 (50 of order 2 10.9 against 12.4; of order 5 0.96 times as long; 30 of
+  // order 2 10.2, 9.4; in more rounds 0.4 to 0.7).
+  if (many && mmax > 4 && mmax < 64 && h->Nmax <= 8) {
+    const int64_t wgs = (int64_t)h->B * R * ((n_theta + 63) / 64);  // of the other kernel
+    if (wgs >= 4 * (int64_t)h->n_cu) many = R >= (h->Nmax <= 2 ? 6 : 5);
+    else if (wgs <= h->n_cu) many = mmax < 40 || h->Nmax > 4;
+  }
   const int nw = mmax > 4 ? 16 : 4;
   // (a launch has fewer than 2^32 threads along x; the other kernel has its columns along y)
   if (many && h->Nmax <= FF_MFMA_N && nct * ntt * 64 * nw < ((int64_t)1 << 32)) {

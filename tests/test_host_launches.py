@@ -32,6 +32,24 @@ def test_farfield_grid_within_the_launch_limit(host, M, R, n_theta):
     host.check(host.lib.mudiff_destroy(h))
 
 
+@pytest.mark.parametrize("B,M,N,n_theta,R,mfma", [
+    # (us of the other kernel and of the matrix-core kernel)
+    (64, 12, 2, 3600, 4, False), (64, 12, 2, 360, 4, False),  # 207, 265; 23.5, 30.0
+    (64, 12, 2, 360, 6, True), (64, 12, 12, 360, 4, True),    # 34, 30; 44.8, 44.1
+    (500, 6, 2, 3600, 4, False), (64, 3, 0, 3600, 4, True),   # 1327, 1690
+    (1, 50, 2, 360, 16, False), (1, 63, 0, 36, 4, False),     # 10.9, 12.7
+    (1, 50, 2, 3600, 5, True), (1, 50, 12, 360, 4, True),     # 24.6, 21.6
+    (1, 16, 2, 1, 4, True), (1, 30, 2, 36, 4, True), (1, 8, 12, 36, 3, False),
+    (1, 300, 5, 36, 8, False), (1, 100, 2, 3600, 8, True),
+])
+def test_farfield_kernel_of_few_columns(host, B, M, N, n_theta, R, mfma):
+    h = host.tables([line(M, N)] * B)
+    host.launches.clear()
+    host.check(host.lib.mudiff_farfield(h, R, 256, n_theta, 256, 256, None))
+    assert ("k_farfield_mfma" in host.launches[0][0]) == mfma
+    host.check(host.lib.mudiff_destroy(h))
+
+
 def batch(sizes, lo, hi):
     """Instances of the given numbers of disks, on grids, with orders lo..hi in turn."""
     out = []
