@@ -160,12 +160,15 @@ struct MatvecPlan {
   size_t lds_bytes = 0;
   int64_t part_total = 0;       // complex partials per right-hand side
   int64_t row_part = 0;         // the same for the LDS-staged kernel's chunks
-  int few = 0;                  // > 0: k_apply_few, ints per task in d_items
+  int few = 0;                  // > 0: tasks of k_apply_few, ints per task
+  int n_few = 0;
+  double few_us = 0.0, lane_us = 0.0;  // estimates per right-hand side (few_applies)
   int lane_rows = LANE_ROWS;    // LANE_UNIFORM: row disks per workgroup
   int few_cols = 0, few_z = 0;  // its LDS: column disks per wave, entries of an input panel
   int32_t* d_items = nullptr;   // [n_items][4] : p, chunk, q_begin, q_end (generic);
                                 // [n_items][LANE_ITEM_INTS] (LANE_UNIFORM),
                                 // [n_items][PAIRS_ITEM_INTS] (LANE_PAIRS)
+  int32_t* d_few = nullptr;     // [n_few][few]
   int32_t* d_tasks = nullptr;   // LANE_PAIRS: [.][2] row disk, first output << 8 | outputs
   int32_t* d_nchunk = nullptr;  // [M_all]
   int64_t* d_partoff = nullptr; // [M_all]

@@ -1968,9 +1968,10 @@ struct PlanHost {
   int bt = 4, nspec = -1, zs = 0, ts = 0, ppcap = 1;
   size_t lds = 0;
   int64_t part = 0;
-  int few = 0, few_cols = 0, few_z = 0, lane_rows = LANE_ROWS;
+  int few = 0, few_cols = 0, few_z = 0, lane_rows = LANE_ROWS;  // few: ints per task
   int64_t row_part = 0;  // partial sums of the LDS-staged kernel (bounds mudiff_matvec_noalloc)
-  std::vector<int32_t> items, nch, tasks;
+  double few_us = 0.0, lane_us = 0.0;
+  std::vector<int32_t> items, nch, tasks, few_tasks;
   std::vector<int64_t> poff;
 };
 
@@ -2152,6 +2153,7 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
     for (int b = 0; b < B; ++b)
       waves += (idisk[b + 1] - idisk[b]) * ((idisk[b + 1] - idisk[b] - 1 + LANE_CHUNK - 1) / LANE_CHUNK);
     P.lane_rows = waves < LANE_FEW_WAVES ? 1 : LANE_ROWS;
+    P.lane_us = (double)waves * (0.085e-3 + 10.6e-6 * np * np);
     int64_t i0 = 0;  // first unknown of instance b
     for (int b = 0; b < B; ++b) {
       const int64_t d0 = idisk[b], Mb = idisk[b + 1] - d0;
@@ -2230,13 +2232,12 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
   }
 }
 
-// Tasks of k_apply_few in place of the plan's items, for batches of small instances
-// whose panels fit its LDS.  The rest of the plan stays: the scratch it asks for is what
-// the entry points check.  us per apply, the kernels before and this one: mixed orders of
-// about 33 modes, 10 disks, one column 9.7, 8.7 (the host's part); 256 x 10 61, 29; 64 x 16, 4
-// columns 110, 65; 1,000 x 10, 7 columns 1,446, 643.  Uniform orders (25 modes), where one
-// lane per pair is the other way: 2 disks 11.9, 8.6; 1,000 x 4 44, 11.5; 256 x 8, 4 columns
-// 72, 34; 256 x 12 80, 71, but 256 x 14 93, 98, 256 x 16 105, 117; 64 x 16 31, 29.
+// Tasks of k_apply_few, for batches of small instances whose panels fit its LDS: in place
+// of the plan's items, but for uniform orders, where few_applies chooses for the number of
+// right-hand sides.  The rest of the plan stays: the scratch it asks for is what the entry
+// points check.  us per apply, the kernels before and this one: mixed orders of about 33
+// modes, 10 disks, one column 9.7, 8.7 (the host's part); 256 x 10 61, 29; 64 x 16, 4 columns
+// 110, 65; 1,000 x 10, 7 columns 1,446, 643.
 #define FEW_LDS (64 * 1024)
 
 static size_t few_lds(int cols, int zcap) { return (size_t)FEW_WAVES * cols * (2 * zcap + FEW_PAD) * 16; }
@@ -2252,7 +2253,7 @@ static void make_few(int B, const int64_t* idisk, const int32_t* N, PlanHost& P)
   P.few = FEW_HDR + FEW_COL * (int)(mmax - 1);
   P.few_cols = cols;
   P.few_z = zcap;
-  P.items.clear();
+  if (P.lane != LANE_UNIFORM) P.items.clear();
   int64_t i0 = 0, t0 = 0;  // first unknown and symbol of the instance
   for (int b = 0; b < B; ++b) {
     const int64_t d0 = idisk[b];
@@ -2268,9 +2269,10 @@ static void make_few(int B, const int64_t* idisk, const int32_t* N, PlanHost& P)
     }
     for (int p = 0; p < M; ++p)
       for (int m0 = 0; m0 <= 2 * N[d0 + p]; m0 += 32) {
-        const size_t w = P.items.size();
-        P.items.resize(w + P.few, 0);
-        int32_t* it = P.items.data() + w;
+        P.few_us += 0.55e-3 + 0.12e-3 * M + 7.9e-6 * (double)off[M];
+        const size_t w = P.few_tasks.size();
+        P.few_tasks.resize(w + P.few, 0);
+        int32_t* it = P.few_tasks.data() + w;
         auto put64 = [&](int k, int64_t x) {
           it[k] = (int32_t)(x & 0xffffffff);
           it[k + 1] = (int32_t)(x >> 32);
@@ -2296,9 +2298,27 @@ static void make_few(int B, const int64_t* idisk, const int32_t* N, PlanHost& P)
   }
 }
 
+// Whether applies of R right-hand sides run on k_apply_few.  For uniform orders one lane per
+// pair is the other way, by far the faster one where the launch is many tasks of few modes:
+// a wave then is a row with all its columns and k_apply_few a workgroup of 256 threads.  Both
+// by estimates (us of whole applies, fitted to 1,300 batches of 1 to 3,000 instances within
+// 13% and 8% in the mean; per row and right-hand side 0.55 + 0.12 M + 0.0079 M n, and 0.085 +
+// 0.0106 n^2 ns, n modes): 4 disks of 31 modes 8.4 with one lane per pair, 6.5 with k_apply_few;
+// of 25 modes 2 disks 11.9, 8.6, 1,000 x 4 44, 11.5, 256 x 12 80, 71; of 3 modes 40 x 12 10.9,
+// 5.4, 1,000 x 12 12.1, 49, with 7 columns 32.7, 325; of 7 modes 1,000 x 10, 4 columns 40.8, 163.
+// split: the sums are added by the kernel that follows, so that one lane per pair is one
+// launch as well.
+#define FEW_MARGIN 1.15
+static bool few_applies(const mudiff_ctx* h, int R, bool split) {
+  const MatvecPlan& P = h->plan;
+  if (!P.few || P.lane != LANE_UNIFORM) return P.few > 0;
+  const double few = R * P.few_us, lane = R * P.lane_us;
+  return FEW_MARGIN * few < lane + 4.0 || (!split && FEW_MARGIN * (few + 4.9) < lane + 10.9);
+}
+
 size_t plan_sched_bytes(const PlanHost& P, int M) {
   return align256(P.items.size() * 4) + align256((size_t)M * 4) + align256((size_t)M * 8) +
-         align256(P.tasks.size() * 4) + 256;
+         align256(P.tasks.size() * 4) + align256(P.few_tasks.size() * 4) + 256;
 }
 
 size_t sched_bytes_for(int B, const int64_t* disk_off, const int32_t* n_modes) {
@@ -2326,8 +2346,9 @@ int ensure_plan(mudiff_ctx* h, hipStream_t s) {
   P.d_nchunk = (int32_t*)(h->sched_base + align256(H.items.size() * 4));
   P.d_partoff = (int64_t*)((char*)P.d_nchunk + align256(h->M_all * 4));
   P.d_tasks = (int32_t*)((char*)P.d_partoff + align256((size_t)h->M_all * 8));
-  // one copy of all four (a copy from pageable memory takes the host some 5 us)
-  std::vector<char> blob((char*)P.d_tasks - h->sched_base + H.tasks.size() * 4);
+  P.d_few = (int32_t*)((char*)P.d_tasks + align256(H.tasks.size() * 4));
+  // one copy of all five (a copy from pageable memory takes the host some 5 us)
+  std::vector<char> blob((char*)P.d_few - h->sched_base + H.few_tasks.size() * 4);
   auto put = [&](const void* d, const void* src, size_t n) {
     if (n) memcpy(blob.data() + ((const char*)d - h->sched_base), src, n);
   };
@@ -2335,6 +2356,7 @@ int ensure_plan(mudiff_ctx* h, hipStream_t s) {
   put(P.d_nchunk, H.nch.data(), (size_t)h->M_all * 4);
   put(P.d_partoff, H.poff.data(), (size_t)h->M_all * 8);
   put(P.d_tasks, H.tasks.data(), H.tasks.size() * 4);
+  put(P.d_few, H.few_tasks.data(), H.few_tasks.size() * 4);
   HIP_TRY(hipMemcpyAsync(h->sched_base, blob.data(), blob.size(), hipMemcpyHostToDevice, s));
   HIP_TRY(hipStreamSynchronize(s));  // the host vectors are released on return
   P.lane = H.lane;
@@ -2351,7 +2373,10 @@ int ensure_plan(mudiff_ctx* h, hipStream_t s) {
   P.lane_rows = H.lane_rows;
   P.few_cols = H.few_cols;
   P.few_z = H.few_z;
-  P.n_items = (int)(H.items.size() / (H.few ? H.few : H.item_ints));
+  P.few_us = H.few_us;
+  P.lane_us = H.lane_us;
+  P.n_few = H.few ? (int)(H.few_tasks.size() / H.few) : 0;
+  P.n_items = (int)(H.items.size() / H.item_ints);
   P.ready = true;
   return MUDIFF_OK;
 }
@@ -2406,7 +2431,7 @@ int apply_operator_split(mudiff_ctx* h, int R, const cplx* x, cplx* y, int op, c
   int st = ensure_plan(h, s);
   if (st != MUDIFF_OK) return st;
   const MatvecPlan& P = h->plan;
-  if (P.lane && !P.few) {
+  if (P.lane && !few_applies(h, R, true)) {
     if ((st = launch_lanes(h, R, x, part, active, s)) != MUDIFF_OK) return st;
     *pending = true;  // the chunk sums still have to be added and finalised
     return MUDIFF_OK;
@@ -2428,14 +2453,14 @@ int apply_operator(mudiff_ctx* h, int R, const cplx* x, cplx* y, int op, cplx* p
   prof_mark(h, s, 1);
   prof_mark(h, s, 2);
   prof_mark(h, s, 3);
-  if (P.few) {
+  if (few_applies(h, R, false)) {
     const DevView& v = h->dv;
     FewView fv{v.t, v.op_col, nullptr, v.invSH, v.sJ, op == OP_RAW_W};
     if (v.op_rowA) fv.be = op == MUDIFF_OP_A ? v.op_rowA : v.op_row;
     else if (op != MUDIFF_OP_A) fv.be = nullptr;
     if (op != MUDIFF_OP_A) fv.al = v.op_rowA ? v.op_diag : v.Ldiag;
-    hipLaunchKernelGGL(k_apply_few, dim3(P.n_items, R), dim3(FEW_THREADS), few_lds(P.few_cols, P.few_z), s, fv, R,
-                       x, y, P.d_items, P.few, active, shift, P.few_cols, P.few_z);
+    hipLaunchKernelGGL(k_apply_few, dim3(P.n_few, R), dim3(FEW_THREADS), few_lds(P.few_cols, P.few_z), s, fv, R,
+                       x, y, P.d_few, P.few, active, shift, P.few_cols, P.few_z);
     HIP_TRY(hipGetLastError());
     prof_mark(h, s, 4);
     prof_mark(h, s, 5);

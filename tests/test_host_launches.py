@@ -88,3 +88,25 @@ def test_kernel_of_mixed_orders(host, sizes, orders, kernel):
     host.check(host.lib.mudiff_matvec(h, 1, 256, 512, 1, 1024, size, None))
     assert kernel + "IL" in host.launches[0][0], host.launches[0][0]
     host.check(host.lib.mudiff_destroy(h))
+
+
+def uniform(B, M, N):
+    return batch([M] * B, N, N)
+
+
+@pytest.mark.parametrize("B,M,N,R,few", [
+    # (us of one lane per pair and of whole rows per workgroup)
+    (1, 4, 12, 1, True), (1000, 4, 12, 1, True), (256, 12, 12, 1, True),  # 44, 11.5; 80, 71
+    (40, 12, 1, 1, True), (300, 3, 5, 7, True), (1000, 8, 9, 4, True),
+    (1000, 12, 1, 1, False), (1000, 12, 1, 7, False),                     # 12.1, 49; 32.7, 325
+    (300, 10, 3, 4, False), (1000, 10, 7, 4, False),                      # 17, 34; 99, 138
+    (3000, 4, 1, 7, False), (300, 16, 1, 1, False),
+])
+def test_kernel_of_uniform_orders(host, B, M, N, R, few):
+    h = host.tables(uniform(B, M, N))
+    size = host.lib.mudiff_matvec_workspace_size(h, R)
+    host.launches.clear()
+    host.check(host.lib.mudiff_matvec(h, R, 256, 512, 1, 1024, size, None))
+    names = [n for n, *_ in host.launches]
+    assert ("k_apply_few" in names[0]) == few and len(names) == (1 if few else 2), names
+    host.check(host.lib.mudiff_destroy(h))
