@@ -450,6 +450,9 @@ int apply_operator_split(mudiff_ctx* h, int R, const cplx* x, cplx* y, int op, c
                          int32_t* counters, const int32_t* active, hipStream_t s,
                          bool* pending);
 size_t apply_scratch_bytes(mudiff_ctx* h, int R);
+// Estimated us of an apply of a batch of small instances inside a solve, beyond the launch
+// (the plan is ready).
+double apply_few_us(const mudiff_ctx* h, int R);
 // Forget MFMA schedules uploaded into an apply scratch: the next apply uploads
 // them into its scratch again.  Every entry point that takes an apply scratch from
 // the caller calls this first, so a buffer whose memory was used for anything

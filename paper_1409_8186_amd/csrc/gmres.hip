@@ -2466,26 +2466,45 @@ static int compact_columns(GmresRun& G, const std::vector<int32_t>& run, int n_r
   return apply_set_tail(G.h, G.s.R, true, G.apply_part, G.st, run.data());
 }
 
-// Whether the cycles of this solve run on k_small_cycle: few columns (from 8 on the
-// apply is on the matrix cores), every instance within a workgroup's threads and LDS.  It
-// was the faster one wherever it fits (whole solves, us, three kernels per step against
-// this one): 4 disks of 31 modes 740, 292; 2 x 25 416, 220; 10 x 25 1,410, 811; 14 x 25
-// 2,495, 2,415; 10 disks of 33 modes (basis in global memory) 1,986, 1,634; 12 of them, 7
-// columns 1,940, 1,905; batches: 256 instances of 4 x 25, 7 columns each, 2,531, 1,028; 64 of
-// 12 mixed disks, 7 columns, 11,677, 5,658.
+// Whether the cycles of this solve run on k_small_cycle: few right-hand sides (from 8 on the
+// apply is on the matrix cores), every instance within a workgroup's threads and LDS, and
+// the faster one by estimates of a step (us; fitted to 2,700 solves of uniform orders, within
+// 5% and 8% in the mean where the two are close).  This kernel: a column per workgroup, so C
+// columns go in rounds of n_cu, and phase A in rounds of tasks over the waves, w = rounds x
+// column disks x (modes / 8 + 2.5):
+//   4.3 + 45 / m + 0.63 M + 0.019 N_b + 0.047 w, and 3.1 + 0.25 M + 0.016 N_b + 0.075 w for
+//   each further round of columns
+// three kernels: 25.0 + 11 / m + 0.08 M + 0.67 (their apply) + 0.21 per 1,000 unknowns.
+// Whole solves, us, three kernels a step against this one: 4 disks of 31 modes 740, 292; 2 x 25
+// 416, 220; 10 disks of 33 modes (basis in global memory) 1,986, 1,634; 256 instances of 4 x 25,
+// 7 columns each, 2,531, 1,028; steps: 12 disks of 25 modes 26.4, 22.4; 16 of 25 28.0, 33.9; 11
+// of 33 29.2, 34.7; 300 x 16 of 3 modes, 7 columns 75, 149, of 25 modes 324, 289.
 static bool small_cycle(const mudiff_ctx* h, const GState& s, SmallGeom* g, bool* vl) {
   if (s.R >= 8) return false;
-  int T = 0, N = 0;
+  int T = 0, N = 0, mmax = 0;
+  double w = 0.0;
   for (int b = 0; b < h->B; ++b) {
-    const int64_t M = h->idisk[b + 1] - h->idisk[b], n = h->imode[b + 1] - h->imode[b];
+    const int64_t d0 = h->idisk[b], M = h->idisk[b + 1] - d0, n = h->imode[b + 1] - h->imode[b];
     if (M > SMALL_DISKS || n > SMALL_THREADS) return false;
     T = std::max(T, (int)(M * (M - 1) / 2 + (M - 1) * (n - M)));
     N = std::max(N, (int)n);
+    mmax = std::max(mmax, (int)M);
+    int tasks = 0, steps = 0;
+    for (int64_t p = d0; p < d0 + M; ++p) {
+      tasks += (2 * h->N[(size_t)p] + 32) / 32;
+      steps += (2 * h->N[(size_t)p] + 8) / 8;
+    }
+    w = std::max(w, (double)((tasks + SMALL_WAVES - 1) / SMALL_WAVES) * (double)(M - 1) * ((double)steps / (double)M + 2.5));
   }
   g->T = T;
   g->N = N;
   *vl = small_lds(T, N, s.m, true) * 16 <= SMALL_LDS;
-  return *vl || small_lds(T, N, s.m, false) * 16 <= SMALL_LDS;
+  if (!*vl && small_lds(T, N, s.m, false) * 16 > SMALL_LDS) return false;
+  const int rounds = (s.C + h->n_cu - 1) / h->n_cu;
+  const double one = 4.3 + 45.0 / s.m + 0.63 * mmax + 0.019 * N + 0.047 * w +
+                     (rounds - 1) * (3.1 + 0.25 * mmax + 0.016 * N + 0.075 * w);
+  const double three = 25.0 + 11.0 / s.m + 0.08 * mmax + 0.67 * apply_few_us(h, s.R) + 0.21e-3 * (double)s.NT;
+  return one < three;
 }
 
 // One restart cycle (Arnoldi steps + solution update + true residual).

@@ -2316,6 +2316,11 @@ static bool few_applies(const mudiff_ctx* h, int R, bool split) {
   return FEW_MARGIN * few < lane + 4.0 || (!split && FEW_MARGIN * (few + 4.9) < lane + 10.9);
 }
 
+double apply_few_us(const mudiff_ctx* h, int R) {
+  if (few_applies(h, R, true)) return R * h->plan.few_us;
+  return h->plan.lane == LANE_UNIFORM ? 3.6 + R * h->plan.lane_us : 10.0;
+}
+
 size_t plan_sched_bytes(const PlanHost& P, int M) {
   return align256(P.items.size() * 4) + align256((size_t)M * 4) + align256((size_t)M * 8) +
          align256(P.tasks.size() * 4) + align256(P.few_tasks.size() * 4) + 256;

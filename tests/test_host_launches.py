@@ -110,3 +110,33 @@ def test_kernel_of_uniform_orders(host, B, M, N, R, few):
     names = [n for n, *_ in host.launches]
     assert ("k_apply_few" in names[0]) == few and len(names) == (1 if few else 2), names
     host.check(host.lib.mudiff_destroy(h))
+
+
+@pytest.mark.parametrize("instances,R,restart,small", [
+    # (us of a step as three kernels and in one workgroup)
+    (uniform(1, 4, 15), 1, 30, True), (uniform(1, 12, 12), 1, 30, True),          # 22.8, 19.4
+    (uniform(10, 8, 15), 4, 40, True), (batch([12] * 64, 5, 18), 7, 30, True),
+    (uniform(300, 12, 12), 7, 20, True), (uniform(256, 4, 12), 7, 30, True),
+    (uniform(1, 16, 12), 1, 10, False), (uniform(1, 16, 15), 4, 10, False),       # 16.5, 21.4
+    (batch([16] * 10, 5, 18), 1, 10, False), (uniform(1, 11, 16), 1, 10, False),  # 14.2, 18.1; 24.8, 29.6
+    (uniform(300, 16, 1), 7, 20, False), (uniform(300, 13, 3), 7, 20, False),     # 75, 149; 93, 125
+    (uniform(64, 16, 1), 7, 20, False),                                           # 29, 41
+])
+def test_cycles_of_small_columns(host, instances, R, restart, small):
+    """The kernels of a solve's first cycle; its state reads as running until one of them is launched,
+    then as ended."""
+    h = host.tables(instances)
+    B = len(instances)
+    size = host.lib.mudiff_gmres_workspace_size(h, R, restart, 0)
+    ws, out = host.array(size), host.array(B * R * 16 + 4096)
+    ws.data[:] = 1
+    ended = lambda read, blocks: ws.data.fill(0)  # noqa: E731
+    host.hooks = {"k_small_cycle": ended, "k_dg_dots": ended}
+    host.launches.clear()
+    host.check(host.lib.mudiff_gmres(h, R, 256, None, 512, restart, 1e-8, 1000, 0, ws.base, size, out.base, out.base,
+                                     out.base, None, None))
+    host.hooks = {}
+    names = {n for n, *_ in host.launches}
+    assert any("k_small_cycle" in n for n in names) == small, names
+    assert any("k_dg_update" in n for n in names) != small, names
+    host.check(host.lib.mudiff_destroy(h))
