@@ -1836,6 +1836,22 @@ static int mfma_autotune(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scr
     time_one(c);
     if (rc != MUDIFF_OK) break;
   }
+  if (rc == MUDIFF_OK && !bc.circ) {
+    // then whole instances and segments of 32 with the fastest tile: the rule counts items, but
+    // short segments of small instances or many row tiles cost more in partial sums than the
+    // evener end saves (us of an apply by rule, and by these: 64 x 12 disks of order 3, 20
+    // columns 46, 38; 200 of order 31, 20 columns 746, 680; 300 x 6 of orders 5..18, 12 columns
+    // 90, 81; 200 of orders 5..18, 20 columns 268, 223)
+    MfmaChoice c = bc;
+    int64_t mmax = 0;
+    for (int b = 0; b < h->B; ++b) mmax = std::max(mmax, h->idisk[b + 1] - h->idisk[b]);
+    const int rule = segment(h, R, bc);
+    for (int qs : {0, 32}) {
+      if (qs == rule || qs >= mmax || rc != MUDIFF_OK) continue;
+      c.QS = qs;
+      time_one(c);
+    }
+  }
   if (rc == MUDIFF_OK && bc.circ) {  // then the other per-frequency product variants
     MfmaChoice c = bc;
     for (size_t k = 1; k < cvars.size() && rc == MUDIFF_OK; ++k) {

@@ -39,7 +39,7 @@ class Applies:
 
     def __init__(self, host, h, R):
         self.host, self.h, self.R = host, h, R
-        n = (ctypes.c_int64 * 2)()
+        n = (ctypes.c_int64 * 512)()  # unknowns of every instance
         host.check(host.lib.mudiff_sizes(h, n))
         self.x = host.array(16 * R * sum(n))
         self.y = host.array(16 * R * sum(n))
@@ -171,7 +171,7 @@ def test_timed_configuration_can_be_fixed(host, instances):
     """What apply_config reports of a timed apply is taken by set_apply_config, here and on another
     handle of the same batch, and reported again; other lengths are refused."""
     for R in (8, 11, 16, 24, 33, 64):
-        for win in range(6):
+        for win in range(10):
             pick(host, win)
             h = host.tables(instances, circulant=True)
             Applies(host, h, R).run()
@@ -189,3 +189,23 @@ def test_timed_configuration_can_be_fixed(host, instances):
                 assert host.lib.mudiff_set_apply_config(h, R, *found[1:3], qs, found[4]) == 1
             assert a.config() == found
             host.check(host.lib.mudiff_destroy(h))
+
+
+@pytest.mark.parametrize("instances,R,timed", [
+    ([grid(12, 2.1, ORDERS)] * 8, 20, {0, 4}), ([grid(200, 2.1, [31])], 20, {0, 8, 16, 32}),
+    ([grid(6, 2.1, ORDERS)] * 300, 12, {0}), ([grid(20, 2.1, ORDERS)] * 64, 20, {0, 4}),
+], ids=["8x12", "200", "300x6", "64x20"])
+def test_segments_that_are_timed(host, instances, R, timed):
+    """The direct form's segment lengths that first use tries: the rule's, and whole instances and 32
+    with the tile that is fastest by rule."""
+    h = host.tables(instances)
+    seen = set()
+    for win in range(12):
+        pick(host, win)
+        h2 = host.tables(instances)
+        a = Applies(host, h2, R)
+        a.run()
+        seen.add(a.config()[3])
+        host.check(host.lib.mudiff_destroy(h2))
+    assert seen == timed
+    host.check(host.lib.mudiff_destroy(h))
