@@ -193,7 +193,7 @@ def test_timed_configuration_can_be_fixed(host, instances):
 
 @pytest.mark.parametrize("instances,R,timed", [
     ([grid(12, 2.1, ORDERS)] * 8, 20, {0, 4}), ([grid(200, 2.1, [31])], 20, {0, 8, 16, 32}),
-    ([grid(6, 2.1, ORDERS)] * 300, 12, {0}), ([grid(20, 2.1, ORDERS)] * 64, 20, {0, 4}),
+    ([grid(6, 2.1, ORDERS)] * 300, 12, {0, 4}), ([grid(20, 2.1, ORDERS)] * 64, 20, {0, 16}),
 ], ids=["8x12", "200", "300x6", "64x20"])
 def test_segments_that_are_timed(host, instances, R, timed):
     """The direct form's segment lengths that first use tries: the rule's, and whole instances and 32
