@@ -125,6 +125,7 @@ struct DevView {
 #define LANE_ITEM_INTS 18
 #define LANE_ROWS 4   // row disks per workgroup of k_apply_lane
 #define LANE_FEW_WAVES 400
+#define LANE_ROWS_NMIN 9  // smallest order that takes them
 #define LANE_MIN 12   // lanes of a wave that work at least
 #define LANE_NMAX 12
 // Largest order of the one-lane-per-pair kernel for any orders: its input panel
@@ -163,7 +164,7 @@ struct MatvecPlan {
   int few = 0;                  // > 0: tasks of k_apply_few, ints per task
   int n_few = 0;
   double few_us = 0.0, lane_us = 0.0;  // estimates per right-hand side (few_applies)
-  int lane_rows = LANE_ROWS;    // LANE_UNIFORM: row disks per workgroup
+  int lane_rows = 1;            // LANE_UNIFORM: row disks per workgroup
   int few_cols = 0, few_z = 0;  // its LDS: column disks per wave, entries of an input panel
   int32_t* d_items = nullptr;   // [n_items][4] : p, chunk, q_begin, q_end (generic);
                                 // [n_items][LANE_ITEM_INTS] (LANE_UNIFORM),

@@ -1952,21 +1952,17 @@ struct LaneVariant {
   lane_fn fn_op[2];  // column factors of an operator set by mudiff_set_operator
 };
 
-// one-lane-per-pair kernels (uniform N)
-const LaneVariant kLane[] = {
-    {1, {k_apply_lane<1, false>, k_apply_lane<1, false, 1>}, {k_apply_lane<1, true>, k_apply_lane<1, true, 1>}},
-    {2, {k_apply_lane<2, false>, k_apply_lane<2, false, 1>}, {k_apply_lane<2, true>, k_apply_lane<2, true, 1>}},
-    {3, {k_apply_lane<3, false>, k_apply_lane<3, false, 1>}, {k_apply_lane<3, true>, k_apply_lane<3, true, 1>}},
-    {4, {k_apply_lane<4, false>, k_apply_lane<4, false, 1>}, {k_apply_lane<4, true>, k_apply_lane<4, true, 1>}},
-    {5, {k_apply_lane<5, false>, k_apply_lane<5, false, 1>}, {k_apply_lane<5, true>, k_apply_lane<5, true, 1>}},
-    {6, {k_apply_lane<6, false>, k_apply_lane<6, false, 1>}, {k_apply_lane<6, true>, k_apply_lane<6, true, 1>}},
-    {7, {k_apply_lane<7, false>, k_apply_lane<7, false, 1>}, {k_apply_lane<7, true>, k_apply_lane<7, true, 1>}},
-    {8, {k_apply_lane<8, false>, k_apply_lane<8, false, 1>}, {k_apply_lane<8, true>, k_apply_lane<8, true, 1>}},
-    {9, {k_apply_lane<9, false>, k_apply_lane<9, false, 1>}, {k_apply_lane<9, true>, k_apply_lane<9, true, 1>}},
-    {10, {k_apply_lane<10, false>, k_apply_lane<10, false, 1>}, {k_apply_lane<10, true>, k_apply_lane<10, true, 1>}},
-    {11, {k_apply_lane<11, false>, k_apply_lane<11, false, 1>}, {k_apply_lane<11, true>, k_apply_lane<11, true, 1>}},
-    {12, {k_apply_lane<12, false>, k_apply_lane<12, false, 1>}, {k_apply_lane<12, true>, k_apply_lane<12, true, 1>}},
-};
+// one-lane-per-pair kernels (uniform N); LANE_ROWS rows from order LANE_ROWS_NMIN on
+template <int N>
+constexpr LaneVariant lane_variant() {
+  if constexpr (N >= LANE_ROWS_NMIN)
+    return {N, {k_apply_lane<N, false>, k_apply_lane<N, false, 1>}, {k_apply_lane<N, true>, k_apply_lane<N, true, 1>}};
+  else
+    return {N, {nullptr, k_apply_lane<N, false, 1>}, {nullptr, k_apply_lane<N, true, 1>}};
+}
+const LaneVariant kLane[] = {lane_variant<1>(), lane_variant<2>(),  lane_variant<3>(),  lane_variant<4>(),
+                             lane_variant<5>(), lane_variant<6>(),  lane_variant<7>(),  lane_variant<8>(),
+                             lane_variant<9>(), lane_variant<10>(), lane_variant<11>(), lane_variant<12>()};
 
 const LaneVariant* find_lane(int n) {
   for (const LaneVariant& v : kLane)
@@ -1984,7 +1980,7 @@ struct PlanHost {
   int bt = 4, nspec = -1, zs = 0, ts = 0, ppcap = 1;
   size_t lds = 0;
   int64_t part = 0;
-  int few = 0, few_cols = 0, few_z = 0, lane_rows = LANE_ROWS;  // few: ints per task
+  int few = 0, few_cols = 0, few_z = 0, lane_rows = 1;  // few: ints per task
   int64_t row_part = 0;  // partial sums of the LDS-staged kernel (bounds mudiff_matvec_noalloc)
   double few_us = 0.0, lane_us = 0.0;
   std::vector<int32_t> items, nch, tasks, few_tasks;
@@ -2165,10 +2161,18 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
       P.items.push_back((int32_t)(v & 0xffffffff));
       P.items.push_back((int32_t)(v >> 32));
     };
-    int64_t waves = 0;
-    for (int b = 0; b < B; ++b)
-      waves += (idisk[b + 1] - idisk[b]) * ((idisk[b + 1] - idisk[b] - 1 + LANE_CHUNK - 1) / LANE_CHUNK);
-    P.lane_rows = waves < LANE_FEW_WAVES ? 1 : LANE_ROWS;
+    // Four rows of a workgroup share the scaled inputs of their chunk (k_apply_lane) where the
+    // inputs are many and the waves that a last group of an instance leaves idle are few.  Time
+    // with four rows over that with one, launches of 6,000 waves and more: order 9 0.92 to
+    // 0.97, 12 0.93 to 1.00, but 1.00 to 1.05 for orders 8 and less (7: 1.01 to 1.12); in
+    // instances of 13 disks (16 waves for 13) 1.17, of 17 1.10, of 22 1.06, of 50 1.00.
+    int64_t waves = 0, padded = 0;
+    for (int b = 0; b < B; ++b) {
+      const int64_t Mb = idisk[b + 1] - idisk[b], n = (Mb - 1 + LANE_CHUNK - 1) / LANE_CHUNK;
+      waves += Mb * n;
+      padded += (Mb + LANE_ROWS - 1) / LANE_ROWS * LANE_ROWS * n;
+    }
+    P.lane_rows = N[0] >= LANE_ROWS_NMIN && waves >= LANE_FEW_WAVES && 20 * padded <= 21 * waves ? LANE_ROWS : 1;
     P.lane_us = (double)waves * (0.085e-3 + 10.6e-6 * np * np);
     int64_t i0 = 0;  // first unknown of instance b
     for (int b = 0; b < B; ++b) {

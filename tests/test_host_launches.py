@@ -140,3 +140,20 @@ def test_cycles_of_small_columns(host, instances, R, restart, small):
     assert any("k_small_cycle" in n for n in names) == small, names
     assert any("k_dg_update" in n for n in names) != small, names
     host.check(host.lib.mudiff_destroy(h))
+
+
+@pytest.mark.parametrize("B,M,N,rows", [
+    # (four rows per workgroup over one, in time)
+    (1, 400, 12, 4), (1, 700, 9, 4), (100, 64, 10, 4),    # 0.91 to 0.96
+    (1, 400, 8, 1), (1, 700, 7, 1), (1, 300, 1, 1),       # 1.00 to 1.3
+    (300, 17, 12, 1), (300, 22, 9, 1), (100, 13, 11, 1),  # 1.15, 1.09, 1.2: groups of 1 to 3 rows
+    (300, 20, 12, 4), (1, 100, 12, 1),                    # 200 waves
+])
+def test_rows_per_workgroup(host, B, M, N, rows):
+    h = host.tables(uniform(B, M, N))
+    size = host.lib.mudiff_matvec_workspace_size(h, 7)
+    host.launches.clear()
+    host.check(host.lib.mudiff_matvec(h, 7, 256, 512, 1, 1024, size, None))
+    (name, _, threads, _, _), *_ = host.launches
+    assert "k_apply_lane" in name and threads == 64 * rows, (name, threads)
+    host.check(host.lib.mudiff_destroy(h))
