@@ -323,7 +323,7 @@ __global__ __launch_bounds__(FEW_THREADS) void k_apply_few(
 // whose lanes load their inputs themselves: the hop through LDS would only lengthen the
 // chain (solves, ms: 50 disks 9.6, 10.0; 100 disks 16.5, 16.7; 150 disks, 450 waves, 29.2, 29.1).
 template <int N, bool OPC, int ROWS = LANE_ROWS>
-__global__ __launch_bounds__(64 * ROWS, 2) void k_apply_lane(
+__global__ __launch_bounds__(64 * ROWS, ROWS > 1 ? 2 : 1) void k_apply_lane(
     DevView v, int R, const cplx* __restrict__ x, cplx* __restrict__ part, int64_t part_total,
     const int32_t* __restrict__ items, const int32_t* __restrict__ active) {
   constexpr int n = 2 * N + 1, S = 2 * N;
@@ -334,26 +334,55 @@ __global__ __launch_bounds__(64 * ROWS, 2) void k_apply_lane(
   const int32_t* itp = items + (int64_t)LANE_ITEM_INTS * blockIdx.x;
   const int p0 = itp[0], rows = itp[1], jb = itp[2], je = itp[3], b = itp[4];
   if (active && active[b * R + r] == 0) return;
-  const int lane = tid & 63, wv = tid >> 6;
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t d0 = itp[5];
   const int64_t i0 = *reinterpret_cast<const int64_t*>(itp + 6);
   const int64_t cb = (int64_t)R * i0 + (int64_t)r * *reinterpret_cast<const int64_t*>(itp + 8);
   const int p = p0 + wv, j = jb + lane;
-  // at least LANE_MIN lanes work, those past the last column on its record and zeros: waves of
-  // 2 to 8 active lanes run half as fast (200 disks, whose last chunk has 7: 19 us, 11 so)
-  const bool live = wv < rows && lane < (ROWS > 1 ? max(je - jb, LANE_MIN) : je - jb);
-  cplx h0, H, E;
-  double r2 = 0.0;
-  if (live) {
-    // records and partial sums of consecutive rows lie at a fixed distance
-    const cplx* __restrict__ rec = v.lt + *reinterpret_cast<const int64_t*>(itp + 10) +
-                                   wv * *reinterpret_cast<const int64_t*>(itp + 14) + min(lane, je - jb - 1);
-    h0 = rec[0];
-    H = rec[LANE_CHUNK];
-    E = rec[2 * LANE_CHUNK];
-    r2 = rec[3 * LANE_CHUNK].x;
-  }
+  const int64_t recb = *reinterpret_cast<const int64_t*>(itp + 10);
+  const int64_t pb = *reinterpret_cast<const int64_t*>(itp + 12);
+  cplx acc[n];
+  // the sums of a lane's pair: h0, H: H_0, H_1; E: e^{i alpha}; r2: 2 / (k b); z: its inputs
+  auto pair = [&](cplx h0, cplx H, cplx E, double r2, const cplx (&z)[n]) {
+#pragma unroll
+    for (int m = 0; m < n; ++m) cmac(acc[m], h0, z[m]);
+    cplx Hm = h0;
+    cplx P = E;
+#pragma unroll
+    for (int nu = 1; nu <= S; ++nu) {
+      if (nu > 1) {
+        const cplx Hn = csub(cscale(H, (nu - 1) * r2), Hm);  // H_nu from H_{nu-1}, H_{nu-2}
+        Hm = H;
+        H = Hn;
+        P = cmul(P, E);
+      }
+      const cplx tp = cmul(H, P);
+      cplx tm = cmul(H, cconj(P));
+      if (nu & 1) tm = cmk(-tm.x, -tm.y);
+#pragma unroll
+      for (int m = 0; m < n - nu; ++m) cmac(acc[m], tp, z[m + nu]);
+#pragma unroll
+      for (int m = nu; m < n; ++m) cmac(acc[m], tm, z[m - nu]);
+    }
+  };
+  int64_t rowp = 0;  // this row's partial sums after the first row's
   if constexpr (ROWS > 1) {
+    // records and partial sums of consecutive rows lie at a fixed distance, by the chunks of a row
+    const int chunks = (*reinterpret_cast<const int32_t*>(itp + 8) / n - 1 + LANE_CHUNK - 1) / LANE_CHUNK;
+    rowp = (int64_t)wv * chunks * n;
+    // at least LANE_MIN lanes work, those past the last column on its record and zeros: waves of
+    // 2 to 8 active lanes run half as fast (200 disks, whose last chunk has 7: 19 us, 11 so)
+    const bool live = wv < rows && lane < max(je - jb, LANE_MIN);
+    cplx h0, H, E;
+    double r2 = 0.0;
+    if (live) {
+      const cplx* __restrict__ rec =
+          v.lt + recb + (int64_t)wv * chunks * (LANE_CHUNK * LANE_REC) + min(lane, je - jb - 1);
+      h0 = rec[0];
+      H = rec[LANE_CHUNK];
+      E = rec[2 * LANE_CHUNK];
+      r2 = rec[3 * LANE_CHUNK].x;
+    }
     // column disks jb .. je of the instance (those of a row skip the row itself), scaled
     const int64_t e0 = (int64_t)jb * n;
     const int ne = (je - jb + 1) * n;
@@ -377,42 +406,29 @@ __global__ __launch_bounds__(64 * ROWS, 2) void k_apply_lane(
       else if (e < (LANE_MIN + 1) * n) zl[e] = cmk(0.0, 0.0);
     }
     __syncthreads();
-  }
-  if (wv >= rows) return;
-  cplx acc[n];
+    if (wv >= rows) return;
 #pragma unroll
-  for (int m = 0; m < n; ++m) acc[m] = cmk(0.0, 0.0);
-  if (live) {
-    const int jl = lane + (d0 + j >= p ? 1 : 0);
-    cplx z[n];
-    if constexpr (ROWS > 1) {
+    for (int m = 0; m < n; ++m) acc[m] = cmk(0.0, 0.0);
+    if (live) {
+      const int jl = lane + (d0 + j >= p ? 1 : 0);
+      cplx z[n];
 #pragma unroll
       for (int k = 0; k < n; ++k) z[k] = zl[jl * n + k];
-    } else {
-      const int64_t iq = (int64_t)(jb + jl) * n;
+      pair(h0, H, E, r2, z);
+    }
+  } else {
+#pragma unroll
+    for (int m = 0; m < n; ++m) acc[m] = cmk(0.0, 0.0);
+    if (j < je) {
+      const cplx* __restrict__ rec = v.lt + recb + lane;
+      const int64_t iq = (int64_t)(j + (d0 + j >= p ? 1 : 0)) * n;
+      const cplx h0 = rec[0], H = rec[LANE_CHUNK], E = rec[2 * LANE_CHUNK];
+      const double r2 = rec[3 * LANE_CHUNK].x;
+      cplx z[n];
 #pragma unroll
       for (int k = 0; k < n; ++k)
         z[k] = OPC ? cmul(x[cb + iq + k], v.op_col[i0 + iq + k]) : cscale(x[cb + iq + k], v.sJ[i0 + iq + k]);
-    }
-#pragma unroll
-    for (int m = 0; m < n; ++m) cmac(acc[m], h0, z[m]);
-    cplx Hm = h0;
-    cplx P = E;
-#pragma unroll
-    for (int nu = 1; nu <= S; ++nu) {
-      if (nu > 1) {
-        const cplx Hn = csub(cscale(H, (nu - 1) * r2), Hm);  // H_nu from H_{nu-1}, H_{nu-2}
-        Hm = H;
-        H = Hn;
-        P = cmul(P, E);
-      }
-      const cplx tp = cmul(H, P);
-      cplx tm = cmul(H, cconj(P));
-      if (nu & 1) tm = cmk(-tm.x, -tm.y);
-#pragma unroll
-      for (int m = 0; m < n - nu; ++m) cmac(acc[m], tp, z[m + nu]);
-#pragma unroll
-      for (int m = nu; m < n; ++m) cmac(acc[m], tm, z[m - nu]);
+      pair(h0, H, E, r2, z);
     }
   }
   double val[NV];
@@ -421,9 +437,7 @@ __global__ __launch_bounds__(64 * ROWS, 2) void k_apply_lane(
   lane_reduce_scatter<NV>(val, lane);
   const int vi = lane >> SH;
   if ((lane & ((1 << SH) - 1)) == 0 && vi < 2 * n) {
-    double* pr = reinterpret_cast<double*>(part + (int64_t)r * part_total +
-                                           *reinterpret_cast<const int64_t*>(itp + 12) +
-                                           wv * (int64_t)itp[16]);
+    double* pr = reinterpret_cast<double*>(part + (int64_t)r * part_total + pb + rowp);
     pr[vi] = val[0];
   }
 }
@@ -2173,7 +2187,7 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
       padded += (Mb + LANE_ROWS - 1) / LANE_ROWS * LANE_ROWS * n;
     }
     P.lane_rows = N[0] >= LANE_ROWS_NMIN && waves >= LANE_FEW_WAVES && 20 * padded <= 21 * waves ? LANE_ROWS : 1;
-    P.lane_us = (double)waves * (0.085e-3 + 10.6e-6 * np * np);
+    P.lane_us = (double)waves * np * (0.037e-3 + 9.4e-6 * np);
     int64_t i0 = 0;  // first unknown of instance b
     for (int b = 0; b < B; ++b) {
       const int64_t d0 = idisk[b], Mb = idisk[b + 1] - d0;
@@ -2183,7 +2197,6 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
         P.poff[p] = P.part;
         P.part += std::max<int64_t>(n, 1) * np;
       }
-      const int64_t rec = n * (int64_t)(LANE_CHUNK * LANE_REC);  // records of a row
       for (int64_t p = d0; p < d0 + Mb; p += P.lane_rows)
         for (int64_t c = 0; c < n; ++c) {
           const int64_t jb = c * LANE_CHUNK, je = std::min<int64_t>(jb + LANE_CHUNK, Mb - 1);
@@ -2197,8 +2210,7 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
           push64(Mb * np);
           push64(ltoff[p] + c * (int64_t)(LANE_CHUNK * LANE_REC));
           push64(P.poff[p] + c * np);
-          push64(rec);
-          push64(std::max<int64_t>(n, 1) * np);  // partial sums of a row
+          push64(0);
         }
       i0 += Mb * np;
     }
@@ -2289,7 +2301,7 @@ static void make_few(int B, const int64_t* idisk, const int32_t* N, PlanHost& P)
     }
     for (int p = 0; p < M; ++p)
       for (int m0 = 0; m0 <= 2 * N[d0 + p]; m0 += 32) {
-        P.few_us += 0.55e-3 + 0.12e-3 * M + 7.9e-6 * (double)off[M];
+        P.few_us += 0.45e-3 + 0.158e-3 * M + 8.5e-6 * (double)off[M];
         const size_t w = P.few_tasks.size();
         P.few_tasks.resize(w + P.few, 0);
         int32_t* it = P.few_tasks.data() + w;
@@ -2321,11 +2333,12 @@ static void make_few(int B, const int64_t* idisk, const int32_t* N, PlanHost& P)
 // Whether applies of R right-hand sides run on k_apply_few.  For uniform orders one lane per
 // pair is the other way, by far the faster one where the launch is many tasks of few modes:
 // a wave then is a row with all its columns and k_apply_few a workgroup of 256 threads.  Both
-// by estimates (us of whole applies, fitted to 1,300 batches of 1 to 3,000 instances within
-// 13% and 8% in the mean; per row and right-hand side 0.55 + 0.12 M + 0.0079 M n, and 0.085 +
-// 0.0106 n^2 ns, n modes): 4 disks of 31 modes 8.4 with one lane per pair, 6.5 with k_apply_few;
-// of 25 modes 2 disks 11.9, 8.6, 1,000 x 4 44, 11.5, 256 x 12 80, 71; of 3 modes 40 x 12 10.9,
-// 5.4, 1,000 x 12 12.1, 49, with 7 columns 32.7, 325; of 7 modes 1,000 x 10, 4 columns 40.8, 163.
+// by estimates (us of whole applies, 4.5 and 9.3 besides, fitted to 1,900 batches of 1 to 3,000
+// instances within 15% and 9% in the mean; per row and right-hand side 0.45 + 0.158 M + 0.0085 M
+// n, and 0.037 n + 0.0094 n^2 ns, n modes): 4 disks of 31 modes 8.4 with one lane per pair, 6.5
+// with k_apply_few; of 25 modes 2 disks 11.9, 8.6, 1,000 x 4 44, 11.5, 256 x 12 80, 71; of 3
+// modes 40 x 12 10.9, 5.4, 1,000 x 12 12.1, 49, with 7 columns 32.7, 325; of 15 modes 1,000 x 8, 7
+// columns 155, 193.
 // split: the sums are added by the kernel that follows, so that one lane per pair is one
 // launch as well.
 #define FEW_MARGIN 1.15
@@ -2333,7 +2346,7 @@ static bool few_applies(const mudiff_ctx* h, int R, bool split) {
   const MatvecPlan& P = h->plan;
   if (!P.few || P.lane != LANE_UNIFORM) return P.few > 0;
   const double few = R * P.few_us, lane = R * P.lane_us;
-  return FEW_MARGIN * few < lane + 4.0 || (!split && FEW_MARGIN * (few + 4.9) < lane + 10.9);
+  return FEW_MARGIN * few < lane + 4.0 || (!split && FEW_MARGIN * (few + 4.5) < lane + 9.3);
 }
 
 double apply_few_us(const mudiff_ctx* h, int R) {
