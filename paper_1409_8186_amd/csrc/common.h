@@ -120,7 +120,7 @@ struct DevView {
 // One-lane work item, int32 words: first row disk p, row disks, q_begin, q_end,
 // instance b, its first disk, then int64 at word 6: first unknown of b, unknowns of b,
 // record offset of (p, chunk) in lt, partial-sum offset of (p, chunk); word 14: 0.  64
-// bytes, a cache line: records of 72 took 8% more time at orders 1 to 3.
+// bytes, a cache line: with records of 72 the kernel took 4% longer at order 3.
 // All the kernel needs before its vector loads comes from this one record.
 #define LANE_ITEM_INTS 16
 #define LANE_ROWS 4   // row disks per workgroup of k_apply_lane

@@ -203,8 +203,8 @@ __global__ __launch_bounds__(APPLY_THREADS) void k_apply(
 // 4 disks of 31 modes: 6.35 us as LDS-staged rows, 3.5 so.
 #define FEW_THREADS 256
 #define FEW_WAVES (FEW_THREADS / 64)
-#define FEW_HDR 16  // instance, first output, N_p, column disks, unknown of mode -N_p, imode, N_b, M
-#define FEW_COL 8   // offset in the instance vector, N_q, symbol t^{pq}_0, 1: times (-1)^s
+#define FEW_HDR 12  // instance, first output, N_p, column disks, then 64 bits: unknown of mode -N_p, imode, N_b
+#define FEW_COL 4   // offset in the instance vector, 2 N_q + (1: times (-1)^s), 64 bits: symbol t^{pq}_0
 #define FEW_PAD 31  // window entries before output m0's, for the outputs after it
 
 // The tables it reads, for the operator and op of the launch: y = alpha x + beta w
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(FEW_THREADS) void k_apply_few(
   int k = 0;
   for (int c = wv; c < nc; c += FEW_WAVES, ++k) {
     const int32_t* rec = it + FEW_HDR + FEW_COL * c;
-    const int qo = rec[0], Nq = rec[1], neg = rec[4];
+    const int qo = rec[0], Nq = rec[1] >> 1, neg = rec[1] & 1;
     const cplx* __restrict__ t = v.t + *reinterpret_cast<const int64_t*>(rec + 2);
     cplx* zl = base + (size_t)k * (2 * zcap + FEW_PAD);
     cplx* tl = zl + zcap;
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(FEW_THREADS) void k_apply_few(
   for (int i = 0; i < 4; ++i) a[i] = cmk(0.0, 0.0);
   k = 0;
   for (int c = wv; c < nc; c += FEW_WAVES, ++k) {
-    const int nq = 2 * it[FEW_HDR + FEW_COL * c + 1] + 1, full = nq >> 3;
+    const int nq = (it[FEW_HDR + FEW_COL * c + 1] | 1), full = nq >> 3;  // 2 N_q + 1
     const cplx* zq = base + (size_t)k * (2 * zcap + FEW_PAD) + part;
     const cplx* tq = zq + zcap + FEW_PAD - mi;
     cplx t1 = tq[-8], t2 = tq[-16], t3 = tq[-24];
@@ -2274,18 +2274,31 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
 
 static size_t few_lds(int cols, int zcap) { return (size_t)FEW_WAVES * cols * (2 * zcap + FEW_PAD) * 16; }
 
-static void make_few(int B, const int64_t* idisk, const int32_t* N, PlanHost& P) {
+// Shape of the tasks (P.few and the LDS they take); the ints of all tasks, 0: none.
+static size_t few_shape(int B, const int64_t* idisk, const int32_t* N, PlanHost& P) {
   int64_t mmax = 0;
   int nmax = 0;
   for (int b = 0; b < B; ++b) mmax = std::max(mmax, idisk[b + 1] - idisk[b]);
-  for (int64_t p = 0; p < idisk[B]; ++p) nmax = std::max(nmax, (int)N[p]);
+  if (mmax > FEW_DISKS || (P.lane == LANE_UNIFORM && mmax > 12 && idisk[B] > 1024)) return 0;
+  size_t tasks = 0;
+  for (int64_t p = 0; p < idisk[B]; ++p) {
+    nmax = std::max(nmax, (int)N[p]);
+    tasks += (size_t)(2 * N[p] + 32) / 32;
+  }
   const int cols = (int)(mmax - 1 + FEW_WAVES - 1) / FEW_WAVES, zcap = 2 * nmax + 1;
-  if (mmax > FEW_DISKS || few_lds(cols, zcap) > FEW_LDS) return;
-  if (P.lane == LANE_UNIFORM && mmax > 12 && idisk[B] > 1024) return;
+  if (few_lds(cols, zcap) > FEW_LDS) return 0;
   P.few = FEW_HDR + FEW_COL * (int)(mmax - 1);
   P.few_cols = cols;
   P.few_z = zcap;
+  return tasks * (size_t)P.few;
+}
+
+static void make_few(int B, const int64_t* idisk, const int32_t* N, PlanHost& P) {
+  const size_t ints = few_shape(B, idisk, N, P);
+  if (ints == 0) return;
+  P.few_tasks.resize(ints, 0);
   if (P.lane != LANE_UNIFORM) P.items.clear();
+  int32_t* it = P.few_tasks.data();
   int64_t i0 = 0, t0 = 0;  // first unknown and symbol of the instance
   for (int b = 0; b < B; ++b) {
     const int64_t d0 = idisk[b];
@@ -2302,9 +2315,6 @@ static void make_few(int B, const int64_t* idisk, const int32_t* N, PlanHost& P)
     for (int p = 0; p < M; ++p)
       for (int m0 = 0; m0 <= 2 * N[d0 + p]; m0 += 32) {
         P.few_us += 0.45e-3 + 0.158e-3 * M + 8.5e-6 * (double)off[M];
-        const size_t w = P.few_tasks.size();
-        P.few_tasks.resize(w + P.few, 0);
-        int32_t* it = P.few_tasks.data() + w;
         auto put64 = [&](int k, int64_t x) {
           it[k] = (int32_t)(x & 0xffffffff);
           it[k + 1] = (int32_t)(x >> 32);
@@ -2319,11 +2329,11 @@ static void make_few(int B, const int64_t* idisk, const int32_t* N, PlanHost& P)
         for (int q = 0, k = FEW_HDR; q < M; ++q) {
           if (q == p) continue;
           it[k] = (int32_t)off[q];
-          it[k + 1] = N[d0 + q];
+          it[k + 1] = 2 * N[d0 + q] + (p > q ? 1 : 0);
           put64(k + 2, sym[p][q]);
-          it[k + 4] = p > q;
           k += FEW_COL;
         }
+        it += P.few;
       }
     i0 += off[M];
     t0 = t;
@@ -2360,15 +2370,15 @@ size_t plan_sched_bytes(const PlanHost& P, int M) {
 }
 
 size_t sched_bytes_for(int B, const int64_t* disk_off, const int32_t* n_modes) {
-  size_t bytes = 0;
-  for (bool pairs : {false, true}) {  // which of the two also depends on the centers
-    PlanHost H;
-    make_plan(B, disk_off, n_modes, pairs, H);
-    bytes = std::max(bytes, plan_sched_bytes(H, (int)disk_off[B]));
-    make_few(B, disk_off, n_modes, H);
-    bytes = std::max(bytes, plan_sched_bytes(H, (int)disk_off[B]));
-  }
-  return bytes;
+  PlanHost H;
+  make_plan(B, disk_off, n_modes, false, H);
+  const size_t few = few_shape(B, disk_off, n_modes, H);
+  if (few > 0 && H.lane != LANE_UNIFORM) H.items.clear();
+  const size_t bytes = plan_sched_bytes(H, (int)disk_off[B]) + align256(few * 4);
+  if (H.lane == LANE_UNIFORM || few > 0 || !pairs_batch(B, disk_off, n_modes)) return bytes;
+  PlanHost Q;  // which of the two also depends on the centers
+  make_plan(B, disk_off, n_modes, true, Q);
+  return std::max(bytes, plan_sched_bytes(Q, (int)disk_off[B]));
 }
 
 int ensure_plan(mudiff_ctx* h, hipStream_t s) {
@@ -2424,6 +2434,7 @@ int ensure_plan(mudiff_ctx* h, hipStream_t s) {
 size_t apply_scratch_bytes(mudiff_ctx* h, int R) {
   const size_t counters = align256((size_t)R * h->M_all * 4);
   if (use_mfma(h, R)) return align256(mfma_scratch_bytes(h, R)) + counters;
+  if (h->plan.ready) h->plan_part = h->plan.part_total;
   if (h->plan_part < 0) {
     PlanHost H;
     make_plan(h->B, h->idisk.data(), h->N.data(), h->pairs_ok, H);
