@@ -1805,6 +1805,8 @@ static int mfma_autotune(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scr
     }
     dflops += 8.0 * R * (sn * sn - sn2);
   }
+  int64_t mmax = 0;  // disks of the largest instance
+  for (int b = 0; b < h->B; ++b) mmax = std::max(mmax, h->idisk[b + 1] - h->idisk[b]);
   const float direct_floor_ms = (float)(2.0 * dflops / 78.6e12 * 1e3);
   // one warm-up and two timed applies of candidate c; keeps the fastest (and
   // returns the time, 0 when skipped or failed)
@@ -1847,23 +1849,20 @@ static int mfma_autotune(mudiff_ctx* h, int R, const cplx* x, cplx* y, char* scr
   for (MfmaChoice c : cands) {
     if (!c.circ && best > 0.0f && direct_floor_ms > best) continue;
     if (c.circ) c.cvar = cvars[0];
-    time_one(c);
+    const float ms = time_one(c);
     if (rc != MUDIFF_OK) break;
-  }
-  if (rc == MUDIFF_OK && !bc.circ) {
-    // then whole instances and segments of 32 with the fastest tile: the rule counts items, but
-    // short segments of small instances or many row tiles cost more in partial sums than the
-    // evener end saves (us of an apply by rule, and by these: 64 x 12 disks of order 3, 20
-    // columns 46, 38; 200 of order 31, 20 columns 746, 680; 300 x 6 of orders 5..18, 12 columns
-    // 90, 81; 200 of orders 5..18, 20 columns 268, 223)
-    MfmaChoice c = bc;
-    int64_t mmax = 0;
-    for (int b = 0; b < h->B; ++b) mmax = std::max(mmax, h->idisk[b + 1] - h->idisk[b]);
-    const int rule = segment(h, R, bc);
+    // A tile of the direct form that is no more than 1.3 times as slow as the best is also timed
+    // with whole instances and segments of 32: the rule counts items, but short segments of
+    // small instances or of many row tiles cost more in partial sums than the evener end saves
+    // (us of an apply by rule, and by these: 64 x 12 disks of order 3, 20 columns 46, 38; 200 of
+    // order 31, 20 columns 746, 680; 300 x 6 of orders 5..18, 12 columns 90, 81; 200 of orders
+    // 5..18, 20 columns 268, 223).
+    const int rule = segment(h, R, c);
     for (int qs : {0, 32}) {
-      if (qs == rule || qs >= mmax || rc != MUDIFF_OK) continue;
-      c.QS = qs;
-      time_one(c);
+      if (c.circ || ms == 0.0f || ms > 1.3f * best || qs == rule || qs >= mmax || rc != MUDIFF_OK) continue;
+      MfmaChoice q = c;
+      q.QS = qs;
+      time_one(q);
     }
   }
   if (rc == MUDIFF_OK && bc.circ) {  // then the other per-frequency product variants
@@ -1997,6 +1996,8 @@ struct PlanHost {
   int few = 0, few_cols = 0, few_z = 0, lane_rows = 1;  // few: ints per task
   int64_t row_part = 0;  // partial sums of the LDS-staged kernel (bounds mudiff_matvec_noalloc)
   double few_us = 0.0, lane_us = 0.0;
+  bool count = false;  // only the sizes: nothing goes into items and tasks
+  size_t item_total = 0, task_total = 0;  // ints of items and tasks
   std::vector<int32_t> items, nch, tasks, few_tasks;
   std::vector<int64_t> poff;
 };
@@ -2102,7 +2103,7 @@ static void make_pairs_plan(int B, const int64_t* idisk, const int32_t* N, int64
   P.item_ints = PAIRS_ITEM_INTS;
   int lane_N = -1, nmax = 0;
   std::vector<int32_t> ord;
-  lane_layout(B, idisk, N, &lane_N, nullptr, &ord);
+  if (!P.count) lane_layout(B, idisk, N, &lane_N, nullptr, &ord);
   int64_t part1 = 0;  // partial sums at one chunk per segment
   for (int b = 0; b < B; ++b) {
     const int64_t d0 = idisk[b], Mb = idisk[b + 1] - d0;
@@ -2130,20 +2131,22 @@ static void make_pairs_plan(int B, const int64_t* idisk, const int32_t* N, int64
   for (int b = 0; b < B; ++b) {
     const int64_t d0 = idisk[b], Mb = idisk[b + 1] - d0;
     const int64_t nch = Mb > 1 ? (Mb + LANE_CHUNK - 1) / LANE_CHUNK : 0, nseg = (nch + K - 1) / K;
-    const int64_t tb = (int64_t)P.tasks.size() / 2;
+    const int64_t tb = (int64_t)P.task_total / 2;
     for (int64_t k = d0; k < d0 + Mb; ++k) {
-      const int p = ord[(size_t)k], np = 2 * N[p] + 1;
+      const int p = P.count ? (int)k : ord[(size_t)k], np = 2 * N[p] + 1;
       P.nch[p] = (int32_t)nseg;
       P.poff[p] = P.part;
       P.part += std::max<int64_t>(nseg, 1) * np;
       const int nblk = (np + btmax - 1) / btmax, w = pairs_width((np + nblk - 1) / nblk, P.wide);
-      for (int ms = 0; ms < np && nch > 0; ms += w) {
+      if (nch > 0) P.task_total += 2 * (size_t)((np + w - 1) / w);
+      for (int ms = 0; ms < np && nch > 0 && !P.count; ms += w) {
         P.tasks.push_back(p);
         P.tasks.push_back((ms << 8) | w);
       }
     }
-    const int64_t te = (int64_t)P.tasks.size() / 2;
-    for (int64_t sg = 0; sg < nseg; ++sg)
+    const int64_t te = (int64_t)P.task_total / 2;
+    P.item_total += (size_t)(nseg * ((te - tb + run - 1) / run)) * PAIRS_ITEM_INTS;
+    for (int64_t sg = 0; sg < nseg && !P.count; ++sg)
       for (int64_t t = tb; t < te; t += run) {
         const int64_t rec[PAIRS_ITEM_INTS] = {b, sg * K, std::min(K, nch - sg * K), t, std::min(te, t + run),
                                               d0, sg, Mb};
@@ -2156,6 +2159,7 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
   const int M = (int)idisk[B];
   P.items.clear();
   P.tasks.clear();
+  P.item_total = P.task_total = 0;
   P.nch.assign(M, 0);
   P.poff.assign(M, 0);
   P.part = 0;
@@ -2197,7 +2201,8 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
         P.poff[p] = P.part;
         P.part += std::max<int64_t>(n, 1) * np;
       }
-      for (int64_t p = d0; p < d0 + Mb; p += P.lane_rows)
+      P.item_total += (size_t)((Mb + P.lane_rows - 1) / P.lane_rows * n) * LANE_ITEM_INTS;
+      for (int64_t p = d0; p < d0 + Mb && !P.count; p += P.lane_rows)
         for (int64_t c = 0; c < n; ++c) {
           const int64_t jb = c * LANE_CHUNK, je = std::min<int64_t>(jb + LANE_CHUNK, Mb - 1);
           P.items.push_back((int32_t)p);
@@ -2250,7 +2255,8 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
       P.nch[p] = (int32_t)n;
       P.poff[p] = P.part;
       P.part += n * np;
-      for (int64_t c = 0; c < n; ++c) {
+      P.item_total += (size_t)n * 4;
+      for (int64_t c = 0; c < n && !P.count; ++c) {
         int64_t jb = c * qc, je = std::min<int64_t>(jb + qc, Mb - 1);
         P.items.push_back((int32_t)p);
         P.items.push_back((int32_t)c);
@@ -2297,7 +2303,10 @@ static void make_few(int B, const int64_t* idisk, const int32_t* N, PlanHost& P)
   const size_t ints = few_shape(B, idisk, N, P);
   if (ints == 0) return;
   P.few_tasks.resize(ints, 0);
-  if (P.lane != LANE_UNIFORM) P.items.clear();
+  if (P.lane != LANE_UNIFORM) {
+    P.items.clear();
+    P.item_total = 0;
+  }
   int32_t* it = P.few_tasks.data();
   int64_t i0 = 0, t0 = 0;  // first unknown and symbol of the instance
   for (int b = 0; b < B; ++b) {
@@ -2365,18 +2374,20 @@ double apply_few_us(const mudiff_ctx* h, int R) {
 }
 
 size_t plan_sched_bytes(const PlanHost& P, int M) {
-  return align256(P.items.size() * 4) + align256((size_t)M * 4) + align256((size_t)M * 8) +
-         align256(P.tasks.size() * 4) + align256(P.few_tasks.size() * 4) + 256;
+  return align256(P.item_total * 4) + align256((size_t)M * 4) + align256((size_t)M * 8) +
+         align256(P.task_total * 4) + align256(P.few_tasks.size() * 4) + 256;
 }
 
 size_t sched_bytes_for(int B, const int64_t* disk_off, const int32_t* n_modes) {
   PlanHost H;
+  H.count = true;
   make_plan(B, disk_off, n_modes, false, H);
   const size_t few = few_shape(B, disk_off, n_modes, H);
-  if (few > 0 && H.lane != LANE_UNIFORM) H.items.clear();
+  if (few > 0 && H.lane != LANE_UNIFORM) H.item_total = 0;
   const size_t bytes = plan_sched_bytes(H, (int)disk_off[B]) + align256(few * 4);
   if (H.lane == LANE_UNIFORM || few > 0 || !pairs_batch(B, disk_off, n_modes)) return bytes;
   PlanHost Q;  // which of the two also depends on the centers
+  Q.count = true;
   make_plan(B, disk_off, n_modes, true, Q);
   return std::max(bytes, plan_sched_bytes(Q, (int)disk_off[B]));
 }

@@ -196,16 +196,16 @@ def test_timed_configuration_can_be_fixed(host, instances):
     ([grid(6, 2.1, ORDERS)] * 300, 12, {0, 4}), ([grid(20, 2.1, ORDERS)] * 64, 20, {0, 16}),
 ], ids=["8x12", "200", "300x6", "64x20"])
 def test_segments_that_are_timed(host, instances, R, timed):
-    """The direct form's segment lengths that first use tries: the rule's, and whole instances and 32
-    with the tile that is fastest by rule."""
-    h = host.tables(instances)
+    """Each tile of the direct form that first use times is timed with the rule's segment length, with
+    whole instances and with segments of 32."""
     seen = set()
-    for win in range(12):
+    for win in range(18):
         pick(host, win)
-        h2 = host.tables(instances)
-        a = Applies(host, h2, R)
+        h = host.tables(instances)
+        a = Applies(host, h, R)
         a.run()
-        seen.add(a.config()[3])
-        host.check(host.lib.mudiff_destroy(h2))
-    assert seen == timed
-    host.check(host.lib.mudiff_destroy(h))
+        seen.add(tuple(a.config()[1:4]))
+        host.check(host.lib.mudiff_destroy(h))
+    assert {qs for *_, qs in seen} == timed
+    tiles = {(ct, rp) for ct, rp, _ in seen}
+    assert all({qs for c, r, qs in seen if (c, r) == t} >= {0} | ({32} & timed) for t in tiles), seen
