@@ -2472,13 +2472,14 @@ static int compact_columns(GmresRun& G, const std::vector<int32_t>& run, int n_r
 // 5% and 8% in the mean where the two are close).  This kernel: a column per workgroup, so C
 // columns go in rounds of n_cu, and phase A in rounds of tasks over the waves, w = rounds x
 // column disks x (modes / 8 + 2.5):
-//   4.3 + 45 / m + 0.63 M + 0.019 N_b + 0.047 w, and 3.1 + 0.25 M + 0.016 N_b + 0.075 w for
-//   each further round of columns
+//   6.6 + 43 / m + 0.34 M + 1.6 max(M - 12, 0) + 0.015 N_b + 0.058 w, and 3.1 + 0.25 M + 0.016
+//   N_b + 0.075 w for each further round of columns
 // three kernels: 25.0 + 11 / m + 0.08 M + 0.67 (their apply) + 0.21 per 1,000 unknowns.
 // Whole solves, us, three kernels a step against this one: 4 disks of 31 modes 740, 292; 2 x 25
 // 416, 220; 10 disks of 33 modes (basis in global memory) 1,986, 1,634; 256 instances of 4 x 25,
 // 7 columns each, 2,531, 1,028; steps: 12 disks of 25 modes 26.4, 22.4; 16 of 25 28.0, 33.9; 11
-// of 33 29.2, 34.7; 300 x 16 of 3 modes, 7 columns 75, 149, of 25 modes 324, 289.
+// of 33 29.2, 34.7; 300 x 16 of 3 modes, 7 columns 75, 149, of 25 modes 324, 289; 16 x 16 of 25, 4
+// columns 31.5, 34.7 (graph).
 static bool small_cycle(const mudiff_ctx* h, const GState& s, SmallGeom* g, bool* vl) {
   if (s.R >= 8) return false;
   int T = 0, N = 0, mmax = 0;
@@ -2501,7 +2502,7 @@ static bool small_cycle(const mudiff_ctx* h, const GState& s, SmallGeom* g, bool
   *vl = small_lds(T, N, s.m, true) * 16 <= SMALL_LDS;
   if (!*vl && small_lds(T, N, s.m, false) * 16 > SMALL_LDS) return false;
   const int rounds = (s.C + h->n_cu - 1) / h->n_cu;
-  const double one = 4.3 + 45.0 / s.m + 0.63 * mmax + 0.019 * N + 0.047 * w +
+  const double one = 6.6 + 43.0 / s.m + 0.34 * mmax + 1.6 * std::max(mmax - 12, 0) + 0.015 * N + 0.058 * w +
                      (rounds - 1) * (3.1 + 0.25 * mmax + 0.016 * N + 0.075 * w);
   const double three = 25.0 + 11.0 / s.m + 0.08 * mmax + 0.67 * apply_few_us(h, s.R) + 0.21e-3 * (double)s.NT;
   return one < three;

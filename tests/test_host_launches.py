@@ -121,6 +121,7 @@ def test_kernel_of_uniform_orders(host, B, M, N, R, few):
     (batch([16] * 10, 5, 18), 1, 10, False), (uniform(1, 11, 16), 1, 10, False),  # 14.2, 18.1; 24.8, 29.6
     (uniform(300, 16, 1), 7, 20, False), (uniform(300, 13, 3), 7, 20, False),     # 75, 149; 93, 125
     (uniform(64, 16, 1), 7, 20, False),                                           # 29, 41
+    (uniform(16, 16, 12), 4, 24, False), (uniform(1, 12, 15), 1, 30, True),       # 31.5, 34.7; 26.5, 23.5
 ])
 def test_cycles_of_small_columns(host, instances, R, restart, small):
     """The kernels of a solve's first cycle; its state reads as running until one of them is launched,
