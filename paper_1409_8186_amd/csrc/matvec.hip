@@ -1948,7 +1948,9 @@ struct Variant {
   apply_fn fn;
 };
 
-// LDS-staged kernels: generic (nspec = -1) and uniform-N specialisations
+// LDS-staged kernels: generic (nspec = -1) and uniform-N specialisations (batches of N = 15 with
+// instances of 17 to some 65 disks, us, generic and exact loop bounds: one of 20 10.3, 8.2, 40
+// of 22 25.9, 17.9, 8 of 50, 4 columns 67.8, 44.7, 40 of 65 142.8, 94.9)
 const Variant kVariants[] = {
     {4, -1, k_apply<4, -1>}, {4, 15, k_apply<4, 15>},
 };
@@ -2075,7 +2077,13 @@ bool pairs_batch(int B, const int64_t* idisk, const int32_t* N) {
     }
   }
   const double n = 2.0 * nmax + 1.0;
-  const double lds = 5.9 + 0.096 * passes * n + (macs_span > 0.0 ? 9.5 : 0.0) + 0.010 * wgs + 0.92e-6 * macs + 0.24e-6 * macs_span;
+  double lds = 5.9 + 0.096 * passes * n + (macs_span > 0.0 ? 9.5 : 0.0) + 0.010 * wgs + 0.92e-6 * macs + 0.24e-6 * macs_span;
+  int bt = 0, nspec = -1;
+  choose_variant((int)idisk[B], N, &bt, &nspec);
+  // the variant for one order (the factors fit the choices at 71 batches; k_apply_pairs in turn,
+  // us): 40 instances of 24 disks 20.4, 25.2, 120 of 28 62.7, 77.2, 40 of 50 63.6, 51.5, 40 of 65
+  // 94.9, 122.6, one of 100 27.6, 15.6
+  if (nspec >= 0) lds *= macs_span > 0.0 ? 0.9 : 0.57;
   const double pairs = 6.8 + 0.144 * n + 2.33e-6 * instr + 0.00107 * tasks;
   return PAIRS_MARGIN * pairs < lds;
 }

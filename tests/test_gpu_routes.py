@@ -48,7 +48,8 @@ def test_uniform_orders_by_number_of_columns(B, M, N):
 
 
 @pytest.mark.parametrize("Ms,orders", [([5, 12, 9, 7] * 25 + [24], (13, 20)), ([3] * 20 + [25], (24, 31)),
-                                       ([26], (1, 4)), ([5, 12] * 20 + [70], (13, 20)), ([26], (13, 20))])
+                                       ([26], (1, 4)), ([5, 12] * 20 + [70], (13, 20)), ([26], (13, 20)),
+                                       ([17, 23], (15, 15)), ([65, 24], (15, 15)), ([66], (15, 15))])
 def test_mixed_orders_by_the_whole_batch(Ms, orders):
     check_applies([cluster(M, orders, M + i) for i, M in enumerate(Ms)], [1, 4], sample=[0, len(Ms) - 1])
 

@@ -80,6 +80,11 @@ SMALL, TINY = [5 + i % 8 for i in range(1000)], [2 + i % 3 for i in range(300)]
     ([400], (13, 20), "k_apply_pairs"),
     ([40], (24, 31), "k_apply_pairs"),                 # 41, 20
     ([40], (24, 32), "k_apply"),                       # orders beyond the kernel's
+    # one order that has a variant of its own
+    ([24] * 40, (15, 15), "k_apply"), ([28] * 120, (15, 15), "k_apply"),  # 20.4, 25.2; 62.7, 77.2
+    ([32] * 8, (15, 15), "k_apply"), ([65] * 40, (15, 15), "k_apply"),    # 9.9, 13.9; 94.9, 122.6
+    ([50] * 120, (15, 15), "k_apply_pairs"),                              # 175, 148
+    ([100], (15, 15), "k_apply_pairs"), ([24] * 120, (14, 14), "k_apply_pairs"),
 ])
 def test_kernel_of_mixed_orders(host, sizes, orders, kernel):
     h = host.tables(batch(sizes, *orders))
