@@ -21,18 +21,27 @@ def _misfit_grad(inst, device, betas, thetas, target, opts):
     R = (betas if isinstance(betas, torch.Tensor) else np.asarray(betas)).reshape(len(inst), -1).shape[1]
     restart = opts.get("restart", 50)
     circulant, sstep = opts.get("circulant"), opts.get("sstep")
-    # The circulant form carries the solves of 8 and more columns (orders up to 31); the
-    # first apply times it against the direct form.  Its tables are two to three times the
-    # direct form's, so where they do not fit the direct form solves alone.
+    disks = [len(n) for _, _, n, _ in inst]
+    orders_ok = max(int(np.max(n)) for _, _, n, _ in inst) <= 31  # else no apply on the matrix cores
+    unknowns = sum(2 * int(np.sum(n)) + len(n) for _, _, n, _ in inst) / len(inst)  # of a column
+    # The circulant form carries the solves of 8 and more columns, but for instances so small
+    # that its transforms cost what it saves (ms a gradient, direct and circulant form: 100 disks
+    # of order 31, 64 columns 257, 54; 30 of order 4, 8 columns 13.4, 11.7; 16 x 10 of order 31 9.7,
+    # 6.1; 4 x 10 of orders 13..20 9.7, 11.3; 200 x 3 of order 4 3.4, 3.7).  Its tables are two to
+    # three times the direct form's, so where they do not fit the direct form solves alone.
     auto_circulant = circulant is None
     if auto_circulant:
-        circulant = R >= 8 and max(int(np.max(n)) for _, _, n, _ in inst) <= 31
-    # s-step solves for many columns (restarts up to 64): their basis sweeps are half of a
-    # lockstep step (4 x 100 disks x 64 columns: 179 against 249 ms per gradient).  Where
-    # one stagnates, one-vector cycles solve.
+        circulant = R >= 8 and orders_ok and (max(disks) >= 24 or (max(disks) >= 10 and sum(disks) >= 128))
+    # s-step solves (restarts of 20 to 64) halve the basis sweeps of long solves of long columns,
+    # and take the host 6 to 20 us a column for their shifts (ms a gradient, one-vector and s-step
+    # solves: 4 x 100 disks of order 4, 64 columns 118, 102; 60 of order 31, 64 columns 35, 30; 16 x 30
+    # of order 31, 16 columns 32, 29, of order 4 19.1, 19.6; 32 x 16 of order 31, 64 columns 79, 101;
+    # 200 x 3 of order 4 10, 261).  Where one stagnates, one-vector cycles solve.
     auto_sstep = sstep is None
     if auto_sstep:
-        sstep = 10 if R >= 8 and 20 <= restart <= 64 else 0
+        mean = sum(disks) / len(inst)
+        long = mean >= 50 or (mean >= 24 and unknowns >= 1500)
+        sstep = 10 if R >= 8 and orders_ok and long and 20 <= restart <= 64 else 0
     while True:
         P = None
         try:
@@ -61,8 +70,8 @@ class FarFieldMisfit(torch.autograd.Function):
     betas [B,R], thetas [n_rec], target [B*R, n_rec] complex128 and a dict of
     solver options: restart, tol, maxit; circulant (True or False: tables with or
     without the circulant form) and sstep (Newton vectors per block of s-step
-    solves, 0 for one-vector ones), both chosen by the number of columns when
-    absent or None."""
+    solves, 0 for one-vector ones), both chosen by the sizes when absent or
+    None."""
 
     @staticmethod
     def forward(ctx, centers, radii, k, n_modes, disk_off, betas, thetas, target, opts=None):

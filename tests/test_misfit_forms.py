@@ -40,44 +40,60 @@ OOM = torch.OutOfMemoryError("workspace")
 STUCK = L.MudiffError(5, "forward solve did not converge")
 
 
-@pytest.mark.parametrize("R,N,opts,fails,calls", [
-    (2, 4, {}, {}, [(False, 0)]),
-    (8, 4, {}, {}, [(True, 10)]),
-    (8, 32, {}, {}, [(False, 10)]),
-    (8, 4, {"restart": 65}, {}, [(True, 0)]),
-    (8, 4, {"circulant": False, "sstep": 0}, {}, [(False, 0)]),
-    (2, 4, {"circulant": True, "sstep": 4}, {}, [(True, 4)]),
-    (8, 4, {}, {(True, "tables"): True}, [(True, "tables"), (False, 0)]),
-    (8, 4, {}, {(True, 10): OOM}, [(True, 10), (False, 0)]),
-    (8, 4, {"sstep": 5}, {(True, 5): OOM}, [(True, 5), (False, 5)]),
-    (8, 4, {}, {(True, 10): STUCK}, [(True, 10), (True, 0)]),
-    (8, 4, {}, {(True, 10): STUCK, (True, 0): OOM}, [(True, 10), (True, 0), (False, 0)]),
-    # what nothing is left for is raised, and so is what the caller asked for
-    (2, 4, {}, {(False, 0): OOM}, [(False, 0)]),
-    (2, 4, {}, {(False, 0): STUCK}, [(False, 0)]),
-    (8, 4, {}, {(True, 10): STUCK, (True, 0): STUCK}, [(True, 10), (True, 0)]),
-    (8, 4, {}, {(True, 10): L.MudiffError(4, "device")}, [(True, 10)]),
-    (8, 4, {"circulant": True, "sstep": 6}, {(True, 6): STUCK}, [(True, 6)]),
-    (8, 4, {"circulant": True, "sstep": 0}, {(True, 0): OOM}, [(True, 0)]),
-])
-def test_form_and_solver(monkeypatch, R, N, opts, fails, calls):
+def run(monkeypatch, B, M, N, R, opts, fails):
+    """(calls, what was raised) of a gradient of B instances of M disks of order N."""
     monkeypatch.setattr(autograd, "Problem", Fake)
     Fake.fails, Fake.calls, Fake.open = fails, [], 0
-    c = torch.zeros(4, 2, dtype=torch.float64, requires_grad=True)
-    args = (c, torch.ones(4, dtype=torch.float64), torch.ones(2, dtype=torch.float64), np.full(4, N), np.array([0, 2, 4]),
-            np.zeros((2, R)), np.zeros(3), np.zeros((2 * R, 3), complex), opts)
-    last = fails.get(calls[-1])
-    if last is None:
+    c = torch.zeros(B * M, 2, dtype=torch.float64, requires_grad=True)
+    args = (c, torch.ones(B * M, dtype=torch.float64), torch.ones(B, dtype=torch.float64), np.full(B * M, N),
+            np.arange(B + 1) * M, np.zeros((B, R)), np.zeros(3), np.zeros((B * R, 3), complex), opts)
+    err = None
+    try:
         autograd.FarFieldMisfit.apply(*args).sum().backward()
-        assert c.grad.shape == (4, 2)
-    else:
-        with pytest.raises(type(last)):
-            autograd.FarFieldMisfit.apply(*args)
-    assert Fake.calls == calls and Fake.open == 0
+        assert c.grad.shape == (B * M, 2)
+    except (torch.OutOfMemoryError, L.MudiffError) as e:
+        err = e
+    assert Fake.open == 0
+    return Fake.calls, err
+
+
+@pytest.mark.parametrize("B,M,N,R,opts,call", [
+    (2, 60, 4, 7, {}, (False, 0)), (2, 60, 4, 8, {}, (True, 10)), (2, 60, 32, 8, {}, (False, 0)),
+    (2, 60, 4, 8, {"restart": 65}, (True, 0)), (2, 60, 4, 8, {"restart": 19}, (True, 0)),
+    (1, 30, 4, 8, {}, (True, 0)), (4, 30, 31, 8, {}, (True, 10)),
+    (16, 10, 31, 64, {}, (True, 0)), (4, 10, 16, 64, {}, (False, 0)), (200, 3, 4, 64, {}, (False, 0)),
+    (32, 16, 31, 64, {}, (True, 0)), (1, 2, 4, 8, {}, (False, 0)),
+    (2, 60, 4, 8, {"circulant": False, "sstep": 0}, (False, 0)),
+    (2, 2, 4, 2, {"circulant": True, "sstep": 4}, (True, 4)),
+    (2, 60, 4, 8, {"circulant": None, "sstep": None}, (True, 10)),
+])
+def test_form_and_solver(monkeypatch, B, M, N, R, opts, call):
+    assert run(monkeypatch, B, M, N, R, opts, {}) == ([call], None)
+
+
+@pytest.mark.parametrize("opts,fails,calls", [
+    ({}, {(True, "tables"): True}, [(True, "tables"), (False, 0)]),
+    ({}, {(True, 10): OOM}, [(True, 10), (False, 0)]),
+    ({"sstep": 5}, {(True, 5): OOM}, [(True, 5), (False, 5)]),
+    ({}, {(True, 10): STUCK}, [(True, 10), (True, 0)]),
+    ({}, {(True, 10): STUCK, (True, 0): OOM}, [(True, 10), (True, 0), (False, 0)]),
+    # what nothing is left for is raised, and so is what the caller asked for
+    ({"circulant": False, "sstep": 0}, {(False, 0): OOM}, [(False, 0)]),
+    ({"circulant": False, "sstep": 0}, {(False, 0): STUCK}, [(False, 0)]),
+    ({}, {(True, 10): STUCK, (True, 0): STUCK}, [(True, 10), (True, 0)]),
+    ({}, {(True, 10): L.MudiffError(4, "device")}, [(True, 10)]),
+    ({"circulant": True, "sstep": 6}, {(True, 6): STUCK}, [(True, 6)]),
+    ({"circulant": True, "sstep": 0}, {(True, 0): OOM}, [(True, 0)]),
+])
+def test_what_is_left_after_a_failure(monkeypatch, opts, fails, calls):
+    got, err = run(monkeypatch, 2, 60, 4, 8, opts, fails)
+    assert got == calls
+    last = fails.get(calls[-1])
+    assert err is None if last is None else type(err) is type(last)
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("opts", [{}, {"circulant": False}, {"sstep": 0}, {"circulant": False, "sstep": 0}])
+@pytest.mark.parametrize("opts", [{}, {"circulant": True, "sstep": 10}, {"circulant": False, "sstep": 10}, {"circulant": True}])
 def test_gradient_of_many_columns(opts):
     """8 and 17 incidences on two instances of well-separated disks: the oracle's adjoint gradient to
     1e-10, as for the direct form and one-vector solves."""
