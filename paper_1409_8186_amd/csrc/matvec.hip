@@ -2367,18 +2367,26 @@ static void make_few(int B, const int64_t* idisk, const int32_t* N, PlanHost& P)
 // modes 40 x 12 10.9, 5.4, 1,000 x 12 12.1, 49, with 7 columns 32.7, 325; of 15 modes 1,000 x 8, 7
 // columns 155, 193.
 // split: the sums are added by the kernel that follows, so that one lane per pair is one
-// launch as well.
+// launch as well, its chain of 2 N orders against the panels of M disks (steps of solves, us,
+// one lane per pair and whole rows: one instance of 4 disks of 3 modes 24.7, 24.1, of 25 30.6,
+// 25.0, 16 of 3 modes 25.0, 26.5, of 25 32.1, 27.8; 64 x 8 of 3, 4 columns 26.2, 30.9).
 #define FEW_MARGIN 1.15
+static double lane_chain(const MatvecPlan& P) {
+  const int M = (P.few - FEW_HDR) / FEW_COL + 1;
+  return 0.5 * P.spec_N - 0.8 - 0.13 * (M - 4);
+}
+
 static bool few_applies(const mudiff_ctx* h, int R, bool split) {
   const MatvecPlan& P = h->plan;
   if (!P.few || P.lane != LANE_UNIFORM) return P.few > 0;
   const double few = R * P.few_us, lane = R * P.lane_us;
-  return FEW_MARGIN * few < lane + 4.0 || (!split && FEW_MARGIN * (few + 4.5) < lane + 9.3);
+  return FEW_MARGIN * few < lane + lane_chain(P) || (!split && FEW_MARGIN * (few + 4.5) < lane + 9.3);
 }
 
 double apply_few_us(const mudiff_ctx* h, int R) {
   if (few_applies(h, R, true)) return R * h->plan.few_us;
-  return h->plan.lane == LANE_UNIFORM ? 3.6 + R * h->plan.lane_us : 10.0;
+  if (h->plan.lane != LANE_UNIFORM) return 10.0;
+  return (h->plan.few ? 1.5 * lane_chain(h->plan) : 3.0) + R * h->plan.lane_us;
 }
 
 size_t plan_sched_bytes(const PlanHost& P, int M) {
