@@ -111,7 +111,12 @@ enum {
 /* ---------------------------------------------------------------- tables */
 
 /* Bytes of device workspace mudiff_tables needs for this batch and flags
- * (pure host computation, no device call).  Returns 0 for invalid arguments,
+ * (pure host computation, no device call).  Per instance of M disks mostly
+ * 16 bytes per order of each pair's symbols (2 (N_p + N_q) + 1 of them), 16 L M^2
+ * bytes with MUDIFF_TABLES_CIRCULANT (L the embedding length), and 64 bytes per
+ * ordered pair of records for the one-lane-per-pair kernels, whether or not an
+ * apply comes to use them: uniform orders up to 12, and batches of orders up to
+ * 31 where those kernels are the faster ones.  Returns 0 for invalid arguments,
  * including MUDIFF_TABLES_CIRCULANT with an order N_p > 31. */
 size_t mudiff_tables_workspace_size(int B, const int64_t* disk_off /*[host] B+1*/,
                                     const int32_t* n_modes /*[host] M_tot*/, int flags);
@@ -258,8 +263,8 @@ int mudiff_matvec_noalloc(mudiff_t h, int R, const void* x, void* y, int op, voi
  * handle (host outputs; any pointer may be NULL):
  *   kind       0 one lane per pair (uniform N_p <= 12, R < 8), 1 FP64-MFMA
  *              work queue (R >= 8, N_p <= 31), 2 any orders (one lane per pair
- *              in blocks of outputs for N_p <= 31 and enough disks, else the
- *              LDS-staged kernel),
+ *              in blocks of outputs for N_p <= 31 where that is the faster
+ *              one, else the LDS-staged kernel),
  *              3 circulant form on the FP64 matrix cores for the well-separated
  *              pairs and the MFMA work queue for the close ones
  *   ct, rp     MFMA tile: 8*ct right-hand sides x rp row disks per work item

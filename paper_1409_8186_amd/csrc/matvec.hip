@@ -303,10 +303,11 @@ __global__ __launch_bounds__(FEW_THREADS) void k_apply_few(
 // Uniform N_p = N (<= 12), few right-hand sides.  A wave takes a row disk p, one
 // right-hand side and a chunk of up to 64 column disks q, one
 // lane per ordered pair (p, q), with all n = 2N+1 outputs of the pair in
-// registers; a workgroup is four row disks on the same chunk, whose scaled inputs
-// it loads once, coalesced, and hands to the lanes through LDS (loaded lane by lane,
-// n entries apart, they took 25 loads of 64 cache lines each).  Each pair is read as one lane-interleaved record (H_0, H_1,
-// e^{i alpha_pq}, 2 / (k b_pq)): the orders H_nu(k b_pq), nu <= 2N, follow by
+// registers; a workgroup is one row disk, whose lanes load their inputs, or from order
+// LANE_ROWS_NMIN on four row disks on the same chunk, whose scaled inputs it loads once,
+// coalesced, and hands to the lanes through LDS (loaded lane by lane, n entries apart,
+// they take 25 loads of 64 cache lines each at order 12).  Each pair is read as one
+// lane-interleaved record (H_0, H_1, e^{i alpha_pq}, 2 / (k b_pq)): the orders H_nu(k b_pq), nu <= 2N, follow by
 // the upward recurrence H_{nu+1} = (2 nu / x) H_nu - H_{nu-1}, whose rounding
 // error stays at the level of eps |H_nu| (the growing Y part dominates |H_nu|
 // wherever the J part decays), and the phase e^{i nu alpha} by recurrence;
@@ -317,11 +318,11 @@ __global__ __launch_bounds__(FEW_THREADS) void k_apply_few(
 // stored as the chunk's partial sum; k_apply_finish adds the chunks of each
 // row in order; the two launches need no counters or memory fences.
 // Bound by FP64 issue: 3,000 vector instructions per wave at N = 12, 2.7 waves per
-// SIMD at 400 disks, so 3 rounds of 5.6 us.  us per apply, single-wave workgroups and
-// these: 400 x 12 28.2, 25.9; 700 67.9, 61.4; 1,000 120, 114; 400, 7 columns 139, 133; 48
-// x 50, 4 columns 73.5, 69.7.  Below LANE_FEW_WAVES waves a workgroup is one row (ROWS 1)
-// whose lanes load their inputs themselves: the hop through LDS would only lengthen the
-// chain (solves, ms: 50 disks 9.6, 10.0; 100 disks 16.5, 16.7; 150 disks, 450 waves, 29.2, 29.1).
+// SIMD at 400 disks, so 3 rounds of 5.6 us.  us per apply, one row per workgroup and
+// four: 400 x 12 28.2, 25.9; 700 67.9, 61.4; 1,000 120, 114; 400, 7 columns 139, 133; 48
+// x 50, 4 columns 73.5, 69.7.  Below LANE_FEW_WAVES waves the hop through LDS would only
+// lengthen the chain (solves, one and four rows, ms: 50 disks 9.6, 10.0; 100 disks 16.5, 16.7; 150 disks,
+// 450 waves, 29.2, 29.1).
 template <int N, bool OPC, int ROWS = LANE_ROWS>
 __global__ __launch_bounds__(64 * ROWS, ROWS > 1 ? 2 : 1) void k_apply_lane(
     DevView v, int R, const cplx* __restrict__ x, cplx* __restrict__ part, int64_t part_total,
@@ -1336,20 +1337,21 @@ static void mfma_build(const mudiff_ctx* h, int R, const MfmaChoice& c, MfmaSche
   // Close pairs beside the transforms and products (a fork and a join between two
   // streams): worth it while the rest lasts long enough to cover the host's 50 us for
   // six launches and four event calls, and before it fills the chip so well that the
-  // close pairs take as much from the products as they gain.  In between, by the
-  // product's operations and symbol bytes at the rates they reach and 2.2 ns per disk
-  // and column for the transforms (us in turn, beside): 200 x 16 (24 us) 53.2, 57.4; 150 x
-  // 32 (23) 52.0, 54.6; 200 x 32 (36) 61.5, 55.7; 100 x 128 (42) 70.8, 64.8; 400 x 32
-  // (115) 121, 107; 1,000 x 8 (440) 282, 271; 500 x 128 (472) 473, 450; 700 x 64 (494) 413,
-  // 414; 400 x 256 (602) 607, 617; 1,000 x 64 (947) 772, 792.
-  double us = 2.2e-3 * R * h->M_all;
+  // close pairs take as much from the products as they gain.  In between, by a score fitted to
+  // the measurements: the product's operations and symbol bytes at the rates they reach,
+  // added up though they overlap, and 2.2 ns per disk and column for the transforms (score
+  // in brackets; us in turn, beside): 200 x 16 (24) 53.2, 57.4; 150 x 32 (23) 52.0, 54.6; 200 x
+  // 32 (36) 61.5, 55.7; 100 x 128 (42) 70.8, 64.8; 400 x 32 (115) 121, 107; 1,000 x 8 (370) 282,
+  // 271; 500 x 128 (472) 473, 450; 700 x 64 (494) 413, 414; 400 x 256 (602) 607, 617; 1,000 x 64
+  // (947) 772, 792.
+  double score = 2.2e-3 * R * h->M_all;
   if (c.circ)
     for (int b = 0; b < h->B; ++b)
       if (S.con[(size_t)b]) {
         const double M = (double)(h->idisk[b + 1] - h->idisk[b]), t = h->cL[(size_t)b] * M * M;
-        us += t * (6.0 * R / 60e6 + 16.0 / 4.5e6);
+        score += t * (6.0 * R / 60e6 + 16.0 / 4.5e6);
       }
-  S.close_beside = S.close_rows && !S.crow.empty() && us >= 30.0 && us <= 500.0;
+  S.close_beside = S.close_rows && !S.crow.empty() && score >= 30.0 && score <= 500.0;
 }
 
 // Device view of a schedule's arrays.
