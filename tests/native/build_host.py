@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import concurrent.futures as cf
 import ctypes
+import fcntl
 import os
 import subprocess
 import sys
@@ -34,6 +35,12 @@ def _run(cmd: list) -> str:
 
 def build() -> str:
     os.makedirs(OUT, exist_ok=True)
+    with open(os.path.join(OUT, "lock"), "w") as lock:  # one test process at a time
+        fcntl.flock(lock, fcntl.LOCK_EX)
+        return _build()
+
+
+def _build() -> str:
     flags = [libbuild.HIPCC, f"--offload-arch={libbuild.ARCH}", "--offload-host-only", "-O1", "-std=c++17", "-fPIC",
              "-Wno-unused-result"]
 
