@@ -54,15 +54,23 @@ def test_mixed_orders_by_the_whole_batch(Ms, orders):
     check_applies([cluster(M, orders, M + i) for i, M in enumerate(Ms)], [1, 4], sample=[0, len(Ms) - 1])
 
 
-@pytest.mark.parametrize("M,orders,R", [(11, (16, 16), 1), (16, (12, 12), 2), (12, (12, 12), 1), (14, (5, 18), 1)])
-def test_cycles_on_either_side(M, orders, R):
+@pytest.mark.parametrize("B,M,orders,R", [(1, 11, (16, 16), 1), (1, 16, (12, 12), 2), (1, 12, (12, 12), 1),
+                                          (1, 14, (5, 18), 1), (1, 8, (25, 25), 1), (270, 16, (12, 12), 7)])
+def test_cycles_on_either_side(B, M, orders, R):
+    """Three kernels a step, and whole cycles in one workgroup with the basis in LDS (12 disks of order
+    12), in global memory (8 of order 25) and over several rounds of columns (270 x 16)."""
     from paper_1409_8186_amd import Problem
-    c = cluster(M, orders, M)
+    cls = [cluster(M, orders, M + b) for b in range(B)]
     betas = np.linspace(0.3, 2.0, R)
-    pr = Problem.from_cluster(c)
-    rho, flag, relres, _, _ = pr.gmres(betas=betas[None], restart=30, tol=1e-12, maxit=3000)
+    pr = Problem.from_clusters(cls)
+    rho, flag, relres, _, _ = pr.gmres(betas=np.tile(betas, (B, 1)), restart=30, tol=1e-12, maxit=3000)
     assert int(flag.abs().max()) == 0 and float(relres.max()) <= 1e-12
-    L = operator.efie_matrix(c.centers, c.radii, c.n_modes, c.k)
-    ref = solve.efie_solve_lu(L, rhs.planewave(c.centers, c.radii, c.n_modes, c.k, betas))
-    got = torch.stack(pr.split(rho, R)).cpu().numpy().reshape(R, -1)
-    assert np.linalg.norm(got - ref) < 1e-9 * np.linalg.norm(ref)  # a residual of 1e-12, condition below 1e3
+    got = pr.split(rho, R)
+    for b in {0, B // 2, B - 1}:
+        c = cls[b]
+        L = operator.efie_matrix(c.centers, c.radii, c.n_modes, c.k)
+        ref = solve.efie_solve_lu(L, rhs.planewave(c.centers, c.radii, c.n_modes, c.k, betas))
+        d = np.abs(np.diag(L))[None, :]  # in the preconditioned scaling
+        e = np.linalg.norm((got[b].cpu().numpy() - ref) * d) / np.linalg.norm(ref * d)
+        print(B, M, orders, R, b, "err %.2e" % e, flush=True)
+        assert e < 1e-9  # a residual of 1e-12, condition below 1e3

@@ -122,6 +122,7 @@ def test_kernel_of_uniform_orders(host, B, M, N, R, few):
     (uniform(1, 4, 15), 1, 30, True), (uniform(1, 12, 12), 1, 30, True),          # 22.8, 19.4
     (uniform(10, 8, 15), 4, 40, True), (batch([12] * 64, 5, 18), 7, 30, True),
     (uniform(300, 12, 12), 7, 20, True), (uniform(256, 4, 12), 7, 30, True),
+    (uniform(1, 8, 25), 1, 30, True), (uniform(270, 16, 12), 7, 30, True),
     (uniform(1, 16, 12), 1, 10, False), (uniform(1, 16, 15), 4, 10, False),       # 16.5, 21.4
     (batch([16] * 10, 5, 18), 1, 10, False), (uniform(1, 11, 16), 1, 10, False),  # 14.2, 18.1; 24.8, 29.6
     (uniform(300, 16, 1), 7, 20, False), (uniform(300, 13, 3), 7, 20, False),     # 75, 149; 93, 125
