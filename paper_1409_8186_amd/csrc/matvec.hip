@@ -2034,6 +2034,31 @@ static int lds_cols(int np, int nmax, int bt) {
   return std::max(1, std::min(APPLY_THREADS / ((np + bt - 1) / bt), cap));
 }
 
+// The same for the rows of a batch, with the passes and work items of a row in an instance of
+// M disks.  Kept by the order: set-up counts every row several times over, and the divisions
+// were most of it (set-up of 64 instances of 30 disks of orders 2 to 9, with an apply, 568 us
+// with them, 433 without; orders 13 to 20 615, 482).
+struct LdsRows {
+  struct Row {
+    int cols = 0;
+    int64_t M = 0, passes = 0, items = 0;
+  };
+  int nmax, bt;
+  std::vector<Row> rows;
+  LdsRows(int nmax_, int bt_) : nmax(nmax_), bt(bt_), rows((size_t)nmax_ + 1) {}
+  const Row& at(int N, int64_t M) {
+    Row& r = rows[(size_t)N];
+    if (r.M != M) {
+      if (r.cols == 0) r.cols = lds_cols(2 * N + 1, nmax, bt);
+      const int64_t qc = (int64_t)APPLY_NPASS * r.cols;
+      r.M = M;
+      r.passes = (M - 1 + r.cols - 1) / r.cols;
+      r.items = (M - 1 + qc - 1) / qc;
+    }
+    return r;
+  }
+};
+
 // Batches of k_apply_pairs: every N_p <= PAIRS_NMAX, and the faster one of the two by an
 // estimate.  A wave of k_apply_pairs fills its 64 lanes with the disks of one instance and
 // issues the same instructions however few they are; the LDS-staged kernel spreads one
@@ -2056,6 +2081,12 @@ bool pairs_batch(int B, const int64_t* idisk, const int32_t* N) {
   for (int64_t p = 0; p < idisk[B]; ++p) nmax = std::max(nmax, (int)N[p]);
   if (nmax > PAIRS_NMAX || !(mmax >= 24 || (mmax > FEW_DISKS && idisk[B] >= 2048))) return false;
   double passes = 0.0, wgs = 0.0, macs = 0.0, macs_span = 0.0, instr = 0.0, tasks = 0.0;
+  LdsRows rows(nmax, 4);
+  int nblk[PAIRS_NMAX + 1], wid[PAIRS_NMAX + 1];  // blocks of a row and their width, by the order
+  for (int n = 0; n <= nmax; ++n) {
+    nblk[n] = (2 * n + PAIRS_BT_WIDE) / PAIRS_BT_WIDE;
+    wid[n] = std::max((2 * n + nblk[n]) / nblk[n], 7);
+  }
   for (int b = 0; b < B; ++b) {
     const int64_t d0 = idisk[b], d1 = idisk[b + 1], M = d1 - d0;
     if (M < 2) continue;
@@ -2067,13 +2098,12 @@ bool pairs_batch(int B, const int64_t* idisk, const int32_t* N) {
     }
     const double chunks = (double)((M + LANE_CHUNK - 1) / LANE_CHUNK);
     for (int64_t p = d0; p < d1; ++p) {
-      const int np = 2 * N[p] + 1, cols = lds_cols(np, nmax, 4);
-      const int64_t items = (M - 1 + APPLY_NPASS * cols - 1) / (APPLY_NPASS * cols);
-      passes = std::max(passes, (double)((M - 1 + cols - 1) / cols));
-      wgs += (double)items;
+      const int np = 2 * N[p] + 1, blocks = nblk[N[p]], w = wid[N[p]];
+      const LdsRows::Row& r = rows.at(N[p], M);
+      passes = std::max(passes, (double)r.passes);
+      wgs += (double)r.items;
       macs += np * (sum - np);
-      if (items > 1) macs_span += np * (sum - np);
-      const int blocks = (np + PAIRS_BT_WIDE - 1) / PAIRS_BT_WIDE, w = std::max((np + blocks - 1) / blocks, 7);
+      if (r.items > 1) macs_span += np * (sum - np);
       tasks += chunks * blocks;
       instr += chunks * blocks * (2 * nb + w) * (4 * w + 12);
     }
@@ -2126,11 +2156,13 @@ static void make_pairs_plan(int B, const int64_t* idisk, const int32_t* N, int64
   }
   const int64_t K = part1 <= PAIRS_PART_MAX ? 1 : qc / LANE_CHUNK + 1;  // chunks per segment
   auto count = [&](int bt) {  // tasks of all segments with blocks of at most bt outputs
+    int blocks[PAIRS_NMAX + 1];
+    for (int o = 0; o <= nmax; ++o) blocks[o] = (2 * o + bt) / bt;
     int64_t n = 0;
     for (int b = 0; b < B; ++b) {
       const int64_t d0 = idisk[b], Mb = idisk[b + 1] - d0;
-      const int64_t nch = Mb > 1 ? (Mb + LANE_CHUNK - 1) / LANE_CHUNK : 0;
-      for (int64_t p = d0; p < d0 + Mb; ++p) n += (nch + K - 1) / K * ((2 * N[p] + bt) / bt);
+      const int64_t nch = Mb > 1 ? (Mb + LANE_CHUNK - 1) / LANE_CHUNK : 0, nseg = (nch + K - 1) / K;
+      for (int64_t p = d0; p < d0 + Mb; ++p) n += nseg * blocks[N[p]];
     }
     return n;
   };
@@ -2138,6 +2170,12 @@ static void make_pairs_plan(int B, const int64_t* idisk, const int32_t* N, int64
   const int btmax = P.wide ? PAIRS_BT_WIDE : PAIRS_BT_NARROW;
   const int64_t run = std::max<int64_t>(4, (count(btmax) + PAIRS_WGS - 1) / PAIRS_WGS);
   P.lds = (size_t)(2 * nmax + 2) * PAIRS_LD * 16;  // 66,560 bytes at PAIRS_NMAX
+  int wid[PAIRS_NMAX + 1], ntask[PAIRS_NMAX + 1];  // width and number of a row's blocks, by the order
+  for (int o = 0; o <= nmax; ++o) {
+    const int np = 2 * o + 1, nblk = (np + btmax - 1) / btmax;
+    wid[o] = pairs_width((np + nblk - 1) / nblk, P.wide);
+    ntask[o] = (np + wid[o] - 1) / wid[o];
+  }
   for (int b = 0; b < B; ++b) {
     const int64_t d0 = idisk[b], Mb = idisk[b + 1] - d0;
     const int64_t nch = Mb > 1 ? (Mb + LANE_CHUNK - 1) / LANE_CHUNK : 0, nseg = (nch + K - 1) / K;
@@ -2147,8 +2185,8 @@ static void make_pairs_plan(int B, const int64_t* idisk, const int32_t* N, int64
       P.nch[p] = (int32_t)nseg;
       P.poff[p] = P.part;
       P.part += std::max<int64_t>(nseg, 1) * np;
-      const int nblk = (np + btmax - 1) / btmax, w = pairs_width((np + nblk - 1) / nblk, P.wide);
-      if (nch > 0) P.task_total += 2 * (size_t)((np + w - 1) / w);
+      const int w = wid[N[p]];
+      if (nch > 0) P.task_total += 2 * (size_t)ntask[N[p]];
       for (int ms = 0; ms < np && nch > 0 && !P.count; ms += w) {
         P.tasks.push_back(p);
         P.tasks.push_back((ms << 8) | w);
@@ -2240,17 +2278,14 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
   P.zs = ((2 * nmax + 1) + bt - 1) / bt * bt;
   P.ts = P.zs + P.zs - 1;
   P.ppcap = std::max(1, (int)(APPLY_LDS_BUDGET / ((size_t)(P.zs + P.ts) * 16)));
-  // column disks per item of a row of np modes
-  auto cols_of = [&](int np) { return (int64_t)lds_cols(np, nmax, bt) * APPLY_NPASS; };
+  LdsRows rows(nmax, bt);
   if (pairs && pairs_batch(B, idisk, N)) {
-    make_pairs_plan(B, idisk, N, cols_of(1), P);
+    make_pairs_plan(B, idisk, N, (int64_t)lds_cols(1, nmax, bt) * APPLY_NPASS, P);
     P.row_part = 0;
     for (int b = 0; b < B; ++b) {
       const int64_t Mb = idisk[b + 1] - idisk[b];
       for (int64_t p = idisk[b]; p < idisk[b + 1]; ++p) {
-        const int np = 2 * N[p] + 1;
-        const int64_t qc = cols_of(np);
-        P.row_part += std::max<int64_t>(1, (Mb - 1 + qc - 1) / qc) * np;
+        P.row_part += std::max<int64_t>(1, rows.at(N[p], Mb).items) * (2 * N[p] + 1);
       }
     }
     return;
@@ -2260,8 +2295,8 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
     for (int64_t p = d0; p < d0 + Mb; ++p) {
       const int np = 2 * N[p] + 1;
       const int L = (np + bt - 1) / bt;
-      const int64_t qc = cols_of(np);
-      const int64_t n = std::max<int64_t>(1, (Mb - 1 + qc - 1) / qc);
+      const LdsRows::Row& r = rows.at(N[p], Mb);
+      const int64_t qc = (int64_t)APPLY_NPASS * r.cols, n = std::max<int64_t>(1, r.items);
       P.nch[p] = (int32_t)n;
       P.poff[p] = P.part;
       P.part += n * np;
@@ -2273,7 +2308,7 @@ void make_plan(int B, const int64_t* idisk, const int32_t* N, bool pairs, PlanHo
         P.items.push_back((int32_t)jb);
         P.items.push_back((int32_t)je);
       }
-      const int64_t pp = qc / APPLY_NPASS;
+      const int64_t pp = r.cols;
       P.lds = std::max(P.lds, (size_t)pp * (P.zs + P.ts) * 16);
       P.lds = std::max(P.lds, (size_t)pp * L * bt * 16);
     }

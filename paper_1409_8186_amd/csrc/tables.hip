@@ -204,10 +204,17 @@ int64_t lane_layout(int B, const int64_t* disk_off, const int32_t* n_modes, int*
     return 0;
   } else if (lord) {
     lord->resize(M);
-    for (int64_t p = 0; p < M; ++p) (*lord)[p] = (int32_t)p;
-    for (int b = 0; b < B; ++b)
-      std::stable_sort(lord->begin() + disk_off[b], lord->begin() + disk_off[b + 1],
-                       [&](int32_t u, int32_t w) { return n_modes[u] > n_modes[w]; });
+    for (int b = 0; b < B; ++b) {
+      int32_t at[PAIRS_NMAX + 1] = {0};  // disks of each order, then the place of its next one
+      for (int64_t p = disk_off[b]; p < disk_off[b + 1]; ++p) ++at[n_modes[p]];
+      int32_t o = (int32_t)disk_off[b];
+      for (int n = nmax; n >= 0; --n) {
+        const int32_t c = at[n];
+        at[n] = o;
+        o += c;
+      }
+      for (int64_t p = disk_off[b]; p < disk_off[b + 1]; ++p) (*lord)[at[n_modes[p]]++] = (int32_t)p;
+    }
   }
   const int64_t per_chunk = (int64_t)LANE_CHUNK * LANE_REC;
   int64_t o = 0;
